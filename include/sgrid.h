@@ -114,7 +114,7 @@ sgrid_status sgrid_build_packages(const sgrid_desc *desc, const float *coarse_sd
  * negative, until a round changes nothing; such cells are written as |d| with
  * that sign, and cells no diffusion reaches keep d.  `out_dev` [M^3] may be
  * `d_dev` (in place).  *rounds_out (nullable) receives the number of rounds
- * that decided a cell.  Synchronises `stream` once per 16 rounds; workspace
+ * that decided a cell.  Synchronises `stream` once per 128 rounds; workspace
  * M^3 / 2 bytes from the library's caching allocator.  M <= 4096.
  */
 sgrid_status sgrid_correct_signs(const sgrid_desc *desc, const float *d_dev, float *out_dev, void *stream,
@@ -130,8 +130,8 @@ sgrid_status sgrid_correct_signs(const sgrid_desc *desc, const float *d_dev, flo
  * same rounds of diffusion over face neighbours (positive if any decided
  * neighbour is positive, else negative) and take |phi| with it; points no
  * diffusion reaches keep phi.  *rounds_out (nullable) receives the number of
- * rounds that decided a point.  Synchronises `stream` once per 16 rounds;
- * workspace 2 bytes per point from the caching allocator.
+ * rounds that decided a point.  Synchronises `stream` once per 8 rounds;
+ * workspace 40 bytes per package from the caching allocator.
  */
 sgrid_status sgrid_correct_package_signs(const sgrid_grid *grid, sgrid_dtype dtype, void *phi_dev, void *stream,
                                          int32_t *rounds_out);
