@@ -81,12 +81,10 @@ struct Tile {
 
 // Forward pass of one 16-sample tile.  `xs(m, k0, v)` returns the 8 inputs
 // k0..k0+7 of sample m (zero past 215).  `a1`, `a2` are the wave's row-major
-// [16][128] BF16 activation tiles in LDS; `xh` (nullable) receives the BF16 hi
-// part of the inputs [16][224] for the weight gradient.  Ends with the wave's
-// LDS writes complete; callers synchronise the workgroup between phases.
+// [16][128] BF16 activation tiles in LDS.  Ends with the wave's LDS writes
+// complete; callers synchronise the workgroup between phases.
 template <class XSrc>
-__device__ __forceinline__ void forward_tile(const XSrc &xs, const MlpDev &W, bf16 *a1, bf16 *a2, bf16 *xh, Tile &T,
-                                             int lane) {
+__device__ __forceinline__ void forward_tile(const XSrc &xs, const MlpDev &W, bf16 *a1, bf16 *a2, Tile &T, int lane) {
     const int r = lane & 15, q = lane >> 4;
     // every accumulator starts from its bias (the column's hidden unit)
 #pragma unroll
@@ -104,7 +102,6 @@ __device__ __forceinline__ void forward_tile(const XSrc &xs, const MlpDev &W, bf
             ah[j] = hi;
             al[j] = (bf16)(v[j] - (float)hi);
         }
-        if (xh) *reinterpret_cast<bf16x8 *>(xh + r * kInPad + 32 * s + 8 * q) = ah;
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             const bf16x8 b = ld8(W.w1b + (16 * t + r) * kInPad + 32 * s + 8 * q);
@@ -140,12 +137,6 @@ __device__ __forceinline__ void forward_tile(const XSrc &xs, const MlpDev &W, bf
         T.y = mfma(ld8(a2 + r * kH + 32 * s + 8 * q), ld8(W.w3b + r * kH + 32 * s + 8 * q), T.y);
 }
 
-// ---------------------------------------------------------------------------
-// Training: forward + backward of 64 samples per workgroup (4 wavefronts x 16)
-// and this workgroup's partial weight gradient, written to part[blockIdx.x].
-// dY is either given (`dy_in`, [B][4]) or the gradient of the weighted
-// squared error sum_o w_o (y_o - t_o)^2 / B (`t_in`, [B][4], `lw` = w_o).
-// ---------------------------------------------------------------------------
 struct GlobalX {
     const float *x;
     int64_t base, B;
@@ -163,154 +154,274 @@ struct GlobalX {
     }
 };
 
-constexpr int kTrainRows = 64;
+// ---------------------------------------------------------------------------
+// Training, in three kernels.  A batch of a few thousand samples is little
+// work (0.3 GFLOP a step at 2048), so its time is latency: how many dependent
+// memory and LDS round trips follow each other, and over how many CUs the
+// work is spread.
+//   train_rows_kernel   forward and backward of 16 samples per workgroup;
+//   weight_grad_kernel  the weight gradients, a product over the samples,
+//                       split over output tiles and over chunks of samples;
+//   reduce_kernel       sum of the chunks in a fixed order and the Adam step.
+// One kernel with 64 samples per workgroup for the first two (32 workgroups
+// at 2048 samples) took 65 us, then 9 us for the sum, 5 us for Adam and 4 us
+// for a copy of the loss; these three take 10, 9 and 5 us.
+//
+// The first kernel hands its activations and errors to the second as BF16
+// rows of samples, one row per unit: [a1 128 | a2 128 | d1 128 | d2 128 |
+// dy 4][Bp], Bp = B rounded up to kTrainChunk (rows past B carry no error).
+// The C layout holds four consecutive samples of a unit per lane, so these
+// rows are written in 8-byte pieces, and the operands of the products over
+// the samples are 16-byte pieces of them.
+// ---------------------------------------------------------------------------
+constexpr int kTrainRows = 16;         // samples per workgroup of the first kernel
+constexpr int kTrainChunk = 64;        // samples per chunk: two MFMA steps, at least
+constexpr int kMaxChunks = 64;         // partial gradients kept
+constexpr int kActUnits = 4 * kH + kOut;
+constexpr int rA1 = 0, rA2 = kH, rD1 = 2 * kH, rD2 = 3 * kH, rDY = 4 * kH;
+constexpr int kTileSums = 8;           // per workgroup: sum of dY (4 outputs), the loss
+constexpr int kActPad = kH + 8;        // LDS row of activations, padded by 16 bytes (banks)
 
-__global__ __launch_bounds__(256) void train_kernel(MlpDev W, const float *__restrict__ x, int64_t B,
-                                                    const float *__restrict__ t_in, const float *__restrict__ dy_in,
-                                                    float4 lw, float *__restrict__ part, float *__restrict__ loss_part) {
-    __shared__ __attribute__((aligned(16))) bf16 s_xh[kTrainRows * kInPad];
-    __shared__ __attribute__((aligned(16))) bf16 s_a1[kTrainRows * kH];
-    __shared__ __attribute__((aligned(16))) bf16 s_a2[kTrainRows * kH];
-    __shared__ __attribute__((aligned(16))) bf16 s_d1[kTrainRows * kH];
-    __shared__ __attribute__((aligned(16))) bf16 s_d2[kTrainRows * kH];
-    __shared__ float s_dy[kTrainRows][kOut];
-    __shared__ float s_loss[4];
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+// Forward and backward of 16 samples: four wavefronts, each the hidden units
+// 32 w .. 32 w + 31 of every layer (two column tiles), so the chain of one
+// layer is a quarter of a wavefront's that takes all 128.  All weights and
+// inputs are requested at the start.  Every value is computed in the order of
+// forward_tile.
+__global__ __launch_bounds__(256, 1) void train_rows_kernel(MlpDev W, const float *__restrict__ x, int64_t B,
+                                                            const float *__restrict__ t_in,
+                                                            const float *__restrict__ dy_in, float4 lw,
+                                                            bf16 *__restrict__ acts, int64_t Bp,
+                                                            float *__restrict__ tile_sums) {
+    __shared__ __attribute__((aligned(16))) bf16 s_a1[kTrainRows * kActPad];
+    __shared__ __attribute__((aligned(16))) bf16 s_a2[kTrainRows * kActPad];
+    __shared__ __attribute__((aligned(16))) bf16 s_d2[kTrainRows * kActPad];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, r = lane & 15, q = lane >> 4;
-    const int64_t base = (int64_t)blockIdx.x * kTrainRows + 16 * w;
-    Tile T;
-    GlobalX xs{x, base, B};
-    forward_tile(xs, W, s_a1 + 16 * w * kH, s_a2 + 16 * w * kH, s_xh + 16 * w * kInPad, T, lane);
+    const int64_t base = (int64_t)blockIdx.x * kTrainRows;
+    constexpr int S1 = kInPad / 32, S2 = kH / 32;
+    const int n0 = 32 * w + r, n1 = n0 + 16;   // this lane's hidden units
+    float4 xa[S1], xb[S1];
+    {
+        const bool in = base + r < B;
+        const float *row = x + (in ? base + r : 0) * kIn;
+#pragma unroll
+        for (int s = 0; s < S1; ++s) {
+            const int k0 = 32 * s + 8 * q;
+            const float *p = row + (k0 < kIn ? k0 : 0);
+            xa[s] = *reinterpret_cast<const float4 *>(p);
+            xb[s] = *reinterpret_cast<const float4 *>(p + 4);
+            if (!in || k0 >= kIn) xa[s] = xb[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    }
+    bf16x8 w1[2][S1], w2[2][S2], w2t[2][S2], w3[S2];
+#pragma unroll
+    for (int s = 0; s < S1; ++s) {
+        w1[0][s] = ld8(W.w1b + n0 * kInPad + 32 * s + 8 * q);
+        w1[1][s] = ld8(W.w1b + n1 * kInPad + 32 * s + 8 * q);
+    }
+#pragma unroll
+    for (int s = 0; s < S2; ++s) {
+        w2[0][s] = ld8(W.w2b + n0 * kH + 32 * s + 8 * q);
+        w2[1][s] = ld8(W.w2b + n1 * kH + 32 * s + 8 * q);
+        w2t[0][s] = ld8(W.w2tb + n0 * kH + 32 * s + 8 * q);
+        w2t[1][s] = ld8(W.w2tb + n1 * kH + 32 * s + 8 * q);
+        w3[s] = ld8(W.w3b + r * kH + 32 * s + 8 * q);
+    }
+    const float b1[2] = {W.w[oB1 + n0], W.w[oB1 + n1]}, b2[2] = {W.w[oB2 + n0], W.w[oB2 + n1]};
+    const float b3 = r < kOut ? W.w[oB3 + r] : 0.f;
+    float w3f[2][kOut];
+#pragma unroll
+    for (int o = 0; o < kOut; ++o) {
+        w3f[0][o] = W.w[oW3 + o * kH + n0];
+        w3f[1][o] = W.w[oW3 + o * kH + n1];
+    }
+    float dy[4], lsum = 0.f;   // targets, then errors, of the samples 4q .. 4q + 3, output r
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t m = base + 4 * q + i;
+        dy[i] = r < kOut && m < B ? (dy_in ? dy_in : t_in)[m * kOut + r] : 0.f;
+    }
 
-    // dY (rows past B contribute nothing)
-    float lsum = 0.f;
-    if (r < kOut) {
+    floatx4 z1[2], z2[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        z1[c] = floatx4{b1[c], b1[c], b1[c], b1[c]};
+        z2[c] = floatx4{b2[c], b2[c], b2[c], b2[c]};
+    }
+#pragma unroll
+    for (int s = 0; s < S1; ++s) {
+        const float v[8] = {xa[s].x, xa[s].y, xa[s].z, xa[s].w, xb[s].x, xb[s].y, xb[s].z, xb[s].w};
+        bf16x8 ah, al;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const bf16 hi = (bf16)v[j];
+            ah[j] = hi;
+            al[j] = (bf16)(v[j] - (float)hi);
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            z1[c] = mfma(ah, w1[c][s], z1[c]);
+            z1[c] = mfma(al, w1[c][s], z1[c]);
+        }
+    }
+    // four consecutive samples of one unit: to the unit's row, and (for the
+    // next layer's A operand) to the samples' rows in LDS
+    auto hand_on = [&](const float (&v)[4], int unit, int row0, bf16 *lds) {
+        bf16x4 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            o[i] = (bf16)v[i];
+            if (lds) lds[(4 * q + i) * kActPad + unit] = o[i];
+        }
+        *reinterpret_cast<bf16x4 *>(acts + (int64_t)(row0 + unit) * Bp + base + 4 * q) = o;
+    };
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const float g[4] = {gelu(z1[c][0]), gelu(z1[c][1]), gelu(z1[c][2]), gelu(z1[c][3])};
+        hand_on(g, c ? n1 : n0, rA1, s_a1);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < S2; ++s) {
+        const bf16x8 a = ld8(s_a1 + r * kActPad + 32 * s + 8 * q);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) z2[c] = mfma(a, w2[c][s], z2[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const float g[4] = {gelu(z2[c][0]), gelu(z2[c][1]), gelu(z2[c][2]), gelu(z2[c][3])};
+        hand_on(g, c ? n1 : n0, rA2, s_a2);
+    }
+    __syncthreads();
+    // every wavefront takes the output layer, so that each has dY
+    floatx4 y = floatx4{b3, b3, b3, b3};
+#pragma unroll
+    for (int s = 0; s < S2; ++s) y = mfma(ld8(s_a2 + r * kActPad + 32 * s + 8 * q), w3[s], y);
+    if (dy_in == nullptr) {
         const float wo = r == 0 ? lw.x : (r == 1 ? lw.y : (r == 2 ? lw.z : lw.w));
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int64_t s = base + 4 * q + i;
-            float d = 0.f;
-            if (s < B) {
-                if (dy_in) {
-                    d = dy_in[s * kOut + r];
-                } else {
-                    const float e = T.y[i] - t_in[s * kOut + r];
-                    lsum += wo * e * e;
-                    d = 2.0f * wo * e / (float)B;
-                }
-            }
-            s_dy[16 * w + 4 * q + i][r] = d;
+            const float e = y[i] - dy[i];
+            const bool in = r < kOut && base + 4 * q + i < B;   // rows past B contribute nothing
+            lsum += in ? wo * e * e : 0.f;
+            dy[i] = in ? 2.0f * wo * e / (float)B : 0.f;
         }
     }
-    // wave-level loss sum
-    for (int off = 32; off > 0; off >>= 1) lsum += __shfl_down(lsum, off);
-    if (lane == 0) s_loss[w] = lsum;
-    __syncthreads();
-
-    // dA2 = dY W3 (K = 4, FP32 masters), dZ2 = dA2 * gelu'(z2)
+    if (w == 0) {
+        float v = r < kOut ? dy[0] + dy[1] + dy[2] + dy[3] : 0.f;
+        v += __shfl_xor(v, 16);
+        v += __shfl_xor(v, 32);
+        if (lane < kOut) tile_sums[(int64_t)blockIdx.x * kTileSums + lane] = v;
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        const int n = 16 * t + r;
-        const float w0 = W.w[oW3 + n], w1 = W.w[oW3 + kH + n], w2 = W.w[oW3 + 2 * kH + n], w3 = W.w[oW3 + 3 * kH + n];
+        for (int off = 32; off > 0; off >>= 1) lsum += __shfl_down(lsum, off);
+        if (lane == 0) tile_sums[(int64_t)blockIdx.x * kTileSums + kOut] = lsum;
+        if (r < kOut) hand_on(dy, r, rDY, nullptr);
+    }
+    // dA2 = dY W3 (K = 4, FP32 masters), dZ2 = dA2 * gelu'(z2)
+    {
+        float d[2][4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float *d = s_dy[16 * w + 4 * q + i];
-            const float da = d[0] * w0 + d[1] * w1 + d[2] * w2 + d[3] * w3;
-            s_d2[(16 * w + 4 * q + i) * kH + n] = (bf16)(da * gelu_grad(T.z2[t][i]));
+            const float d0 = __shfl(dy[i], 16 * q), d1 = __shfl(dy[i], 16 * q + 1), d2 = __shfl(dy[i], 16 * q + 2),
+                        d3 = __shfl(dy[i], 16 * q + 3);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const float da = d0 * w3f[c][0] + d1 * w3f[c][1] + d2 * w3f[c][2] + d3 * w3f[c][3];
+                d[c][i] = da * gelu_grad(z2[c][i]);
+            }
         }
+        hand_on(d[0], n0, rD2, s_d2);
+        hand_on(d[1], n1, rD2, s_d2);
     }
     __syncthreads();
     // dA1 = dZ2 W2 (B operand from the transposed copy), dZ1 = dA1 * gelu'(z1)
-    {
-        floatx4 acc[8];
+    floatx4 acc[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-        for (int t = 0; t < 8; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-        const bf16 *d2 = s_d2 + 16 * w * kH;
+    for (int s = 0; s < S2; ++s) {
+        const bf16x8 a = ld8(s_d2 + r * kActPad + 32 * s + 8 * q);
 #pragma unroll
-        for (int s = 0; s < kH / 32; ++s) {
-            const bf16x8 a = ld8(d2 + r * kH + 32 * s + 8 * q);
-#pragma unroll
-            for (int t = 0; t < 8; ++t) acc[t] = mfma(a, ld8(W.w2tb + (16 * t + r) * kH + 32 * s + 8 * q), acc[t]);
-        }
-#pragma unroll
-        for (int t = 0; t < 8; ++t)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                s_d1[(16 * w + 4 * q + i) * kH + 16 * t + r] = (bf16)(acc[t][i] * gelu_grad(T.z1[t][i]));
+        for (int c = 0; c < 2; ++c) acc[c] = mfma(a, w2t[c][s], acc[c]);
     }
-    __syncthreads();
-
-    // Weight gradients over the 64 rows: C[o][i] = sum_m D[m][o] S[m][i], with
-    // A[o][m] gathered from column o of D and B[m][i] from column i of S.
-    float *P = part + (int64_t)blockIdx.x * kNParam;
-    const int n_w1 = 8 * (kInPad / 16), n_w2 = 64, n_w3 = 8;
-    for (int tile = w; tile < n_w1 + n_w2 + n_w3; tile += 4) {
-        const bf16 *D, *S;
-        int sl, ot, it, obase, ostride, omax, imax;
-        if (tile < n_w1) {
-            D = s_d1; S = s_xh; sl = kInPad; ot = tile / (kInPad / 16); it = tile % (kInPad / 16);
-            obase = oW1; ostride = kIn; omax = kH; imax = kIn;
-        } else if (tile < n_w1 + n_w2) {
-            const int u = tile - n_w1;
-            D = s_d2; S = s_a1; sl = kH; ot = u / 8; it = u % 8;
-            obase = oW2; ostride = kH; omax = kH; imax = kH;
-        } else {
-            D = nullptr; S = s_a2; sl = kH; ot = 0; it = tile - n_w1 - n_w2;
-            obase = oW3; ostride = kH; omax = kOut; imax = kH;
-        }
-        floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ks = 0; ks < kTrainRows / 32; ++ks) {
-            bf16x8 a, b;
+    for (int c = 0; c < 2; ++c) {
+        float d[4];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int m = 32 * ks + 8 * q + j;
-                const int o = 16 * ot + r;
-                a[j] = D ? D[m * kH + o] : (o < kOut ? (bf16)s_dy[m][o] : (bf16)0.f);
-                b[j] = S[m * sl + 16 * it + r];
-            }
-            acc = mfma(a, b, acc);
-        }
-        const int i = 16 * it + r;
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const int o = 16 * ot + 4 * q + jj;
-            if (o < omax && i < imax) P[obase + o * ostride + i] = acc[jj];
-        }
+        for (int i = 0; i < 4; ++i) d[i] = acc[c][i] * gelu_grad(z1[c][i]);
+        hand_on(d, c ? n1 : n0, rD1, nullptr);
     }
-    // bias gradients: column sums of dZ1, dZ2 (BF16 tiles) and dY (FP32)
-    if (threadIdx.x < kH) {
-        const int o = threadIdx.x;
-        float s1 = 0.f, s2 = 0.f;
-        for (int m = 0; m < kTrainRows; ++m) {
-            s1 += (float)s_d1[m * kH + o];
-            s2 += (float)s_d2[m * kH + o];
-        }
-        P[oB1 + o] = s1;
-        P[oB2 + o] = s2;
-    } else if (threadIdx.x < kH + kOut) {
-        const int o = threadIdx.x - kH;
-        float s3 = 0.f;
-        for (int m = 0; m < kTrainRows; ++m) s3 += s_dy[m][o];
-        P[oB3 + o] = s3;
-    }
-    if (threadIdx.x == 0) loss_part[blockIdx.x] = s_loss[0] + s_loss[1] + s_loss[2] + s_loss[3];
 }
 
-// grad[p] = sum over workgroups of part[wg][p], in workgroup order (deterministic).
-__global__ __launch_bounds__(256) void reduce_kernel(const float *__restrict__ part, int n_part,
-                                                     float *__restrict__ grad, const float *__restrict__ loss_part,
-                                                     float *__restrict__ loss_out) {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p < kNParam) {
-        float s = 0.f;
-        for (int g = 0; g < n_part; ++g) s += part[(int64_t)g * kNParam + p];
-        grad[p] = s;
+// Weight gradients C[o][i] = sum over a chunk's samples of D[m][o] S[m][i].
+// One wavefront per column tile of 16 inputs i and chunk: it reads its B
+// operand once and the eight A operands of all 128 outputs (roles 0..13: W1,
+// whose inputs are x rounded to BF16 and whose column 216 is the constant 1,
+// the bias; 14..21: W2; 22: W3, one A and eight B operands; 23: b2, with the
+// constant 1 as its only input).
+constexpr int kRolesW1 = kInPad / 16, kRolesW2 = kH / 16, kRoles = kRolesW1 + kRolesW2 + 2;
+static_assert(kRoles % 4 == 0 && kInPad > kIn, "four roles per workgroup; a padding column for the bias");
+
+__global__ __launch_bounds__(256) void weight_grad_kernel(const float *__restrict__ x, int64_t B,
+                                                          const bf16 *__restrict__ acts, int64_t Bp, int steps,
+                                                          float *__restrict__ part) {
+    const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+    const int role = (int)(blockIdx.x % (kRoles / 4)) * 4 + (threadIdx.x >> 6);
+    const int64_t chunk = blockIdx.x / (kRoles / 4);
+    const int64_t first = chunk * steps * 32;
+    float *P = part + chunk * kNParam;
+    floatx4 acc[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 zero;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) zero[j] = (bf16)0.f;
+    const bool is_w1 = role < kRolesW1, is_w2 = !is_w1 && role < kRolesW1 + kRolesW2, is_w3 = role == kRoles - 2;
+    const int it = is_w1 ? role : role - kRolesW1;
+    const int col = 16 * it + r;
+    const bf16 *rows8 = acts + (int64_t)((is_w1 ? rD1 : (is_w3 ? rA2 : rD2)) + r) * Bp;   // eight tiles' operands
+    const bf16 *row1 = acts + (int64_t)(is_w3 ? rDY + (r < kOut ? r : 0) : rA1 + (is_w2 ? col : 0)) * Bp;
+    for (int s = 0; s < steps; ++s) {
+        const int64_t m0 = first + 32 * s + 8 * q;
+        if (first + 32 * s >= Bp) break;   // the same for the whole wavefront
+        bf16x8 one;
+        if (is_w1) {
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int64_t m = m0 + j < B ? m0 + j : B - 1;   // rows past B meet d1 = 0
+                v[j] = x[m * kIn + (col < kIn ? col : 0)];
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) one[j] = (bf16)(m0 + j >= B ? 0.f : (col < kIn ? v[j] : (col == kIn ? 1.f : 0.f)));
+        } else if (is_w2 || is_w3) {
+            one = ld8(row1 + m0);
+            if (is_w3 && r >= kOut) one = zero;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) one[j] = (bf16)(r == 0 ? 1.f : 0.f);
+        }
+        bf16x8 many[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) many[t] = ld8(rows8 + (int64_t)(16 * t) * Bp + m0);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc[t] = is_w3 ? mfma(one, many[t], acc[t]) : mfma(many[t], one, acc[t]);
     }
-    if (p == 0 && loss_out) {
-        float s = 0.f;
-        for (int g = 0; g < n_part; ++g) s += loss_part[g];
-        *loss_out = s;
-    }
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int o = 16 * t + 4 * q + j;   // output (W1, W2, b2)
+            if (is_w1) {
+                if (col < kIn) P[oW1 + o * kIn + col] = acc[t][j];
+                if (col == kIn) P[oB1 + o] = acc[t][j];
+            } else if (is_w2) {
+                P[oW2 + o * kH + col] = acc[t][j];
+            } else if (is_w3) {
+                if (4 * q + j < kOut) P[oW3 + (4 * q + j) * kH + 16 * t + r] = acc[t][j];
+            } else if (r == 0) {
+                P[oB2 + o] = acc[t][j];
+            }
+        }
 }
 
 // Refresh the BF16 operand copies of parameter p from the FP32 master.
@@ -334,20 +445,70 @@ __global__ __launch_bounds__(256) void sync_copies_kernel(const float *__restric
     if (p < kNParam) write_bf16_copy(p, w[p], w1b, w2b, w2tb, w3b);
 }
 
+struct AdamArgs {
+    float *w, *m, *v;
+    float lr, b1, b2, eps, c1, c2;
+    bf16 *w1b, *w2b, *w2tb, *w3b;
+};
+
 // Adam (Kingma & Ba 2015) with bias correction, then the BF16 copies.
-__global__ __launch_bounds__(256) void adam_kernel(float *__restrict__ w, float *__restrict__ m, float *__restrict__ v,
-                                                   const float *__restrict__ g, float lr, float b1, float b2, float eps,
-                                                   float c1, float c2, bf16 *w1b, bf16 *w2b, bf16 *w2tb, bf16 *w3b) {
+__device__ __forceinline__ void adam_update(const AdamArgs &A, int p, float gp) {
+    const float mp = A.b1 * A.m[p] + (1.0f - A.b1) * gp;
+    const float vp = A.b2 * A.v[p] + (1.0f - A.b2) * gp * gp;
+    A.m[p] = mp;
+    A.v[p] = vp;
+    const float wp = A.w[p] - A.lr * (mp / A.c1) / (sqrtf(vp / A.c2) + A.eps);
+    A.w[p] = wp;
+    write_bf16_copy(p, wp, A.w1b, A.w2b, A.w2tb, A.w3b);
+}
+
+__global__ __launch_bounds__(256) void adam_kernel(AdamArgs A, const float *__restrict__ g) {
     const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= kNParam) return;
-    const float gp = g[p];
-    const float mp = b1 * m[p] + (1.0f - b1) * gp;
-    const float vp = b2 * v[p] + (1.0f - b2) * gp * gp;
-    m[p] = mp;
-    v[p] = vp;
-    const float wp = w[p] - lr * (mp / c1) / (sqrtf(vp / c2) + eps);
-    w[p] = wp;
-    write_bf16_copy(p, wp, w1b, w2b, w2tb, w3b);
+    if (p < kNParam) adam_update(A, p, g[p]);
+}
+
+// Gradient of parameter p = sum over the chunks of part[c][p], in chunk order
+// (deterministic); written to `grad`, or given to Adam at once.  The last
+// workgroup takes the output biases and the loss from the tiles' sums.
+constexpr int kReduceBlocks = (oB3 + 255) / 256 + 1;
+
+template <bool ADAM>
+__global__ __launch_bounds__(256) void reduce_kernel(const float *__restrict__ part, int n_part,
+                                                     const float *__restrict__ tile_sums, int64_t n_tiles,
+                                                     float *__restrict__ grad, AdamArgs A,
+                                                     float *__restrict__ loss_out) {
+    if (blockIdx.x == kReduceBlocks - 1) {
+        // lanes 8 k + c of 256: column c of the tiles k, k + 32, ...; the 32
+        // partial sums of a column are added in order
+        __shared__ float s[256];
+        const int c = threadIdx.x & (kTileSums - 1);
+        float v = 0.f;
+        if (c <= kOut)
+            for (int64_t k = threadIdx.x / kTileSums; k < n_tiles; k += 256 / kTileSums) v += tile_sums[k * kTileSums + c];
+        s[threadIdx.x] = v;
+        __syncthreads();
+        if (threadIdx.x > kOut) return;
+        v = 0.f;
+        for (int k = 0; k < 256 / kTileSums; ++k) v += s[k * kTileSums + c];
+        if (c < kOut) {
+            if (ADAM)
+                adam_update(A, oB3 + c, v);
+            else
+                grad[oB3 + c] = v;
+        } else if (loss_out) {
+            *loss_out = v;
+        }
+        return;
+    }
+    const int p = blockIdx.x * 256 + threadIdx.x;
+    if (p >= oB3) return;
+    float s = 0.f;
+#pragma unroll 8
+    for (int g = 0; g < n_part; ++g) s += part[(int64_t)g * kNParam + p];
+    if (ADAM)
+        adam_update(A, p, s);
+    else
+        grad[p] = s;
 }
 
 // Forward only, for [B][216] inputs.
@@ -358,7 +519,7 @@ __global__ __launch_bounds__(256) void forward_kernel(MlpDev W, const float *__r
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, r = lane & 15, q = lane >> 4;
     const int64_t base = (int64_t)blockIdx.x * 64 + 16 * w;
     Tile T;
-    forward_tile(GlobalX{x, base, B}, W, s_a1 + 16 * w * kH, s_a2 + 16 * w * kH, nullptr, T, lane);
+    forward_tile(GlobalX{x, base, B}, W, s_a1 + 16 * w * kH, s_a2 + 16 * w * kH, T, lane);
     if (r < kOut)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -374,11 +535,13 @@ __global__ __launch_bounds__(256) void forward_kernel(MlpDev W, const float *__r
 // ---------------------------------------------------------------------------
 struct sgrid_mlp {
     int device = 0;
-    float *w = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr, *loss = nullptr;
+    float *w = nullptr, *m = nullptr, *v = nullptr;
     bf16 *w1b = nullptr, *w2b = nullptr, *w2tb = nullptr, *w3b = nullptr;
-    float *part = nullptr;        // training partial gradients
-    float *loss_part = nullptr;
-    int64_t part_rows = 0;        // workgroups the partial buffers hold
+    // training workspace: partial gradients [chunk][parameter], the tiles'
+    // sums and the rows of activations and errors, for up to train_rows samples
+    float *part = nullptr, *tile_sums = nullptr;
+    bf16 *acts = nullptr;
+    int64_t train_rows = 0;
     int64_t step = 0;
     float gate_tau = FLT_MAX;     // non-planarity threshold (mean squared residual, units of h^2)
     float kw_lo = -0.05f, kw_hi = 1.05f;
@@ -396,8 +559,7 @@ namespace sgrid {
 
 static void free_mlp(sgrid_mlp *m) {
     if (!m) return;
-    void *ptrs[] = {m->w, m->m, m->v, m->grad, m->loss, m->w1b, m->w2b, m->w2tb, m->w3b, m->part, m->loss_part,
-                    m->fallback};
+    void *ptrs[] = {m->w, m->m, m->v, m->w1b, m->w2b, m->w2tb, m->w3b, m->part, m->tile_sums, m->acts, m->fallback};
     for (void *p : ptrs) dev_free(p);
     if (m->done) (void)hipEventDestroy(m->done);
     delete m;
@@ -423,19 +585,38 @@ static sgrid_status end_use(const sgrid_mlp *mc, hipStream_t st) {
 // Growing a buffer frees the old block, which kernels queued by earlier calls
 // (on any stream) may still use: wait for the device before handing it back
 // to the allocator, which may give it to the next request of that size.
-static sgrid_status ensure_part(sgrid_mlp *m, int64_t rows) {
-    if (rows <= m->part_rows) return SGRID_OK;
-    if (m->part || m->loss_part) SG_CHECK_HIP(hipDeviceSynchronize());
+// How a batch is split: rounded up to whole chunks of kTrainChunk samples, at
+// most kMaxChunks of them (then longer ones).
+struct TrainSplit {
+    int64_t rows, tiles;
+    int chunks, steps;
+    explicit TrainSplit(int64_t B) {
+        const int64_t units = (B + kTrainChunk - 1) / kTrainChunk;
+        const int64_t per = (units + kMaxChunks - 1) / kMaxChunks;
+        rows = units * kTrainChunk;
+        tiles = rows / kTrainRows;
+        chunks = (int)((units + per - 1) / per);
+        steps = (int)(per * (kTrainChunk / 32));
+    }
+};
+
+static sgrid_status ensure_train(sgrid_mlp *m, const TrainSplit &t) {
+    if (t.rows <= m->train_rows) return SGRID_OK;
+    if (m->part || m->tile_sums || m->acts) SG_CHECK_HIP(hipDeviceSynchronize());
     dev_free(m->part);
-    dev_free(m->loss_part);
-    m->part = nullptr;
-    m->loss_part = nullptr;
-    m->part_rows = 0;
-    sgrid_status s = dev_alloc((void **)&m->part, (size_t)rows * kNParam * 4, "MLP partial gradients");
+    dev_free(m->tile_sums);
+    dev_free(m->acts);
+    m->part = m->tile_sums = nullptr;
+    m->acts = nullptr;
+    m->train_rows = 0;
+    const int64_t chunks = std::min<int64_t>(t.rows / kTrainChunk, kMaxChunks);
+    sgrid_status s = dev_alloc((void **)&m->part, (size_t)chunks * kNParam * 4, "MLP partial gradients");
     if (s != SGRID_OK) return s;
-    s = dev_alloc((void **)&m->loss_part, (size_t)rows * 4, "MLP partial losses");
+    s = dev_alloc((void **)&m->tile_sums, (size_t)t.tiles * kTileSums * 4, "MLP partial losses");
     if (s != SGRID_OK) return s;
-    m->part_rows = rows;
+    s = dev_alloc((void **)&m->acts, (size_t)t.rows * kActUnits * sizeof(bf16), "MLP activations");
+    if (s != SGRID_OK) return s;
+    m->train_rows = t.rows;
     return SGRID_OK;
 }
 
@@ -451,16 +632,22 @@ sgrid_status mlp_ensure_fallback(sgrid_mlp *m, int64_t cells) {
     return SGRID_OK;
 }
 
+// Forward, backward and weight gradients of a batch; the gradient goes to
+// `grad` (ADAM false) or into an Adam step (ADAM true).
+template <bool ADAM>
 static sgrid_status run_backward(sgrid_mlp *m, const float *x, int64_t B, const float *t, const float *dy,
-                                 const float lw[4], hipStream_t st) {
-    const int64_t nwg = (B + kTrainRows - 1) / kTrainRows;
-    sgrid_status s = ensure_part(m, nwg);
+                                 const float lw[4], float *grad, const AdamArgs &A, float *loss, hipStream_t st) {
+    const TrainSplit sp(B);
+    sgrid_status s = ensure_train(m, sp);
     if (s != SGRID_OK) return s;
-    hipLaunchKernelGGL(train_kernel, dim3((unsigned)nwg), dim3(256), 0, st, m->dev(), x, B, t, dy,
-                       make_float4(lw[0], lw[1], lw[2], lw[3]), m->part, m->loss_part);
-    SG_CHECK_LAUNCH("MLP train kernel");
-    hipLaunchKernelGGL(reduce_kernel, dim3((kNParam + 255) / 256), dim3(256), 0, st, m->part, (int)nwg, m->grad,
-                       m->loss_part, m->loss);
+    hipLaunchKernelGGL(train_rows_kernel, dim3((unsigned)sp.tiles), dim3(256), 0, st, m->dev(), x, B, t, dy,
+                       make_float4(lw[0], lw[1], lw[2], lw[3]), m->acts, sp.rows, m->tile_sums);
+    SG_CHECK_LAUNCH("MLP forward and backward");
+    hipLaunchKernelGGL(weight_grad_kernel, dim3((unsigned)(sp.chunks * (kRoles / 4))), dim3(256), 0, st, x, B, m->acts,
+                       sp.rows, sp.steps, m->part);
+    SG_CHECK_LAUNCH("MLP weight gradient");
+    hipLaunchKernelGGL(reduce_kernel<ADAM>, dim3(kReduceBlocks), dim3(256), 0, st, m->part, sp.chunks, m->tile_sums,
+                       sp.tiles, grad, A, loss);
     SG_CHECK_LAUNCH("MLP gradient reduction");
     return SGRID_OK;
 }
@@ -481,7 +668,6 @@ extern "C" sgrid_status sgrid_mlp_create(const float *params_host, sgrid_mlp **o
     }
     struct A { void **p; size_t bytes; };
     A allocs[] = {{(void **)&m->w, kNParam * 4}, {(void **)&m->m, kNParam * 4}, {(void **)&m->v, kNParam * 4},
-                  {(void **)&m->grad, kNParam * 4}, {(void **)&m->loss, 4},
                   {(void **)&m->w1b, kH * kInPad * 2}, {(void **)&m->w2b, kH * kH * 2},
                   {(void **)&m->w2tb, kH * kH * 2}, {(void **)&m->w3b, 16 * kH * 2}};
     for (auto &a : allocs) {
@@ -578,32 +764,27 @@ extern "C" sgrid_status sgrid_mlp_backward(sgrid_mlp *m, const float *x, const f
     SG_REQUIRE(B >= 1, "B must be >= 1");
     SG_REQUIRE(x && dy && grad && sg_aligned(x, 16) && sg_aligned(dy, 16) && sg_aligned(grad, 4),
                "x / dy / grad NULL or misaligned");
-    SG_REQUIRE((B + kTrainRows - 1) / kTrainRows <= kMaxGrid, "batch too large");
+    SG_REQUIRE((B + 63) / 64 <= kMaxGrid, "batch too large");
     hipStream_t st = sg_stream(stream);
     sgrid_status s = sgrid::begin_use(m, st);
     if (s != SGRID_OK) return s;
     const float lw[4] = {0, 0, 0, 0};
-    s = sgrid::run_backward(m, x, B, nullptr, dy, lw, st);
+    s = sgrid::run_backward<false>(m, x, B, nullptr, dy, lw, grad, AdamArgs{}, nullptr, st);
     if (s != SGRID_OK) return s;
-    SG_CHECK_HIP(hipMemcpyAsync(grad, m->grad, kNParam * 4, hipMemcpyDeviceToDevice, st));
     return sgrid::end_use(m, st);
 }
 
 namespace sgrid {
 
-// One Adam step on the model's masters from the gradient in `g` (device,
-// kNParam values), then the BF16 copies.  The decay rates are the FP32
-// numbers nearest 0.9 and 0.999, and the bias corrections 1 - beta^t use
-// those same numbers, so the step is Adam with these rates.
-static sgrid_status adam_step(sgrid_mlp *m, const float *g, float lr, hipStream_t st) {
+// The model's next Adam step.  The decay rates are the FP32 numbers nearest
+// 0.9 and 0.999, and the bias corrections 1 - beta^t use those same numbers,
+// so the step is Adam with these rates.
+static AdamArgs next_adam(sgrid_mlp *m, float lr) {
     m->step += 1;
     const float b1 = 0.9f, b2 = 0.999f;
     const float c1 = (float)(1.0 - pow((double)b1, (double)m->step));
     const float c2 = (float)(1.0 - pow((double)b2, (double)m->step));
-    hipLaunchKernelGGL(adam_kernel, dim3((kNParam + 255) / 256), dim3(256), 0, st, m->w, m->m, m->v, g, lr,
-                       b1, b2, 1e-8f, c1, c2, m->w1b, m->w2b, m->w2tb, m->w3b);
-    SG_CHECK_LAUNCH("Adam");
-    return SGRID_OK;
+    return AdamArgs{m->w, m->m, m->v, lr, b1, b2, 1e-8f, c1, c2, m->w1b, m->w2b, m->w2tb, m->w3b};
 }
 
 }  // namespace sgrid
@@ -615,15 +796,17 @@ extern "C" sgrid_status sgrid_mlp_train_step(sgrid_mlp *m, const float *x, const
     SG_REQUIRE(B >= 1, "B must be >= 1");
     SG_REQUIRE(x && t && loss_weights && sg_aligned(x, 16) && sg_aligned(t, 16), "x / t / weights NULL or misaligned");
     SG_REQUIRE(lr >= 0.f, "lr must be >= 0");
-    SG_REQUIRE((B + kTrainRows - 1) / kTrainRows <= kMaxGrid, "batch too large");
+    SG_REQUIRE((B + 63) / 64 <= kMaxGrid, "batch too large");
     hipStream_t st = sg_stream(stream);
     sgrid_status s = sgrid::begin_use(m, st);
     if (s != SGRID_OK) return s;
-    s = sgrid::run_backward(m, x, B, t, nullptr, loss_weights, st);
+    s = sgrid::ensure_train(m, sgrid::TrainSplit(B));   // before the step counts
     if (s != SGRID_OK) return s;
-    s = sgrid::adam_step(m, m->grad, lr, st);
-    if (s != SGRID_OK) return s;
-    if (loss_dev) SG_CHECK_HIP(hipMemcpyAsync(loss_dev, m->loss, 4, hipMemcpyDeviceToDevice, st));
+    s = sgrid::run_backward<true>(m, x, B, t, nullptr, loss_weights, nullptr, sgrid::next_adam(m, lr), loss_dev, st);
+    if (s != SGRID_OK) {
+        m->step -= 1;
+        return s;
+    }
     return sgrid::end_use(m, st);
 }
 
@@ -635,8 +818,8 @@ extern "C" sgrid_status sgrid_mlp_apply_gradient(sgrid_mlp *m, const float *grad
     hipStream_t st = sg_stream(stream);
     sgrid_status s = sgrid::begin_use(m, st);
     if (s != SGRID_OK) return s;
-    s = sgrid::adam_step(m, grad_dev, lr, st);
-    if (s != SGRID_OK) return s;
+    hipLaunchKernelGGL(adam_kernel, dim3((kNParam + 255) / 256), dim3(256), 0, st, sgrid::next_adam(m, lr), grad_dev);
+    SG_CHECK_LAUNCH("Adam");
     return sgrid::end_use(m, st);
 }
 
