@@ -95,7 +95,7 @@ int32_t sgrid_version(void);
  * but one of its 26 neighbours is; both are activated and numbered 2.. in
  * ascending linear order; every other cell maps to far field 0 (d < 0) or 1.
  * The result is bit-identical for identical inputs.  On success *out owns the
- * tables until sgrid_destroy.  Synchronises `stream` once (to learn P); the
+ * tables until sgrid_destroy.  Waits on the host once (to learn P); the
  * tables are complete when `stream` reaches the end of the call, so work on
  * other streams must wait for it.  Memory comes from the library's caching
  * allocator (blocks of destroyed grids are reused).

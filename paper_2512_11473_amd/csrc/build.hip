@@ -8,7 +8,7 @@
 //                   one ballot each;
 //   dilate_kernel   one lane per word: activated = core dilated by one cell in
 //                   x, y, z (word shifts and ORs); per-group counts;
-//   scan_pair       exclusive scan of the counts (block sums, one workgroup
+//   scan_counts     exclusive scan of the counts (block sums, one workgroup
 //                   over them, block scans);
 //   (host)          read back P and n_core once, allocate the package tables;
 //   scatter_kernel  16 words per wavefront in steps of four, four cells per lane: rank by
@@ -241,152 +241,154 @@ __global__ __launch_bounds__(256) void dilate_kernel(const uint64_t *__restrict_
     }
 }
 
-// Exclusive scan of two count arrays in three passes: per-block sums of
-// kScanBlock entries, one workgroup scanning the block sums (and writing the
-// totals), then every block scanning its entries from its offset.
+// Exclusive scan of one or two count arrays (N) in three passes: per-block
+// sums of kScanBlock entries, one workgroup scanning the block sums (and
+// writing the totals), then every block scanning its entries from its offset.
+// Few counts take the one workgroup alone.
 constexpr int kScanThreads = 1024;
 constexpr int kScanTile = kScanThreads * 4;
 constexpr int kScanBlock = 1024;   // entries per block of the first and last pass (256 lanes x 4)
 
-__global__ __launch_bounds__(256) void scan_reduce_kernel(const uint32_t *__restrict__ a, const uint32_t *__restrict__ b,
-                                                          int64_t n, uint32_t *__restrict__ sa,
-                                                          uint32_t *__restrict__ sb) {
-    __shared__ uint32_t ra[4], rb[4];
+template <int N>
+struct Counts {
+    uint32_t *p[N];
+};
+
+template <int N>
+__global__ __launch_bounds__(256) void scan_reduce_kernel(Counts<N> a, int64_t n, Counts<N> sums) {
+    __shared__ uint32_t ra[N][4];
     const int64_t base = (int64_t)blockIdx.x * kScanBlock + threadIdx.x * 4;
-    uint32_t xa = 0, xb = 0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-        if (base + k < n) {
-            xa += a[base + k];
-            xb += b[base + k];
-        }
+    for (int c = 0; c < N; ++c) {
+        uint32_t x = 0;
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        xa += __shfl_xor(xa, off);
-        xb += __shfl_xor(xb, off);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        ra[threadIdx.x >> 6] = xa;
-        rb[threadIdx.x >> 6] = xb;
+        for (int k = 0; k < 4; ++k)
+            if (base + k < n) x += a.p[c][base + k];
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
+        if ((threadIdx.x & 63) == 0) ra[c][threadIdx.x >> 6] = x;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        sa[blockIdx.x] = ra[0] + ra[1] + ra[2] + ra[3];
-        sb[blockIdx.x] = rb[0] + rb[1] + rb[2] + rb[3];
+    if (threadIdx.x < N) {
+        const uint32_t *r = ra[threadIdx.x];
+        sums.p[threadIdx.x][blockIdx.x] = r[0] + r[1] + r[2] + r[3];
     }
 }
 
-// One workgroup, in tiles of kScanTile entries: coalesced loads into LDS, a
-// sequential scan of 4 entries per thread, a Hillis-Steele scan of the thread
-// sums, coalesced stores, and a running carry between tiles.  totals = the
-// two sums.
-__global__ __launch_bounds__(kScanThreads) void scan_kernel(uint32_t *__restrict__ a, uint32_t *__restrict__ b,
-                                                            int64_t n, uint64_t *__restrict__ totals) {
-    __shared__ uint32_t ta[kScanTile], tb[kScanTile];
-    __shared__ uint64_t sa[kScanThreads], sb[kScanThreads];
-    uint64_t carry_a = 0, carry_b = 0;
-    const int t = threadIdx.x;
-    for (int64_t base = 0; base < n; base += kScanTile) {
-        for (int i = t; i < kScanTile; i += kScanThreads) {
-            const int64_t g = base + i;
-            ta[i] = g < n ? a[g] : 0u;
-            tb[i] = g < n ? b[g] : 0u;
-        }
-        __syncthreads();
-        uint64_t xa = 0, xb = 0;
-        for (int i = 0; i < 4; ++i) { xa += ta[4 * t + i]; xb += tb[4 * t + i]; }
-        sa[t] = xa;
-        sb[t] = xb;
-        __syncthreads();
-        for (int off = 1; off < kScanThreads; off <<= 1) {
-            const uint64_t va = t >= off ? sa[t - off] : 0, vb = t >= off ? sb[t - off] : 0;
-            __syncthreads();
-            sa[t] += va;
-            sb[t] += vb;
-            __syncthreads();
-        }
-        uint64_t ra = carry_a + sa[t] - xa, rb = carry_b + sb[t] - xb;
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t va = ta[4 * t + i], vb = tb[4 * t + i];
-            ta[4 * t + i] = (uint32_t)ra;
-            tb[4 * t + i] = (uint32_t)rb;
-            ra += va;
-            rb += vb;
-        }
-        carry_a += sa[kScanThreads - 1];
-        carry_b += sb[kScanThreads - 1];
-        __syncthreads();
-        for (int i = t; i < kScanTile; i += kScanThreads) {
-            const int64_t g = base + i;
-            if (g < n) {
-                a[g] = ta[i];
-                b[g] = tb[i];
-            }
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        totals[0] = carry_a;
-        totals[1] = carry_b;
-    }
-}
-
-__global__ __launch_bounds__(256) void scan_apply_kernel(uint32_t *__restrict__ a, uint32_t *__restrict__ b, int64_t n,
-                                                         const uint32_t *__restrict__ off_a,
-                                                         const uint32_t *__restrict__ off_b) {
-    __shared__ uint32_t wa[4], wb[4];
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const int64_t base = (int64_t)blockIdx.x * kScanBlock + t * 4;
-    uint32_t va[4], vb[4], xa = 0, xb = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        va[k] = base + k < n ? a[base + k] : 0u;
-        vb[k] = base + k < n ? b[base + k] : 0u;
-        xa += va[k];
-        xb += vb[k];
-    }
-    // inclusive scan of the thread sums inside the wavefront
-    uint32_t ia = xa, ib = xb;
+// Inclusive scan over the lanes of a wavefront.
+template <typename U>
+__device__ __forceinline__ U wave_scan(U v, int lane) {
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t pa = __shfl_up(ia, off), pb = __shfl_up(ib, off);
-        if (lane >= off) {
-            ia += pa;
-            ib += pb;
-        }
+        const U u = __shfl_up(v, off);
+        if (lane >= off) v += u;
     }
-    if (lane == 63) {
-        wa[wv] = ia;
-        wb[wv] = ib;
-    }
-    __syncthreads();
-    uint32_t ra = off_a[blockIdx.x] + ia - xa, rb = off_b[blockIdx.x] + ib - xb;
-    for (int k = 0; k < wv; ++k) {
-        ra += wa[k];
-        rb += wb[k];
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        if (base + k < n) {
-            a[base + k] = ra;
-            b[base + k] = rb;
-            ra += va[k];
-            rb += vb[k];
-        }
+    return v;
 }
 
-// Exclusive scan of a[n] and b[n] in place; totals = {sum a, sum b}.  part
-// holds 2 * ceil(n / kScanBlock) words.
-static void scan_pair(uint32_t *a, uint32_t *b, int64_t n, uint32_t *part, uint64_t *totals, hipStream_t st) {
+// One workgroup, in tiles of kScanTile entries, four per thread: a scan of the
+// thread sums inside each wavefront, the wavefronts' totals through LDS (two
+// barriers a tile), and a running carry between tiles.  totals (nullable, in
+// pinned host memory) = the sums, then 1 in the word after them.
+// Latency-bound: a Hillis-Steele scan over LDS, twenty barriers a tile, took
+// 4.9 us on the 64 counts of a 16^3 grid, this one 2.4 (one array) and 3.8 (two).
+template <int N>
+__global__ __launch_bounds__(kScanThreads) void scan_kernel(Counts<N> a, int64_t n, uint64_t *__restrict__ totals) {
+    __shared__ uint64_t wsum[2][N][kScanThreads / 64];
+    uint64_t carry[N] = {};
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    int buf = 0;
+    for (int64_t base = 0; base < n; base += kScanTile, buf ^= 1) {
+        uint32_t v[N][4];
+        uint64_t x[N], inc[N];
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+            x[c] = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int64_t g = base + 4 * t + k;
+                v[c][k] = g < n ? a.p[c][g] : 0u;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x[c] += v[c][k];
+            inc[c] = wave_scan(x[c], lane);
+            if (lane == 63) wsum[buf][c][wv] = inc[c];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+            uint64_t before = 0, all = 0;
+#pragma unroll
+            for (int k = 0; k < kScanThreads / 64; ++k) {
+                const uint64_t s = wsum[buf][c][k];
+                if (k < wv) before += s;
+                all += s;
+            }
+            uint64_t o = carry[c] + before + inc[c] - x[c];
+            carry[c] += all;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int64_t g = base + 4 * t + k;
+                if (g < n) a.p[c][g] = (uint32_t)o;
+                o += v[c][k];
+            }
+        }
+    }
+    if (t == 0 && totals != nullptr) {
+#pragma unroll
+        for (int c = 0; c < N; ++c) __hip_atomic_store(totals + c, carry[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(totals + N, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+template <int N>
+__global__ __launch_bounds__(256) void scan_apply_kernel(Counts<N> a, int64_t n, Counts<N> offsets) {
+    __shared__ uint32_t wsum[N][4];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int64_t base = (int64_t)blockIdx.x * kScanBlock + t * 4;
+    uint32_t v[N][4], x[N], inc[N];
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+        x[c] = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[c][k] = base + k < n ? a.p[c][base + k] : 0u;
+            x[c] += v[c][k];
+        }
+        inc[c] = wave_scan(x[c], lane);
+        if (lane == 63) wsum[c][wv] = inc[c];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+        uint32_t o = offsets.p[c][blockIdx.x] + inc[c] - x[c];
+        for (int k = 0; k < wv; ++k) o += wsum[c][k];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (base + k < n) {
+                a.p[c][base + k] = o;
+                o += v[c][k];
+            }
+    }
+}
+
+// Exclusive scan of the N arrays a[n] in place; totals (nullable) = their
+// sums.  part holds N * ceil(n / kScanBlock) words.
+template <int N>
+static void scan_counts(Counts<N> a, int64_t n, uint32_t *part, uint64_t *totals, hipStream_t st) {
     const int64_t nb = (n + kScanBlock - 1) / kScanBlock;
-    if (nb <= 1) {
-        hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(kScanThreads), 0, st, a, b, n, totals);
+    if (n <= kScanTile) {
+        hipLaunchKernelGGL(scan_kernel<N>, dim3(1), dim3(kScanThreads), 0, st, a, n, totals);
         return;
     }
-    uint32_t *pa = part, *pb = part + nb;
-    hipLaunchKernelGGL(scan_reduce_kernel, dim3((unsigned)nb), dim3(256), 0, st, a, b, n, pa, pb);
-    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(kScanThreads), 0, st, pa, pb, nb, totals);
-    hipLaunchKernelGGL(scan_apply_kernel, dim3((unsigned)nb), dim3(256), 0, st, a, b, n, pa, pb);
+    Counts<N> sums;
+    for (int c = 0; c < N; ++c) sums.p[c] = part + c * nb;
+    hipLaunchKernelGGL(scan_reduce_kernel<N>, dim3((unsigned)nb), dim3(256), 0, st, a, n, sums);
+    hipLaunchKernelGGL(scan_kernel<N>, dim3(1), dim3(kScanThreads), 0, st, sums, nb, totals);
+    hipLaunchKernelGGL(scan_apply_kernel<N>, dim3((unsigned)nb), dim3(256), 0, st, a, n, sums);
 }
 
 // Pass 4: numbering.  One workgroup per group of 16 words, four words per
@@ -415,6 +417,10 @@ __global__ __launch_bounds__(256) void scatter_kernel(const uint64_t *__restrict
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t grp = (int64_t)blockIdx.x * 4 + wv;
     const int64_t g0 = grp * 16;
+    if (blockIdx.x == 0 && threadIdx.x < 2) {   // the far-field packages
+        pkg_cell[threadIdx.x] = sgrid::kNoCell;
+        pkg_type[threadIdx.x] = 0;
+    }
     if (g0 >= n_words) return;   // the same for the whole wavefront
     const int64_t wl = g0 + (lane & 15);
     const bool inl = wl < n_words;
@@ -506,7 +512,7 @@ __global__ __launch_bounds__(256) void scatter_kernel(const uint64_t *__restrict
 // 64-bit mask, bit lx + 4 ly + 16 lz.  Most boxes of a narrow band are empty
 // and cost 16 word reads; a box with activated cells is walked in Morton order
 // and reads the package id of its activated cells only.
-constexpr int kCodesPerBlock = kTagBlock * 64;
+constexpr int kBoxesPerGroup = 64;   // boxes per count, and per workgroup of the scatter
 
 __device__ __forceinline__ void morton_decode(int64_t code, int bits, int &x, int &y, int &z) {
     x = y = z = 0;
@@ -544,58 +550,77 @@ __device__ __forceinline__ uint64_t box_mask(const uint64_t *__restrict__ act, i
     return m;
 }
 
+// Every box's mask, and the activated cells of every 64 boxes.
 __global__ __launch_bounds__(kTagBlock) void morton_count_kernel(const uint64_t *__restrict__ act, int M, int W,
                                                                  int bits, int64_t n_codes,
+                                                                 uint64_t *__restrict__ mask,
                                                                  uint32_t *__restrict__ cnt) {
-    __shared__ uint32_t s_n[kTagBlock / 64];
+    const int64_t box = (int64_t)blockIdx.x * kTagBlock + threadIdx.x;
     int ox, oy, oz;
-    const uint64_t m = box_mask(act, M, W, bits, (int64_t)blockIdx.x * kTagBlock + threadIdx.x, n_codes, ox, oy, oz);
+    const uint64_t m = box_mask(act, M, W, bits, box, n_codes, ox, oy, oz);
+    if (box * 64 < n_codes) mask[box] = m;
     uint32_t n = (uint32_t)__popcll(m);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d);
-    if ((threadIdx.x & 63) == 0) s_n[threadIdx.x >> 6] = n;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t a = 0;
-        for (int i = 0; i < kTagBlock / 64; ++i) a += s_n[i];
-        cnt[blockIdx.x] = a;
-    }
+    if ((threadIdx.x & 63) == 0 && box * 64 < n_codes) cnt[box / kBoxesPerGroup] = n;
 }
 
-__global__ __launch_bounds__(kTagBlock) void morton_scatter_kernel(const uint32_t *__restrict__ cell_pkg,
-                                                                   const uint64_t *__restrict__ act, int M, int W,
-                                                                   int bits, int64_t n_codes,
-                                                                   const uint32_t *__restrict__ off,
-                                                                   uint32_t *__restrict__ work) {
-    __shared__ uint32_t s_n[kTagBlock / 64];
-    int ox, oy, oz;
-    const uint64_t m = box_mask(act, M, W, bits, (int64_t)blockIdx.x * kTagBlock + threadIdx.x, n_codes, ox, oy, oz);
-    // exclusive prefix of the boxes' counts over the workgroup (lane order is code order)
+// Writes the worklist and every package's position in it: a workgroup takes
+// 64 boxes.  Every wavefront holds a box's mask and place in the list per lane;
+// the wavefronts share the boxes with activated cells, each taking kBoxes in
+// turn, one lane per code of a box (code order is lane order, so the ballot of
+// the activated lanes gives each its place), with the map reads of kBoxes boxes
+// in flight.  A lane that walked its own box, one dependent load and store after
+// another, took 14 us on the smallest grids and 57 us at 512^3 cells; now 6.4 us
+// with eight wavefronts per workgroup (8.1 with four) and 30 us with four (38
+// with eight, which the many empty groups of a large grid only start and end).
+constexpr int kBoxes = 4;
+constexpr int kScatterWaves = 8;          // most of a workgroup
+constexpr int kScatterFewGroups = 2048;   // eight per CU: below, more wavefronts for each
+
+__global__ __launch_bounds__(64 * kScatterWaves) void morton_scatter_kernel(const uint32_t *__restrict__ cell_pkg,
+                                                                            const uint64_t *__restrict__ mask, int M,
+                                                                            int bits, int64_t n_boxes,
+                                                                            const uint32_t *__restrict__ off,
+                                                                            uint32_t *__restrict__ work,
+                                                                            uint32_t *__restrict__ wpos) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+    const int64_t box = (int64_t)blockIdx.x * kBoxesPerGroup + lane;
+    const uint64_t m = box < n_boxes ? mask[box] : 0ull;
+    uint64_t todo = __ballot(m != 0ull);
+    if (!todo) return;   // the same for the whole workgroup
     const uint32_t n = (uint32_t)__popcll(m);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    uint32_t inc = n;
+    const uint32_t pos = off[blockIdx.x] + wave_scan(n, lane) - n;
+    int ox = 0, oy = 0, oz = 0;
+    if (bits > 2) morton_decode(box, bits - 2, ox, oy, oz);
+    // code t of a box has lx = t0 + 2 t3, ly = t1 + 2 t4, lz = t2 + 2 t5
+    const int lx = (lane & 1) | ((lane >> 2) & 2), ly = ((lane >> 1) & 1) | ((lane >> 3) & 2),
+              lz = ((lane >> 2) & 1) | ((lane >> 4) & 2);
+    const int bit = lx + 4 * ly + 16 * lz;
+    for (int k = 0; k < wv * kBoxes && todo; ++k) todo &= todo - 1ull;
+    while (todo) {   // the same for the whole wavefront
+        uint32_t id[kBoxes], at[kBoxes];
+        bool on[kBoxes];
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t v = __shfl_up(inc, d);
-        if (lane >= d) inc += v;
+        for (int k = 0; k < kBoxes; ++k) {
+            const bool live = todo != 0ull;
+            const int src = live ? __builtin_ctzll(todo) : 0;
+            todo &= todo - 1ull;
+            const uint64_t mk = ((uint64_t)(uint32_t)__shfl((int)(m >> 32), src) << 32) | (uint32_t)__shfl((int)m, src);
+            on[k] = live && ((mk >> bit) & 1ull);
+            const uint64_t placed = __ballot(on[k]);
+            at[k] = (uint32_t)__shfl((int)pos, src) + (uint32_t)__popcll(placed & lanemask_lt());
+            const int x = 4 * __shfl(ox, src) + lx, y = 4 * __shfl(oy, src) + ly, z = 4 * __shfl(oz, src) + lz;
+            id[k] = on[k] ? cell_pkg[x + (int64_t)M * (y + (int64_t)M * z)] : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < kBoxes; ++k)
+            if (on[k]) {
+                work[at[k]] = id[k];
+                wpos[id[k]] = at[k];
+            }
+        for (int k = 0; k < (n_waves - 1) * kBoxes && todo; ++k) todo &= todo - 1ull;
     }
-    if (lane == 63) s_n[wv] = inc;
-    __syncthreads();
-    uint32_t pos = off[blockIdx.x] + inc - n;
-    for (int i = 0; i < wv; ++i) pos += s_n[i];
-    if (!m) return;
-    // the box in Morton order: code t has lx = t0 + 2 t3, ly = t1 + 2 t4, lz = t2 + 2 t5
-    for (int t = 0; t < 64; ++t) {
-        const int lx = (t & 1) | ((t >> 2) & 2), ly = ((t >> 1) & 1) | ((t >> 3) & 2), lz = ((t >> 2) & 1) | ((t >> 4) & 2);
-        if ((m >> (lx + 4 * ly + 16 * lz)) & 1ull)
-            work[pos++] = cell_pkg[(ox + lx) + (int64_t)M * ((oy + ly) + (int64_t)M * (oz + lz))];
-    }
-}
-
-__global__ __launch_bounds__(256) void worklist_pos_kernel(const uint32_t *__restrict__ work, int64_t P,
-                                                           uint32_t *__restrict__ wpos) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < P) wpos[work[e]] = (uint32_t)e;
 }
 
 // Face rows in worklist order, three times: wface holds the six face
@@ -639,18 +664,6 @@ __global__ __launch_bounds__(256) void sweep_face_kernel(const uint32_t *__restr
         wface[e * 8 + f] = w;
         sface[e * 8 + f] = v;
         mface[e * 8 + f] = m;
-    }
-}
-
-__global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t *__restrict__ p, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0u;
-}
-
-__global__ void far_rows_kernel(uint32_t *__restrict__ pkg_cell, uint8_t *__restrict__ pkg_type) {
-    if (threadIdx.x < 2) {
-        pkg_cell[threadIdx.x] = sgrid::kNoCell;
-        pkg_type[threadIdx.x] = 0;
     }
 }
 
@@ -724,47 +737,95 @@ __global__ __launch_bounds__(256) void core_slot_kernel(const uint32_t *__restri
     if (i < n_core) core_slot[core_list[i]] = (uint32_t)i;
 }
 
-// Core and sign bits of the refined layer, one wavefront per 64-cell word as
-// in bits_kernel.  A fine cell under a core parent takes its own distance
-// (child b = bx + 2 by + 4 bz of the parent's row); any other cell takes the
-// parent's sign from the parent layer's rank map and is not core (the parent
-// is not core, so its distance is at least the parent cell size, twice the
-// fine one).
+// Core and sign bits of the refined layer.  A fine cell under a core parent
+// takes its own distance (child b = bx + 2 by + 4 bz of the parent's row); any
+// other cell takes the parent's sign from the parent layer's rank map and is
+// not core (the parent is not core, so its distance is at least the parent
+// cell size, twice the fine one).  The 64 cells of a word lie under the 32
+// parents of one rank-map entry: a lane takes a word, and most of a narrow
+// band's words have no activated parent, so their bits follow from the entry
+// alone.  The others are listed in LDS, and each wavefront takes kRefineWords
+// listed words at a time, a lane per cell, with the three dependent loads
+// (package type, core slot, distance) of all of them in flight.  One wavefront
+// per word, empty or not, took 340 us at 512^3 cells; this takes 45 us.
+constexpr int kRefineWords = 4;
+
+// Bit i of v at bits 2i and 2i + 1.
+__device__ __forceinline__ uint64_t doubled_bits(uint32_t v) {
+    uint64_t x = v;
+    x = (x | (x << 16)) & 0x0000FFFF0000FFFFull;
+    x = (x | (x << 8)) & 0x00FF00FF00FF00FFull;
+    x = (x | (x << 4)) & 0x0F0F0F0F0F0F0F0Full;
+    x = (x | (x << 2)) & 0x3333333333333333ull;
+    x = (x | (x << 1)) & 0x5555555555555555ull;
+    return x | (x << 1);
+}
+
 __global__ __launch_bounds__(256) void refine_bits_kernel(const uint4 *__restrict__ rank_map, int W32c,
                                                           const uint8_t *__restrict__ pkg_type,
                                                           const uint32_t *__restrict__ core_slot,
                                                           const float *__restrict__ child_d, int Mc, int W,
                                                           int64_t n_words, double lc, uint64_t *__restrict__ core,
                                                           uint64_t *__restrict__ neg) {
-    const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (w >= n_words) return;   // whole wavefronts
-    const int lane = threadIdx.x & 63;
+    __shared__ uint4 s_entry[256];
+    __shared__ uint32_t s_word[256];   // listed: word within the workgroup, parity of y and z
+    __shared__ uint32_t s_n;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int Mf = 2 * Mc;
-    const int64_t r = quot(w, W);
-    const int x = (int)(w - r * W) * 64 + lane;
-    const int64_t rz = quot(r, Mf);
-    const int y = (int)(r - rz * Mf), z = (int)rz;
-    bool is_core = false, is_neg = false;
-    if (x < Mf) {
-        const int px = x >> 1, py = y >> 1, pz = z >> 1;
-        const uint4 e = rank_map[((int64_t)py + (int64_t)Mc * pz) * W32c + (px >> 5)];
-        const uint32_t bit = 1u << (px & 31);
-        is_neg = (e.y & bit) != 0u;
-        if (e.x & bit) {
-            const uint32_t id = 2u + e.z + (uint32_t)__popc(e.x & (bit - 1u));
-            if (pkg_type[id] == 1) {
-                const int b = (x & 1) + 2 * (y & 1) + 4 * (z & 1);
-                const float v = child_d[(int64_t)core_slot[id] * 8 + b];
-                is_core = fabs((double)v) < lc;
-                is_neg = v < 0.0f;
-            }
+    const int64_t w0 = (int64_t)blockIdx.x * 256, w = w0 + threadIdx.x;
+    if (threadIdx.x == 0) s_n = 0u;
+    __syncthreads();
+    if (w < n_words) {
+        const int64_t r = quot(w, W);
+        const int i = (int)(w - r * W);
+        const int64_t rz = quot(r, Mf);
+        const int y = (int)(r - rz * Mf), z = (int)rz;
+        const uint4 e = rank_map[((int64_t)(y >> 1) + (int64_t)Mc * (z >> 1)) * W32c + i];
+        if (e.x == 0u) {
+            const int left = Mf - 64 * i;
+            core[w] = 0ull;
+            neg[w] = doubled_bits(e.y) & (left >= 64 ? ~0ull : (1ull << left) - 1ull);
+        } else {
+            const uint32_t at = atomicAdd(&s_n, 1u);
+            s_entry[at] = make_uint4(e.x, e.y, e.z, (uint32_t)min(64, Mf - 64 * i));
+            s_word[at] = threadIdx.x | ((uint32_t)(y & 1) << 8) | ((uint32_t)(z & 1) << 9);
         }
     }
-    const uint64_t bc = __ballot(is_core);
-    const uint64_t bn = __ballot(is_neg);
-    if (lane == 0) {
-        core[w] = bc;
-        neg[w] = bn;
+    __syncthreads();
+    const uint32_t n = s_n;
+    const uint32_t bit = 1u << (lane >> 1);
+    for (uint32_t k0 = wv * kRefineWords; k0 < n; k0 += 4 * kRefineWords) {   // the same for a wavefront
+        uint4 e[kRefineWords];
+        uint32_t word[kRefineWords], id[kRefineWords], slot[kRefineWords];
+        uint8_t type[kRefineWords];
+        float v[kRefineWords];
+#pragma unroll
+        for (int k = 0; k < kRefineWords; ++k) {
+            const uint32_t at = k0 + k < n ? k0 + k : n - 1;
+            e[k] = s_entry[at];
+            word[k] = s_word[at];
+            // 2 + rank of an activated parent; else package 0, a far field
+            id[k] = (e[k].x & bit) ? 2u + e[k].z + (uint32_t)__popc(e[k].x & (bit - 1u)) : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < kRefineWords; ++k) type[k] = pkg_type[id[k]];
+#pragma unroll
+        for (int k = 0; k < kRefineWords; ++k) slot[k] = type[k] == 1 ? core_slot[id[k]] : 0u;
+#pragma unroll
+        for (int k = 0; k < kRefineWords; ++k) {
+            const uint32_t b = (lane & 1) + 2 * ((word[k] >> 8) & 1u) + 4 * ((word[k] >> 9) & 1u);
+            v[k] = type[k] == 1 ? child_d[(int64_t)slot[k] * 8 + b] : 0.f;
+        }
+#pragma unroll
+        for (int k = 0; k < kRefineWords; ++k) {
+            const bool in = lane < (int)e[k].w, own = in && type[k] == 1;
+            const uint64_t bc = __ballot(own && fabs((double)v[k]) < lc);
+            const uint64_t bn = __ballot(in && (own ? v[k] < 0.0f : (e[k].y & bit) != 0u));
+            if (lane == 0 && k0 + k < n) {
+                core[w0 + (word[k] & 255u)] = bc;
+                neg[w0 + (word[k] & 255u)] = bn;
+            }
+        }
     }
 }
 
@@ -777,14 +838,36 @@ void free_grid(sgrid_grid *g) {
     delete g;
 }
 
-// Pinned host word for the one readback of a build (per thread).
+// Pinned host words for the one readback of a build (per thread): P, the core
+// packages and a flag, written by the scan kernel itself.
 uint64_t *pinned_totals() {
     static thread_local uint64_t *buf = nullptr;
-    if (!buf && hipHostMalloc((void **)&buf, 2 * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess) {
+    if (!buf && hipHostMalloc((void **)&buf, 3 * sizeof(uint64_t),
+                              hipHostMallocCoherent | hipHostMallocMapped | hipHostMallocPortable) != hipSuccess) {
         (void)hipGetLastError();
         buf = nullptr;
     }
     return buf;
+}
+
+// Waits for the flag of `host`.  The word arrives while later kernels of the
+// stream run, which a copy and a stream synchronisation would wait for (and
+// cost about 10 us more).  When the flag stays away the stream itself is
+// asked, so a failed launch or a stream being captured ends the wait with the
+// runtime's error.
+hipError_t wait_totals(uint64_t *host, hipStream_t st) {
+    for (int spin = 0;; ++spin) {
+        if (__atomic_load_n(host + 2, __ATOMIC_ACQUIRE) != 0) return hipSuccess;
+        if ((spin & 16383) == 16383) {
+            const hipError_t e = hipStreamQuery(st);
+            if (e != hipErrorNotReady) {
+                const hipError_t f = e == hipSuccess ? hipStreamSynchronize(st) : e;
+                if (f != hipSuccess) return f;
+                return __atomic_load_n(host + 2, __ATOMIC_ACQUIRE) != 0 ? hipSuccess : hipErrorUnknown;
+            }
+            (void)hipGetLastError();
+        }
+    }
 }
 
 }  // namespace
@@ -808,12 +891,13 @@ uint64_t *pinned_totals() {
 namespace {
 
 // A new grid of M^3 cells at spacing h with its build workspace: three
-// bitmaps (core, negative sign, activated), the per-group counts, the scan's
-// block sums and the totals.
+// bitmaps (core, negative sign, activated), the per-group counts and the scan's
+// block sums; the masks, counts and block sums of the worklist's boxes.
 struct BuildWs {
-    int64_t W, n_words, n_groups;
-    uint64_t *core_bits, *neg_bits, *act_bits, *totals;
-    uint32_t *ca, *cc, *part;
+    int64_t W, n_words, n_groups, n_boxes;
+    int bits;   // of a Morton code per axis
+    uint64_t *core_bits, *neg_bits, *act_bits, *box_masks;
+    uint32_t *ca, *cc, *part, *box_counts, *box_part;
 };
 
 sgrid_status new_grid(int64_t M, double h, sgrid_grid **out, BuildWs &ws) {
@@ -834,14 +918,23 @@ sgrid_status new_grid(int64_t M, double h, sgrid_grid **out, BuildWs &ws) {
     const size_t ws_bits = ((size_t)ws.n_words * 8 + 255) / 256 * 256;
     const size_t ws_counts = ((size_t)ws.n_groups * 4 + 255) / 256 * 256;
     const size_t ws_part = ((size_t)n_sblocks * 8 + 255) / 256 * 256;
-    SG_ALLOC(g->workspace, 3 * ws_bits + 2 * ws_counts + ws_part + 256, "build workspace");
+    ws.bits = 0;
+    while ((1ll << ws.bits) < M) ++ws.bits;
+    ws.n_boxes = ws.bits > 2 ? (int64_t)1 << (3 * (ws.bits - 2)) : 1;
+    const int64_t n_box_groups = (ws.n_boxes + kBoxesPerGroup - 1) / kBoxesPerGroup;
+    const size_t ws_masks = ((size_t)ws.n_boxes * 8 + 255) / 256 * 256;
+    const size_t ws_boxes = ((size_t)n_box_groups * 4 + 255) / 256 * 256;
+    const size_t ws_box_part = (size_t)((n_box_groups + kScanBlock - 1) / kScanBlock) * 4;
+    SG_ALLOC(g->workspace, 3 * ws_bits + 2 * ws_counts + ws_part + ws_masks + ws_boxes + ws_box_part, "build workspace");
     ws.core_bits = (uint64_t *)g->workspace;
     ws.neg_bits = (uint64_t *)((uint8_t *)ws.core_bits + ws_bits);
     ws.act_bits = (uint64_t *)((uint8_t *)ws.neg_bits + ws_bits);
     ws.ca = (uint32_t *)((uint8_t *)ws.act_bits + ws_bits);
     ws.cc = (uint32_t *)((uint8_t *)ws.ca + ws_counts);
     ws.part = (uint32_t *)((uint8_t *)ws.cc + ws_counts);
-    ws.totals = (uint64_t *)((uint8_t *)ws.part + ws_part);
+    ws.box_masks = (uint64_t *)((uint8_t *)ws.part + ws_part);
+    ws.box_counts = (uint32_t *)((uint8_t *)ws.box_masks + ws_masks);
+    ws.box_part = (uint32_t *)((uint8_t *)ws.box_counts + ws_boxes);
     SG_ALLOC(g->cell_pkg, n_cells * 4, "cell_pkg");
     *out = g;
     return SGRID_OK;
@@ -849,87 +942,84 @@ sgrid_status new_grid(int64_t M, double h, sgrid_grid **out, BuildWs &ws) {
 
 // Everything after the core and sign bitmaps: dilation, numbering (one host
 // synchronisation learns P), tables, neighbours, the Morton worklist and the
-// worklist face rows.  Frees the grid on failure.
-sgrid_status finish_grid(sgrid_grid *g, const BuildWs &ws, hipStream_t st) {
+// worklist face rows.
+#define SG_TRY_ALLOC(ptr, bytes, what)                                              \
+    do {                                                                            \
+        sgrid_status _s = sgrid::dev_alloc((void **)&(ptr), (size_t)(bytes), what); \
+        if (_s != SGRID_OK) return _s;                                              \
+    } while (0)
+
+sgrid_status fill_grid(sgrid_grid *g, const BuildWs &ws, hipStream_t st) {
     const int64_t M = g->M, W = ws.W, n_words = ws.n_words, n_groups = ws.n_groups;
-    uint64_t *core_bits = ws.core_bits, *neg_bits = ws.neg_bits, *act_bits = ws.act_bits, *totals = ws.totals;
+    uint64_t *core_bits = ws.core_bits, *neg_bits = ws.neg_bits, *act_bits = ws.act_bits;
+    uint64_t *host = pinned_totals();
+    if (host == nullptr) {
+        sgrid::set_error("pinned host words could not be allocated");
+        return SGRID_E_NOMEM;
+    }
+    __atomic_store_n(host + 2, 0ull, __ATOMIC_RELEASE);
     uint32_t *ca = ws.ca, *cc = ws.cc, *part = ws.part;
     hipLaunchKernelGGL(dilate_kernel, dim3((unsigned)((n_words + 255) / 256)), dim3(256), 0, st, core_bits, (int)M,
                        (int)W, n_words, act_bits, ca, cc);
-    SG_HIP_OR_FREE(hipGetLastError());
-    scan_pair(ca, cc, n_groups, part, totals, st);
-    SG_HIP_OR_FREE(hipGetLastError());
-    uint64_t *host = pinned_totals();
-    uint64_t local[2] = {0, 0};
-    uint64_t *dst = host ? host : local;
-    SG_HIP_OR_FREE(hipMemcpyAsync(dst, totals, 2 * sizeof(uint64_t), hipMemcpyDeviceToHost, st));
-    SG_HIP_OR_FREE(hipStreamSynchronize(st));
-    g->P = (int64_t)dst[0];
-    g->n_core = (int64_t)dst[1];
+    SG_CHECK_HIP(hipGetLastError());
+    scan_counts(Counts<2>{{ca, cc}}, n_groups, part, host, st);
+    SG_CHECK_HIP(hipGetLastError());
+    // the worklist's boxes need no package ids: counted while the host waits
+    const int64_t n_box_groups = (ws.n_boxes + kBoxesPerGroup - 1) / kBoxesPerGroup;
+    hipLaunchKernelGGL(morton_count_kernel, dim3((unsigned)((ws.n_boxes + kTagBlock - 1) / kTagBlock)), dim3(kTagBlock),
+                       0, st, act_bits, (int)M, (int)W, ws.bits, ws.n_boxes * 64, ws.box_masks, ws.box_counts);
+    SG_CHECK_HIP(hipGetLastError());
+    scan_counts(Counts<1>{{ws.box_counts}}, n_box_groups, ws.box_part, nullptr, st);
+    SG_CHECK_HIP(hipGetLastError());
+    SG_CHECK_HIP(wait_totals(host, st));
+    g->P = (int64_t)host[0];
+    g->n_core = (int64_t)host[1];
     const int64_t nt = g->total();
-    SG_ALLOC(g->pkg_cell, nt * 4, "pkg_cell");
-    SG_ALLOC(g->pkg_type, nt, "pkg_type");
-    SG_ALLOC(g->nbr, nt * 27 * 4, "pkg_nbr");
-    SG_ALLOC(g->face, nt * 8 * 4, "face table");
-    SG_ALLOC(g->core_list, (g->n_core > 0 ? g->n_core : 1) * 4, "core_list");
-    hipLaunchKernelGGL(far_rows_kernel, dim3(1), dim3(64), 0, st, g->pkg_cell, g->pkg_type);
-    SG_HIP_OR_FREE(hipGetLastError());
+    SG_TRY_ALLOC(g->pkg_cell, nt * 4, "pkg_cell");
+    SG_TRY_ALLOC(g->pkg_type, nt, "pkg_type");
+    SG_TRY_ALLOC(g->nbr, nt * 27 * 4, "pkg_nbr");
+    SG_TRY_ALLOC(g->face, nt * 8 * 4, "face table");
+    SG_TRY_ALLOC(g->core_list, (g->n_core > 0 ? g->n_core : 1) * 4, "core_list");
     g->W32 = (int32_t)((M + 31) / 32);
-    SG_ALLOC(g->rank_map, M * M * g->W32 * 16, "rank map");
+    SG_TRY_ALLOC(g->rank_map, M * M * g->W32 * 16, "rank map");
     hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)((n_groups + 3) / 4)), dim3(256), 0, st, act_bits, core_bits,
                        neg_bits,
                        (int)M, (int)W, n_words, ca, cc, g->cell_pkg, g->pkg_cell, g->pkg_type, g->core_list,
                        g->rank_map, g->W32);
-    SG_HIP_OR_FREE(hipGetLastError());
+    SG_CHECK_HIP(hipGetLastError());
     hipLaunchKernelGGL(nbr_kernel, dim3((unsigned)((nt + 9 * kNbrPkgs - 1) / (9 * kNbrPkgs))), dim3(256), 0, st,
                        g->cell_pkg, g->pkg_cell, (int)M, nt, g->nbr, g->face);
-    SG_HIP_OR_FREE(hipGetLastError());
-    // Morton-order sweep worklist: count activated codes per block of
-    // kCodesPerBlock codes, scan, scatter (the counts and the scan's block sums
-    // live behind the worklist)
-    {
-        int bits = 0;
-        while ((1ll << bits) < M) ++bits;
-        const int64_t n_codes = (int64_t)1 << (3 * bits);
-        const int64_t nbm = (n_codes + kCodesPerBlock - 1) / kCodesPerBlock;
-        const int64_t nbs = (nbm + kScanBlock - 1) / kScanBlock;
-        SG_ALLOC(g->work, ((g->P > 0 ? g->P : 1) + 2 * nbm + 2 * nbs + 64) * 4, "sweep worklist");
-        uint32_t *mc = g->work + (g->P > 0 ? g->P : 1);
-        uint32_t *mz = mc + nbm;
-        uint32_t *mpart = mz + nbm;
-        hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((nbm + 255) / 256)), dim3(256), 0, st, mz, nbm);
-        SG_HIP_OR_FREE(hipGetLastError());
-        hipLaunchKernelGGL(morton_count_kernel, dim3((unsigned)nbm), dim3(kTagBlock), 0, st, act_bits, (int)M, (int)W,
-                           bits, n_codes, mc);
-        SG_HIP_OR_FREE(hipGetLastError());
-        scan_pair(mc, mz, nbm, mpart, totals, st);
-        SG_HIP_OR_FREE(hipGetLastError());
-        hipLaunchKernelGGL(morton_scatter_kernel, dim3((unsigned)nbm), dim3(kTagBlock), 0, st, g->cell_pkg, act_bits,
-                           (int)M, (int)W, bits, n_codes, mc, g->work);
-        SG_HIP_OR_FREE(hipGetLastError());
-    }
+    SG_CHECK_HIP(hipGetLastError());
+    SG_TRY_ALLOC(g->work, (g->P > 0 ? g->P : 1) * 4, "sweep worklist");
+    SG_TRY_ALLOC(g->wpos, nt * 4, "worklist positions");
+    hipLaunchKernelGGL(morton_scatter_kernel, dim3((unsigned)n_box_groups),
+                       dim3(n_box_groups < kScatterFewGroups ? 64 * kScatterWaves : 32 * kScatterWaves), 0, st,
+                       g->cell_pkg, ws.box_masks, (int)M, ws.bits, ws.n_boxes, ws.box_counts, g->work, g->wpos);
+    SG_CHECK_HIP(hipGetLastError());
     // group-relative face rows of the sweep order, through the position of
     // every package in the worklist (kept with the handle)
     {
-        SG_ALLOC(g->sface, (g->P > 0 ? g->P : 1) * 32, "sweep face table");
-        SG_ALLOC(g->wface, (g->P > 0 ? g->P : 1) * 32, "worklist face table");
-        uint32_t *wpos = nullptr;
-        SG_ALLOC(wpos, nt * 4, "worklist positions");
-        if (g->P > 0) {
-            hipLaunchKernelGGL(worklist_pos_kernel, dim3((unsigned)((g->P + 255) / 256)), dim3(256), 0, st, g->work,
-                               g->P, wpos);
-            SG_HIP_OR_FREE(hipGetLastError());
-        }
-        g->wpos = wpos;
-        SG_ALLOC(g->mface, (g->P > 0 ? g->P : 1) * 32, "worklist-ordered face table");
+        SG_TRY_ALLOC(g->sface, (g->P > 0 ? g->P : 1) * 32, "sweep face table");
+        SG_TRY_ALLOC(g->wface, (g->P > 0 ? g->P : 1) * 32, "worklist face table");
+        SG_TRY_ALLOC(g->mface, (g->P > 0 ? g->P : 1) * 32, "worklist-ordered face table");
         if (g->P > 0) {
             const int64_t groups = (g->P + kFacePkgs - 1) / kFacePkgs;
             hipLaunchKernelGGL(sweep_face_kernel, dim3((unsigned)((groups * 8 + 255) / 256)), dim3(256), 0, st,
-                               g->work, g->face, wpos, g->P, g->wface, g->sface, g->mface);
-            SG_HIP_OR_FREE(hipGetLastError());
+                               g->work, g->face, g->wpos, g->P, g->wface, g->sface, g->mface);
+            SG_CHECK_HIP(hipGetLastError());
         }
     }
     return SGRID_OK;
+}
+
+// The same; on failure the grid is freed once its queued kernels have ended.
+sgrid_status finish_grid(sgrid_grid *g, const BuildWs &ws, hipStream_t st) {
+    const sgrid_status s = fill_grid(g, ws, st);
+    if (s != SGRID_OK) {
+        (void)hipStreamSynchronize(st);
+        free_grid(g);
+    }
+    return s;
 }
 
 }  // namespace
@@ -985,7 +1075,7 @@ extern "C" sgrid_status sgrid_build_packages_refined(const sgrid_grid *coarse, c
         SG_HIP_OR_FREE(hipGetLastError());
     }
     const double lc = 4.0 * g->h;
-    hipLaunchKernelGGL(refine_bits_kernel, dim3((unsigned)((ws.n_words + 3) / 4)), dim3(256), 0, st, coarse->rank_map,
+    hipLaunchKernelGGL(refine_bits_kernel, dim3((unsigned)((ws.n_words + 255) / 256)), dim3(256), 0, st, coarse->rank_map,
                        coarse->W32, coarse->pkg_type, core_slot, child_sdf, coarse->M, (int)ws.W, ws.n_words, lc,
                        ws.core_bits, ws.neg_bits);
     SG_HIP_OR_FREE(hipGetLastError());
