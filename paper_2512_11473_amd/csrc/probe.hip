@@ -215,25 +215,38 @@ __global__ __launch_bounds__(256) void probe_field_kernel(Corner<float, true> fi
 // wavefront's corners fall on a few shared lines and the packages a stretch of
 // particles gathers from stay in the L2 of the XCD that probes them.
 //
-// LSD radix sort, 9 bits per pass (three passes for 512^3 coarse cells),
-// stable, so the result is unique: keys non-decreasing, equal keys in their
-// input order.  Per pass, one kernel counts each 4096-element tile's digits in
-// LDS, a scan turns the digit-major [512][tiles] counts into output offsets,
-// and a second kernel (eight wavefronts, three workgroups per CU)
-// ranks the tile's elements stably (wavefront ballots over the digit bits,
-// then per-wavefront running counts in LDS), reorders the tile by digit in
-// LDS and writes each digit's run contiguously.  The first pass's counts
-// compute the keys from the positions and store them for its scatter; the
-// last pass writes the permutation and gathers the sorted positions.  Both kernels take their tiles in XCD-aware order: the
-// runs of one digit from consecutive tiles are adjacent in the output, and
-// the partial cache lines where they meet are then written from one L2.
+// LSD radix sort, at most 9 bits per pass (three passes for 512^3 coarse
+// cells), stable, so the result is unique: keys non-decreasing, equal keys in
+// their input order.  Per pass, one kernel counts
+// each tile's digits in LDS, a scan turns the digit-major [digits][tiles]
+// counts into output offsets, and a second kernel (eight wavefronts, two
+// workgroups per CU) ranks the tile's elements stably (wavefront ballots over
+// the digit bits, then per-wavefront running counts in LDS), reorders the tile
+// by digit in LDS and writes each digit's run contiguously.  Both kernels take
+// their tiles in XCD-aware order: the runs of one digit from consecutive tiles
+// are adjacent in the output, and the partial cache lines where they meet are
+// then written from one L2.
+//
+// An element carries its position through every pass (16 bytes with its index)
+// and its key is computed again from it.  Sorting (key, index) pairs and
+// gathering the positions at the end moves fewer bytes, but the gather fetches
+// a 128-byte line per particle: 1.24 of 2.23 ms at 5e7 particles on 512^3
+// cells.  Now a scatter pass moves 32 bytes per particle in 0.31 ms (5.1 TB/s, a
+// copy's rate) and a count pass reads 12 or 16 in 0.14 to 0.20, 1.5 ms in all;
+// at 1e7 on 128^3, 465 -> 320 us.  Writing the elements straight from the
+// registers instead of in the tile's digit order took 0.31 to 0.71 ms per
+// scatter pass; writing the next pass's digit beside each element, so that its
+// count reads 2 bytes, cost the scatters what it saved the counts.
+//
+// Passes alternate between one workspace buffer (float4: x, y, z, index) and
+// the output arrays, so that the last one ends in the outputs.
 
 constexpr int kScanItems = 4096;    // entries per scan block: 1024 lanes x 4
-constexpr int kRadixBits = 9, kRadixBins = 1 << kRadixBits;
 constexpr int kSortWaves = 8, kSortThreads = 64 * kSortWaves;
 constexpr int kSortRounds = 8;
 constexpr int kSortTile = kSortThreads * kSortRounds;   // 4096 elements per tile
-static_assert(kRadixBins <= kSortThreads && kRadixBins % 64 == 0, "one digit per thread of whole wavefronts");
+constexpr int kMaxBits = 9;                             // of a digit: one digit per thread
+static_assert((1 << kMaxBits) <= kSortThreads && kSortTile <= 65536, "16-bit counts and places in the tile");
 
 __device__ __forceinline__ uint32_t spread3(uint32_t v) {   // bit b of v (b < 10) to bit 3b
     v &= 0x3FFu;
@@ -250,54 +263,53 @@ __device__ __forceinline__ uint32_t home_key(const float *x, int M, float inv_h)
     return spread3((uint32_t)cx) | (spread3((uint32_t)cy) << 1) | (spread3((uint32_t)cz) << 2);
 }
 
+// Where a pass reads from and writes to.
+struct SortBuffers {
+    const float *pos;     // the input
+    float4 *rec;          // workspace: x, y, z, index
+    float *pos_out;       // the outputs
+    uint32_t *perm;
+};
+enum SortPlace { kInput, kRecords, kOutputs };
+
+template <SortPlace P>
+__device__ __forceinline__ void sort_load(const SortBuffers &b, int64_t e, float (&x)[3], uint32_t &idx) {
+    if (P == kRecords) {
+        const float4 v = b.rec[e];
+        x[0] = v.x;
+        x[1] = v.y;
+        x[2] = v.z;
+        idx = __float_as_uint(v.w);
+    } else {
+        const float *p = (P == kInput ? b.pos : b.pos_out) + 3 * e;
+        x[0] = p[0];
+        x[1] = p[1];
+        x[2] = p[2];
+        idx = P == kInput ? (uint32_t)e : b.perm[e];
+    }
+}
+
 // counts[d * n_tiles + tile] = elements of the tile whose digit is d.
-// The first pass's counts compute the keys from the positions and, when the
-// sort has more passes, store them for the first scatter (keys_out).
-template <bool FIRST>
-__global__ __launch_bounds__(256) void radix_count_kernel(const float *__restrict__ pos,
-                                                          const uint32_t *__restrict__ keys, int64_t n, int M,
-                                                          float inv_h, int shift, uint32_t *__restrict__ counts,
-                                                          int64_t n_tiles, uint32_t *__restrict__ keys_out) {
-    __shared__ uint32_t s_hist[kRadixBins];
-    for (int d = threadIdx.x; d < kRadixBins; d += 256) s_hist[d] = 0u;
+template <int BITS, SortPlace SRC>
+__global__ __launch_bounds__(256) void radix_count_kernel(SortBuffers buf, int64_t n, int M, float inv_h, int shift,
+                                                          uint32_t *__restrict__ counts, int64_t n_tiles) {
+    constexpr int kBins = 1 << BITS;
+    __shared__ uint32_t s_hist[kBins];
+    for (int d = threadIdx.x; d < kBins; d += 256) s_hist[d] = 0u;
     __syncthreads();
     const int64_t tile = xcd_block(blockIdx.x, n_tiles);
     const int64_t t0 = tile * kSortTile;
-    if constexpr (FIRST) {
-#pragma unroll 4
-        for (int k = 0; k < kSortTile / 256; ++k) {
-            const int64_t e = t0 + k * 256 + threadIdx.x;
-            if (e < n) {
-                const uint32_t key = home_key(pos + 3 * e, M, inv_h);
-                if (keys_out) keys_out[e] = key;
-                atomicAdd(&s_hist[(key >> shift) & (kRadixBins - 1)], 1u);
-            }
-        }
-    } else {
-        // four consecutive keys per lane and step, one 16-byte load each (the
-        // key arrays are 256-byte aligned and tiles start at multiples of 4),
-        // all of a lane's loads issued before its LDS atomics
-        constexpr int kSteps = kSortTile / 1024;
-        uint4 q[kSteps];
-#pragma unroll
-        for (int k = 0; k < kSteps; ++k) {
-            const int64_t e = t0 + 4 * (k * 256 + threadIdx.x);
-            if (e + 3 < n)
-                q[k] = *reinterpret_cast<const uint4 *>(keys + e);
-            else
-                q[k] = make_uint4(e < n ? keys[e] : 0u, e + 1 < n ? keys[e + 1] : 0u, e + 2 < n ? keys[e + 2] : 0u, 0u);
-        }
-#pragma unroll
-        for (int k = 0; k < kSteps; ++k) {
-            const int64_t e = t0 + 4 * (k * 256 + threadIdx.x);
-            const uint32_t v[4] = {q[k].x, q[k].y, q[k].z, q[k].w};
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (e + u < n) atomicAdd(&s_hist[(v[u] >> shift) & (kRadixBins - 1)], 1u);
-        }
+#pragma unroll 8
+    for (int k = 0; k < kSortTile / 256; ++k) {
+        const int64_t e = t0 + k * 256 + threadIdx.x;
+        float x[3];
+        uint32_t idx;
+        sort_load<SRC>(buf, e < n ? e : n - 1, x, idx);
+        const uint32_t d = (home_key(x, M, inv_h) >> shift) & (kBins - 1);
+        if (e < n) atomicAdd(&s_hist[d], 1u);
     }
     __syncthreads();
-    for (int d = threadIdx.x; d < kRadixBins; d += 256) counts[(int64_t)d * n_tiles + tile] = s_hist[d];
+    for (int d = threadIdx.x; d < kBins; d += 256) counts[(int64_t)d * n_tiles + tile] = s_hist[d];
 }
 
 // Exclusive scan of one block of kScanItems entries in place; the block's
@@ -328,7 +340,7 @@ __global__ __launch_bounds__(1024) void scan_block_kernel(uint32_t *__restrict__
         if (base + k < n) v[base + k] = run;
         run += c;
     }
-    if (threadIdx.x == 1023) sums[blockIdx.x] = run;
+    if (threadIdx.x == 1023) sums[blockIdx.x] = gridDim.x == 1 ? 0u : run;   // one block: its own offset
 }
 
 // Exclusive scan of the block totals by one workgroup, in chunks of 1024.
@@ -358,112 +370,113 @@ __global__ __launch_bounds__(1024) void scan_sums_kernel(uint32_t *__restrict__ 
 }
 
 // One stable pass over a tile: rank, reorder in LDS, write runs.  Element
-// order inside the tile: wavefront w holds elements [64 R w, 64 R (w + 1)),
-// R = kSortRounds, taken in rounds of 64 consecutive ones.
-template <bool FIRST, bool LAST>
-__global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(const float *__restrict__ pos,
-                                                            const uint32_t *__restrict__ keys_in,
-                                                            const uint32_t *__restrict__ idx_in, int64_t n, int M,
-                                                            float inv_h, int shift,
-                                                            const uint32_t *__restrict__ offs,
-                                                            const uint32_t *__restrict__ sums, int64_t n_tiles,
-                                                            uint32_t *__restrict__ keys_out,
-                                                            uint32_t *__restrict__ idx_out,
-                                                            float *__restrict__ pos_out) {
-    __shared__ uint32_t s_cnt[kSortWaves][kRadixBins];   // running count per wavefront, then its base
-    __shared__ uint32_t s_start[kRadixBins];             // first tile position of each digit
-    __shared__ uint32_t s_goff[kRadixBins];              // output position of each digit's run
-    __shared__ uint32_t s_key[kSortTile], s_idx[kSortTile];
-    __shared__ uint32_t s_wsum[kRadixBins / 64];
+// order inside the tile: wavefront w holds elements [64 R w, 64 R (w + 1)), R =
+// rounds, taken in rounds of 64 consecutive ones.
+template <int BITS, SortPlace SRC, SortPlace DST>
+__global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(SortBuffers buf, int64_t n, int M,
+                                                                              float inv_h, int shift,
+                                                                              const uint32_t *__restrict__ offs,
+                                                                              const uint32_t *__restrict__ sums,
+                                                                              int64_t n_tiles) {
+    constexpr int kBins = 1 << BITS;
+    // the tile in digit order; before that, the digits' counts per wavefront
+    union Stage {
+        uint16_t cnt[kSortWaves][kBins];
+        struct {
+            float x[3][kSortTile];
+            uint32_t idx[kSortTile];
+        } el;
+    };
+    __shared__ Stage st;
+    __shared__ uint16_t s_dig[kSortTile];
+    __shared__ uint32_t s_goff[kBins];   // output position of a digit's run, less its position in the tile
+    __shared__ uint32_t s_wsum[kSortWaves];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int i = threadIdx.x; i < kSortWaves * kRadixBins; i += kSortThreads) s_cnt[i / kRadixBins][i % kRadixBins] = 0u;
-    __syncthreads();
+    for (int i = threadIdx.x; i < kSortWaves * kBins / 2; i += kSortThreads)
+        reinterpret_cast<uint32_t *>(&st.cnt[0][0])[i] = 0u;
     const int64_t tile = xcd_block(blockIdx.x, n_tiles);
     const int64_t tile0 = tile * kSortTile;
     const int64_t w0 = tile0 + (int64_t)(64 * kSortRounds) * w;
     const uint64_t below = (1ull << lane) - 1ull;
-    uint32_t key[kSortRounds], idx[kSortRounds], rank[kSortRounds];
+    float x[kSortRounds][3];
+    uint32_t idx[kSortRounds], at[kSortRounds];   // at: digit, and rank in the wavefront, then place in the tile
 #pragma unroll
     for (int j = 0; j < kSortRounds; ++j) {
         const int64_t e = w0 + 64 * j + lane;
-        const bool valid = e < n;
-        const int64_t ec = valid ? e : n - 1;
-        // (a single-pass sort computes the keys here; otherwise the first
-        // pass's counts have stored them)
-        key[j] = (FIRST && LAST) ? home_key(pos + 3 * ec, M, inv_h) : keys_in[ec];
-        idx[j] = FIRST ? (uint32_t)ec : idx_in[ec];
-        const uint32_t d = (key[j] >> shift) & (kRadixBins - 1);
+        sort_load<SRC>(buf, e < n ? e : n - 1, x[j], idx[j]);
+    }
+    const bool owner = threadIdx.x < kBins;   // thread d owns digit d
+    const int d_own = owner ? threadIdx.x : 0;
+    const int64_t oi = (int64_t)d_own * n_tiles + tile;
+    const uint32_t goff = offs[oi] + sums[oi / kScanItems];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSortRounds; ++j) {
+        const bool valid = w0 + 64 * j + lane < n;
+        const uint32_t d = (home_key(x[j], M, inv_h) >> shift) & (kBins - 1);
         // lanes of this round with the same digit (the valid ones)
         uint64_t peers = __ballot(valid);
 #pragma unroll
-        for (int b = 0; b < kRadixBits; ++b) {
+        for (int b = 0; b < BITS; ++b) {
             const uint64_t ones = __ballot((d >> b) & 1u);
             peers &= ((d >> b) & 1u) ? ones : ~ones;
         }
         const uint32_t lower = (uint32_t)__popcll(peers & below);
-        const uint32_t pre = s_cnt[w][d];
-        if (valid && lower == 0) s_cnt[w][d] = pre + (uint32_t)__popcll(peers);
-        rank[j] = pre + lower;
+        const uint32_t pre = st.cnt[w][d];
+        if (valid && lower == 0) st.cnt[w][d] = (uint16_t)(pre + (uint32_t)__popcll(peers));
+        at[j] = (d << 16) | (pre + lower);
     }
     __syncthreads();
-    // thread d < kRadixBins owns digit d: its counts in the wavefronts, its
-    // tile start (exclusive scan over the digits) and each wavefront's base
-    const bool owner = threadIdx.x < kRadixBins;
-    const int d = threadIdx.x;
-    uint32_t c[kSortWaves], tot = 0;
+    // the digit's tile start (exclusive scan over the digits) and every
+    // wavefront's first place in its run
+    uint32_t tot = 0;
 #pragma unroll
-    for (int k = 0; k < kSortWaves; ++k) {
-        c[k] = owner ? s_cnt[k][d] : 0u;
-        tot += c[k];
-    }
+    for (int v = 0; v < kSortWaves; ++v) tot += owner ? st.cnt[v][d_own] : 0u;
     uint32_t inc = tot;
 #pragma unroll
     for (int k = 1; k < 64; k <<= 1) {
         const uint32_t o = __shfl_up(inc, k);
         if (lane >= k) inc += o;
     }
-    if (owner && lane == 63) s_wsum[w] = inc;
+    if (lane == 63) s_wsum[w] = inc;
     __syncthreads();
     if (owner) {
         uint32_t start = inc - tot;
         for (int k = 0; k < w; ++k) start += s_wsum[k];
-        s_start[d] = start;
+        s_goff[d_own] = goff - start;   // modulo 2^32: the sum with a place in the tile is below n
 #pragma unroll
-        for (int k = 0; k < kSortWaves; ++k) {
-            s_cnt[k][d] = start;
-            start += c[k];
+        for (int v = 0; v < kSortWaves; ++v) {
+            const uint32_t c = st.cnt[v][d_own];
+            st.cnt[v][d_own] = (uint16_t)start;
+            start += c;
         }
-        const int64_t oi = (int64_t)d * n_tiles + tile;
-        s_goff[d] = offs[oi] + sums[oi / kScanItems];
     }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSortRounds; ++j) at[j] += st.cnt[w][at[j] >> 16];
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kSortRounds; ++j) {
-        const int64_t e = w0 + 64 * j + lane;
-        if (e < n) {
-            const uint32_t p = s_cnt[w][(key[j] >> shift) & (kRadixBins - 1)] + rank[j];
-            s_key[p] = key[j];
-            s_idx[p] = idx[j];
-        }
+        if (w0 + 64 * j + lane >= n) continue;
+        const uint32_t p = at[j] & 0xFFFFu;
+        st.el.x[0][p] = x[j][0];
+        st.el.x[1][p] = x[j][1];
+        st.el.x[2][p] = x[j][2];
+        st.el.idx[p] = idx[j];
+        s_dig[p] = (uint16_t)(at[j] >> 16);
     }
     __syncthreads();
-    const int64_t n_tile = n - tile0 < kSortTile ? n - tile0 : kSortTile;
+    const int n_tile = (int)(n - tile0 < kSortTile ? n - tile0 : kSortTile);
 #pragma unroll 4
-    for (int k = 0; k < kSortTile / kSortThreads; ++k) {
-        const int p = k * kSortThreads + threadIdx.x;
-        if (p < n_tile) {
-            const uint32_t kp = s_key[p], ip = s_idx[p];
-            const uint32_t dd = (kp >> shift) & (kRadixBins - 1);
-            const int64_t dest = (int64_t)s_goff[dd] + (p - (int64_t)s_start[dd]);
-            if (LAST) {
-                idx_out[dest] = ip;
-                pos_out[3 * dest] = pos[3 * (int64_t)ip];
-                pos_out[3 * dest + 1] = pos[3 * (int64_t)ip + 1];
-                pos_out[3 * dest + 2] = pos[3 * (int64_t)ip + 2];
-            } else {
-                keys_out[dest] = kp;
-                idx_out[dest] = ip;
-            }
+    for (int p = threadIdx.x; p < n_tile; p += kSortThreads) {
+        const int64_t dest = (int64_t)(uint32_t)(s_goff[s_dig[p]] + (uint32_t)p);
+        if (DST == kRecords) {
+            buf.rec[dest] = make_float4(st.el.x[0][p], st.el.x[1][p], st.el.x[2][p], __uint_as_float(st.el.idx[p]));
+        } else {
+            buf.pos_out[3 * dest] = st.el.x[0][p];
+            buf.pos_out[3 * dest + 1] = st.el.x[1][p];
+            buf.pos_out[3 * dest + 2] = st.el.x[2][p];
+            buf.perm[dest] = st.el.idx[p];
         }
     }
 }
@@ -540,13 +553,17 @@ extern "C" sgrid_status sgrid_probe_integral_field(const sgrid_grid *g, const fl
 namespace {
 constexpr int64_t kSortMaxParticles = 0xFFFFFFFFll;   // 32-bit permutation entries
 
-// Layout of the sort's workspace for n particles: key and index ping-pong
-// buffers (when there is more than one pass), the digit counts of every tile
-// and the scan's block totals, each 256-byte aligned.
+// Passes of the sort and the layout of its workspace for n particles: the
+// records (when there is more than one pass), the digit counts of every tile
+// and the scan's block totals, each 256-byte aligned.  As few passes as nine bits
+// allow, and the digits as narrow as that many passes allow (7 bits at the
+// least): the runs that a tile writes grow as the digits shrink.  At 1e7
+// particles on 128^3 cells (21 bits) two passes of 11 bits took 356 us, three
+// of 7 take 320.
 struct SortPlan {
-    int passes = 0;
+    int passes = 0, bits = kMaxBits;
     int64_t n_tiles = 0, n_counts = 0, n_sums = 0;
-    int64_t off_keys[2] = {0, 0}, off_idx[2] = {0, 0}, off_counts = 0, off_sums = 0, bytes = 0;
+    int64_t off_counts = 0, off_sums = 0, bytes = 0;
 };
 
 int64_t align256(int64_t b) { return (b + 255) / 256 * 256; }
@@ -555,18 +572,13 @@ SortPlan sort_plan(const sgrid_grid *g, int64_t n) {
     SortPlan s;
     int bits_axis = 0;
     while ((1 << bits_axis) < g->M) ++bits_axis;
-    s.passes = std::max(1, (3 * bits_axis + kRadixBits - 1) / kRadixBits);
+    const int key_bits = std::max(1, 3 * bits_axis);
+    s.passes = (key_bits + kMaxBits - 1) / kMaxBits;
+    s.bits = std::max(7, (key_bits + s.passes - 1) / s.passes);
     s.n_tiles = (n + kSortTile - 1) / kSortTile;
-    s.n_counts = (int64_t)kRadixBins * s.n_tiles;
+    s.n_counts = ((int64_t)1 << s.bits) * s.n_tiles;
     s.n_sums = (s.n_counts + kScanItems - 1) / kScanItems;
-    int64_t b = 0;
-    if (s.passes > 1)
-        for (int k = 0; k < 2; ++k) {
-            s.off_keys[k] = b;
-            b += align256(4 * n);
-            s.off_idx[k] = b;
-            b += align256(4 * n);
-        }
+    int64_t b = s.passes > 1 ? align256(16 * n) : 0;
     s.off_counts = b;
     b += align256(4 * s.n_counts);
     s.off_sums = b;
@@ -575,25 +587,37 @@ SortPlan sort_plan(const sgrid_grid *g, int64_t n) {
     return s;
 }
 
-template <bool FIRST, bool LAST>
-sgrid_status radix_pass(const sgrid_grid *g, const float *pos, const uint32_t *keys_in, const uint32_t *idx_in,
-                        int64_t n, int shift, const SortPlan &sp, uint32_t *counts, uint32_t *sums,
-                        uint32_t *keys_out, uint32_t *idx_out, float *pos_out, hipStream_t st) {
+template <int BITS, SortPlace SRC, SortPlace DST>
+sgrid_status radix_pass(const sgrid_grid *g, const SortBuffers &buf, int64_t n, int shift, const SortPlan &sp,
+                        uint32_t *counts, uint32_t *sums, hipStream_t st) {
     const float inv_h = (float)(1.0 / g->h);
-    // the first of several passes: the counts store the keys where the scatter reads them
-    uint32_t *first_keys = FIRST && !LAST ? const_cast<uint32_t *>(keys_in) : nullptr;
-    hipLaunchKernelGGL(radix_count_kernel<FIRST>, dim3((unsigned)sp.n_tiles), dim3(256), 0, st, pos, keys_in, n, g->M,
-                       inv_h, shift, counts, sp.n_tiles, first_keys);
+    const dim3 tiles((unsigned)sp.n_tiles);
+    hipLaunchKernelGGL((radix_count_kernel<BITS, SRC>), tiles, dim3(256), 0, st, buf, n, g->M, inv_h, shift, counts,
+                       sp.n_tiles);
     SG_CHECK_LAUNCH("sort digit counts");
     hipLaunchKernelGGL(scan_block_kernel, dim3((unsigned)sp.n_sums), dim3(1024), 0, st, counts, sp.n_counts, sums);
     SG_CHECK_LAUNCH("sort scan");
-    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(1024), 0, st, sums, sp.n_sums);
-    SG_CHECK_LAUNCH("sort scan of block totals");
-    hipLaunchKernelGGL((radix_scatter_kernel<FIRST, LAST>), dim3((unsigned)sp.n_tiles), dim3(kSortThreads), 0, st, pos,
-                       keys_in, idx_in, n, g->M, inv_h, shift, (const uint32_t *)counts, (const uint32_t *)sums,
-                       sp.n_tiles, keys_out, idx_out, pos_out);
+    if (sp.n_sums > 1) {
+        hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(1024), 0, st, sums, sp.n_sums);
+        SG_CHECK_LAUNCH("sort scan of block totals");
+    }
+    hipLaunchKernelGGL((radix_scatter_kernel<BITS, SRC, DST>), tiles, dim3(kSortThreads), 0, st, buf, n, g->M, inv_h,
+                       shift, counts, sums, sp.n_tiles);
     SG_CHECK_LAUNCH("sort scatter");
     return SGRID_OK;
+}
+
+// Pass p of the plan; the last one writes the outputs, and the ones before it
+// alternate between the workspace and them.
+template <int BITS>
+sgrid_status sort_pass(const sgrid_grid *g, const SortBuffers &buf, int64_t n, int p, const SortPlan &sp,
+                       uint32_t *counts, uint32_t *sums, hipStream_t st) {
+    const bool to_outputs = (sp.passes - 1 - p) % 2 == 0;
+    const int shift = p * BITS;
+    if (p == 0 && to_outputs) return radix_pass<BITS, kInput, kOutputs>(g, buf, n, shift, sp, counts, sums, st);
+    if (p == 0) return radix_pass<BITS, kInput, kRecords>(g, buf, n, shift, sp, counts, sums, st);
+    if (to_outputs) return radix_pass<BITS, kRecords, kOutputs>(g, buf, n, shift, sp, counts, sums, st);
+    return radix_pass<BITS, kOutputs, kRecords>(g, buf, n, shift, sp, counts, sums, st);
 }
 }  // namespace
 
@@ -622,21 +646,13 @@ extern "C" sgrid_status sgrid_sort_particles(const sgrid_grid *g, const float *p
     SG_REQUIRE(sp.n_tiles <= kMaxGrid, "too many particles for one launch");
     hipStream_t st = sg_stream(stream);
     char *ws = static_cast<char *>(workspace);
-    uint32_t *keys[2] = {(uint32_t *)(ws + sp.off_keys[0]), (uint32_t *)(ws + sp.off_keys[1])};
-    uint32_t *idx[2] = {(uint32_t *)(ws + sp.off_idx[0]), (uint32_t *)(ws + sp.off_idx[1])};
+    const SortBuffers buf{pos, (float4 *)ws, pos_sorted, perm};
     uint32_t *counts = (uint32_t *)(ws + sp.off_counts), *sums = (uint32_t *)(ws + sp.off_sums);
-    sgrid_status s;
-    if (sp.passes == 1)
-        return radix_pass<true, true>(g, pos, nullptr, nullptr, n, 0, sp, counts, sums, nullptr, perm, pos_sorted, st);
-    // (keys[1] holds the first pass's keys until the second pass writes it)
-    s = radix_pass<true, false>(g, pos, keys[1], nullptr, n, 0, sp, counts, sums, keys[0], idx[0], nullptr, st);
-    if (s != SGRID_OK) return s;
-    int cur = 0;
-    for (int p = 1; p + 1 < sp.passes; ++p, cur ^= 1) {
-        s = radix_pass<false, false>(g, pos, keys[cur], idx[cur], n, p * kRadixBits, sp, counts, sums, keys[cur ^ 1],
-                                     idx[cur ^ 1], nullptr, st);
+    for (int p = 0; p < sp.passes; ++p) {
+        const sgrid_status s = sp.bits == 9   ? sort_pass<9>(g, buf, n, p, sp, counts, sums, st)
+                               : sp.bits == 8 ? sort_pass<8>(g, buf, n, p, sp, counts, sums, st)
+                                              : sort_pass<7>(g, buf, n, p, sp, counts, sums, st);
         if (s != SGRID_OK) return s;
     }
-    return radix_pass<false, true>(g, pos, keys[cur], idx[cur], n, (sp.passes - 1) * kRadixBits, sp, counts, sums,
-                                   nullptr, perm, pos_sorted, st);
+    return SGRID_OK;
 }
