@@ -37,120 +37,178 @@ __device__ __forceinline__ void tap_sums(const float *V, int i, int j, int k, fl
 // The cut fractions of the 7^3 points -1..5 of a package from its staged
 // 9^3 phi window f, by the wavefront's 64 lanes.  A point more than half a
 // cell (in the 1-norm of its gradient) from the surface has V = 0 or 1 by the
-// sign of phi; the cut points are listed (ballot, in LDS) and evaluated one
-// per lane afterwards, so the case code runs once per 64 cut points rather
-// than once per 64 window points.  A saturated point's value is the one the
-// fraction returns (see fraction_saturated).
-__device__ __forceinline__ void window_fractions(const float *f, int lane, float inv_h, float inv_2h, float *V,
-                                                 uint16_t *cut_list) {
+// sign of phi (the value the fraction returns, see fraction_saturated); the cut
+// points are listed (ballot, in LDS) and evaluated one per lane afterwards, so
+// the case code runs once per 64 cut points rather than once per 64 window
+// points.  The tests take one window row of seven per lane (49 lanes): the row's
+// and its four neighbour rows' values are read at constant offsets, and the
+// fractions written as two 16-byte words.  The kernel is bound by vector issue,
+// and a point per lane and step cost 45 instructions each for its index and
+// addresses (six steps); a row costs 17 per point (seven).
+// Returns true when no point is cut and all lie on one side, *side = V there.
+__device__ __forceinline__ bool window_fractions(const float *f, int lane, float inv_h, float inv_2h, float *V,
+                                                 uint32_t *cut_list, float *side) {
     const uint64_t below = (1ull << lane) - 1ull;
+    const int rl = min(lane, kVol * kVol - 1);   // lanes past the rows repeat the last one
+    const int ry = rl % kVol, rz = rl / kVol;
+    const int w0 = 1 + kWin * ((ry + 1) + kWin * (rz + 1)), v0 = vidx(0, ry - 1, rz - 1);
+    const float *c = f + w0;
+    float v[kVol];
     int n_cut = 0;
+    uint64_t pos = 0, neg = 0;
 #pragma unroll
-    for (int u = 0; u < (kVolN + 63) / 64; ++u) {
-        const int v = lane + 64 * u;
-        const int vc = min(v, kVolN - 1);
-        const int x = vc % kVol, y = (vc / kVol) % kVol, z = vc / (kVol * kVol);   // window coords + 1
-        const int c = (x + 1) + kWin * ((y + 1) + kWin * (z + 1));
-        const float a = f[c] * inv_h;
-        const float gx = (f[c + 1] - f[c - 1]) * inv_2h;
-        const float gy = (f[c + kWin] - f[c - kWin]) * inv_2h;
-        const float gz = (f[c + kWin * kWin] - f[c - kWin * kWin]) * inv_2h;
-        const bool sat = sgrid::fraction_saturated(a, gx, gy, gz);
-        if (v < kVolN && sat) V[vidx(x - 1, y - 1, z - 1)] = a > 0.0f ? 1.0f : 0.0f;
-        const bool cut = v < kVolN && !sat;
-        const uint64_t m = __ballot(cut);
-        if (cut) cut_list[n_cut + (int)__popcll(m & below)] = (uint16_t)v;
+    for (int x = 0; x < kVol; ++x) {
+        const float a = c[x] * inv_h;
+        const float s1 = (fabsf(c[x + 1] - c[x - 1]) + fabsf(c[x + kWin] - c[x - kWin]) +
+                          fabsf(c[x + kWin * kWin] - c[x - kWin * kWin])) * inv_2h;
+        const bool cut = !(fabsf(a) > 0.51f * s1 && s1 < 1e30f);
+        const bool above = a > 0.0f;
+        v[x] = above ? 1.0f : 0.0f;
+        pos |= __ballot(above);
+        neg |= __ballot(!above);
+        const uint64_t m = __ballot(cut && lane < kVol * kVol);
+        if (cut && lane < kVol * kVol) 
+            cut_list[n_cut + (int)__popcll(m & below)] = (uint32_t)((w0 + x) | ((v0 + ((x - 1) & 7)) << 16));
         n_cut += (int)__popcll(m);
     }
+    if (n_cut == 0 && (pos == 0ull || neg == 0ull)) {
+        *side = v[0];
+        return true;
+    }
+    float4 *row = reinterpret_cast<float4 *>(V + v0);
+    row[0] = make_float4(v[1], v[2], v[3], v[4]);
+    row[1] = make_float4(v[5], v[6], 0.f, v[0]);
     __builtin_amdgcn_wave_barrier();
     for (int t = lane; t < n_cut; t += 64) {
-        const int v = cut_list[t];
-        const int x = v % kVol, y = (v / kVol) % kVol, z = v / (kVol * kVol);
-        const int c = (x + 1) + kWin * ((y + 1) + kWin * (z + 1));
-        const float gx = (f[c + 1] - f[c - 1]) * inv_2h;
-        const float gy = (f[c + kWin] - f[c - kWin]) * inv_2h;
-        const float gz = (f[c + kWin * kWin] - f[c - kWin * kWin]) * inv_2h;
-        V[vidx(x - 1, y - 1, z - 1)] = sgrid::plane_cube_fraction(f[c] * inv_h, gx, gy, gz);
+        const uint32_t u = cut_list[t];   // window index, fraction index
+        const int w = (int)(u & 0xFFFFu);
+        const float gx = (f[w + 1] - f[w - 1]) * inv_2h;
+        const float gy = (f[w + kWin] - f[w - kWin]) * inv_2h;
+        const float gz = (f[w + kWin * kWin] - f[w - kWin * kWin]) * inv_2h;
+        V[u >> 16] = sgrid::plane_cube_fraction(f[w] * inv_h, gx, gy, gz);
     }
+    return false;
 }
 
-// The 9^3 phi window of a package into LDS (x fastest, window coordinates
-// -2..6), one window row of 9 per lane and step (81 rows): x = -2, -1 from
-// the -x neighbour's row (8-byte load), x = 0..3 the package's own row
-// (16-byte load), x = 4..6 from the +x neighbour's row (16-byte load, the
-// fourth value unused).  The neighbours through the 27-entry row ids with the
-// index shift of Sec. 5.2.
-__device__ __forceinline__ void stage_window_rows(const float *__restrict__ phi, const uint32_t *ids, int lane,
-                                                  float *f) {
-    constexpr int kRows = kWin * kWin;
-    constexpr int kSteps = (kRows + 63) / 64;
+// The 9^3 phi window of a package (x fastest, window coordinates -2..6), one
+// window row of 9 per lane and step (81 rows): x = -2, -1 from the -x
+// neighbour's row (8-byte load), x = 0..3 the package's own row (16-byte load),
+// x = 4..6 from the +x neighbour's row (16-byte load, the fourth value unused).
+// The neighbours through the package's 27-entry row, held by lanes 0..26, with
+// the index shift of Sec. 5.2.
+struct WindowRows {
+    static constexpr int kRows = kWin * kWin, kSteps = (kRows + 63) / 64;
+    int row[kSteps], slot[kSteps];   // the lane's rows: offset in a package, neighbour slot of x = -1
     float2 m[kSteps];
     float4 c[kSteps], q[kSteps];
+
+    __device__ __forceinline__ explicit WindowRows(int lane) {
 #pragma unroll
-    for (int u = 0; u < kSteps; ++u) {
-        const int r = min(lane + 64 * u, kRows - 1);
-        const int y = r % kWin - 2, z = r / kWin - 2;
-        const int ky = (y + 4) >> 2, kz = (z + 4) >> 2;
-        const int row = 4 * ((y + 4 - 4 * ky) + 4 * (z + 4 - 4 * kz));
-        const int s = 3 * ky + 9 * kz;
-        m[u] = *reinterpret_cast<const float2 *>(phi + (int64_t)ids[s] * 64 + row + 2);
-        c[u] = *reinterpret_cast<const float4 *>(phi + (int64_t)ids[s + 1] * 64 + row);
-        q[u] = *reinterpret_cast<const float4 *>(phi + (int64_t)ids[s + 2] * 64 + row);
-    }
-#pragma unroll
-    for (int u = 0; u < kSteps; ++u) {
-        const int r = lane + 64 * u;
-        if (r < kRows) {
-            float *d = f + kWin * r;
-            d[0] = m[u].x;
-            d[1] = m[u].y;
-            d[2] = c[u].x;
-            d[3] = c[u].y;
-            d[4] = c[u].z;
-            d[5] = c[u].w;
-            d[6] = q[u].x;
-            d[7] = q[u].y;
-            d[8] = q[u].z;
+        for (int u = 0; u < kSteps; ++u) {
+            const int r = min(lane + 64 * u, kRows - 1);
+            const int y = r % kWin - 2, z = r / kWin - 2;
+            const int ky = (y + 4) >> 2, kz = (z + 4) >> 2;
+            row[u] = 4 * ((y + 4 - 4 * ky) + 4 * (z + 4 - 4 * kz));
+            slot[u] = 3 * ky + 9 * kz;
         }
     }
-}
+    __device__ __forceinline__ void load(const float *__restrict__ phi, uint32_t id) {
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+            const uint32_t im = __shfl(id, slot[u]), ic = __shfl(id, slot[u] + 1), ip = __shfl(id, slot[u] + 2);
+            m[u] = *reinterpret_cast<const float2 *>(phi + (int64_t)im * 64 + row[u] + 2);
+            c[u] = *reinterpret_cast<const float4 *>(phi + (int64_t)ic * 64 + row[u]);
+            q[u] = *reinterpret_cast<const float4 *>(phi + (int64_t)ip * 64 + row[u]);
+        }
+    }
+    __device__ __forceinline__ void store(float *f, int lane) const {
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+            const int r = lane + 64 * u;
+            if (r < kRows) {
+                float *d = f + kWin * r;
+                d[0] = m[u].x;
+                d[1] = m[u].y;
+                d[2] = c[u].x;
+                d[3] = c[u].y;
+                d[4] = c[u].z;
+                d[5] = c[u].w;
+                d[6] = q[u].x;
+                d[7] = q[u].y;
+                d[8] = q[u].z;
+            }
+        }
+    }
+};
 
 // FIELD = false: the core packages of `list`, output [4][n * 64] in list
 // order.  FIELD = true: every activated package (ids 2 .. n + 1, `list`
 // unused), output one float4 (K_W, h K_grad) per data point in the packed
 // blocked layout of the probe fields.  Each wavefront works on its own
-// package and LDS slices alone, so it waits for no other.
+// packages and LDS slices alone, so it waits for no other.  It takes `per`
+// consecutive packages: the lane's window rows are worked out once (64 of the
+// 352 vector instructions a package took), and a package's rows are requested
+// before the one before it is evaluated.  Bound by vector issue (288
+// instructions a package, 71 % of the issue slots): the field of the torus at
+// 1024^3 points (580 k packages) takes 300 us, from 390 with one package per
+// wavefront, a window point per lane and step, and the taps of one-sided
+// windows summed; workgroups in XCD-aware order took 337 instead of 330.
+// A plane stride that frees the tests' reads of bank conflicts cost registers
+// and a wavefront per SIMD: 309.
+constexpr int kPlainPkgs = 4;      // at most
+constexpr int kPlainWaves = 6144;  // resident at 24 per CU: fewer packages take a wavefront each
+
+int64_t plain_per_wave(int64_t n) { return n < 2 * kPlainWaves ? 1 : (n < kPlainPkgs * kPlainWaves ? 2 : kPlainPkgs); }
+
 template <bool FIELD>
 __global__ __launch_bounds__(256) void integrals_plain_kernel(const float *__restrict__ phi,
                                                               const uint32_t *__restrict__ nbr,
                                                               const uint32_t *__restrict__ list,
-                                                              int64_t n, float inv_h, float inv_2h,
+                                                              int64_t n, int per, float inv_h, float inv_2h,
                                                               float *__restrict__ out) {
     __shared__ float s_phi[4][kWinN];
     __shared__ __align__(16) float s_v[4][kVWinN];
-    __shared__ uint16_t s_cut[4][kVolN + 1];
-    __shared__ uint32_t s_ids[4][27];
+    __shared__ uint32_t s_cut[4][kVolN + 1];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int64_t ci = (int64_t)blockIdx.x * 4 + w;
-    if (ci >= n) return;
-    const int64_t p = FIELD ? ci + 2 : (int64_t)list[ci];
-    if (lane < 27) s_ids[w][lane] = nbr[p * 27 + lane];
-    __builtin_amdgcn_wave_barrier();
-    stage_window_rows(phi, s_ids[w], lane, s_phi[w]);
-    __builtin_amdgcn_wave_barrier();
-    window_fractions(s_phi[w], lane, inv_h, inv_2h, s_v[w], s_cut[w]);
-    __builtin_amdgcn_wave_barrier();
+    const int64_t c0 = ((int64_t)blockIdx.x * 4 + w) * per;
+    if (c0 >= n) return;
+    const int n_pkgs = (int)(n - c0 < per ? n - c0 : per);
+    auto package = [&](int g) -> int64_t {   // past the last: the last again
+        const int64_t ci = c0 + min(g, n_pkgs - 1);
+        return FIELD ? ci + 2 : (int64_t)list[ci];
+    };
+    auto neighbours = [&](int g) { return nbr[package(g) * 27 + min(lane, 26)]; };
     const int i = lane & 3, j = (lane >> 2) & 3, k = lane >> 4;
-    float kw, kx, ky, kz;
-    tap_sums(s_v[w], i, j, k, kw, kx, ky, kz);
-    if (FIELD) {
-        reinterpret_cast<float4 *>(out)[p * 64 + blocked_index(i, j, k)] = make_float4(kw, kx, ky, kz);
-    } else {
-        const int64_t o = ci * 64 + lane, stride = n * 64;
-        out[o] = kw;
-        out[stride + o] = kx;
-        out[2 * stride + o] = ky;
-        out[3 * stride + o] = kz;
+    WindowRows rows(lane);
+    rows.load(phi, neighbours(0));
+    uint32_t id = neighbours(1);
+#pragma unroll 1
+    for (int g = 0; g < n_pkgs; ++g) {
+        rows.store(s_phi[w], lane);
+        __builtin_amdgcn_wave_barrier();
+        rows.load(phi, id);
+        id = neighbours(g + 2);
+        float kw, kx, ky, kz, side;
+        if (window_fractions(s_phi[w], lane, inv_h, inv_2h, s_v[w], s_cut[w], &side)) {
+            // a window on one side of the surface (most inner packages'): its sums without its taps
+            sgrid::tap_sums([](int, int, int) { return 1.0f; }, 0, 0, 0, kw, kx, ky, kz);
+            kw = side > 0.0f ? kw : 0.0f;
+            kx = ky = kz = 0.0f;
+        } else {
+            __builtin_amdgcn_wave_barrier();
+            tap_sums(s_v[w], i, j, k, kw, kx, ky, kz);
+        }
+        __builtin_amdgcn_wave_barrier();
+        const int64_t ci = c0 + g;
+        if (FIELD) {
+            reinterpret_cast<float4 *>(out)[(ci + 2) * 64 + blocked_index(i, j, k)] = make_float4(kw, kx, ky, kz);
+        } else {
+            const int64_t o = ci * 64 + lane, stride = n * 64;
+            out[o] = kw;
+            out[stride + o] = kx;
+            out[2 * stride + o] = ky;
+            out[3 * stride + o] = kz;
+        }
     }
 }
 
@@ -293,9 +351,9 @@ namespace sgrid {
 
 sgrid_status launch_integrals_plain(const sgrid_grid *g, const float *phi, float *out, hipStream_t st) {
     if (g->n_core == 0) return SGRID_OK;
-    const int64_t nb = (g->n_core + 3) / 4;
+    const int64_t per = plain_per_wave(g->n_core), nb = (g->n_core + 4 * per - 1) / (4 * per);
     hipLaunchKernelGGL(integrals_plain_kernel<false>, dim3((unsigned)nb), dim3(256), 0, st, phi, g->nbr,
-                       g->core_list, g->n_core, (float)(1.0 / g->h), (float)(0.5 / g->h), out);
+                       g->core_list, g->n_core, (int)per, (float)(1.0 / g->h), (float)(0.5 / g->h), out);
     SG_CHECK_LAUNCH("plain integrals");
     return SGRID_OK;
 }
@@ -358,10 +416,10 @@ extern "C" sgrid_status sgrid_compute_integral_field(const sgrid_grid *g, const 
     hipLaunchKernelGGL(integral_far_rows_kernel, dim3(1), dim3(128), 0, st, (float4 *)field, (float)c_full);
     SG_CHECK_LAUNCH("integral field far-field rows");
     if (g->P == 0) return SGRID_OK;
-    const int64_t nb = (g->P + 3) / 4;
+    const int64_t per = plain_per_wave(g->P), nb = (g->P + 4 * per - 1) / (4 * per);
     SG_REQUIRE(nb <= kMaxGrid, "too many packages for one launch");
     hipLaunchKernelGGL(integrals_plain_kernel<true>, dim3((unsigned)nb), dim3(256), 0, st, phi, g->nbr,
-                       (const uint32_t *)nullptr, g->P, (float)(1.0 / g->h), (float)(0.5 / g->h), field);
+                       (const uint32_t *)nullptr, g->P, (int)per, (float)(1.0 / g->h), (float)(0.5 / g->h), field);
     SG_CHECK_LAUNCH("integral field");
     return SGRID_OK;
 }
