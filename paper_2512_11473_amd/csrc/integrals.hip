@@ -15,18 +15,15 @@ namespace {
 
 using sgrid::kWin;            // phi window edge (-2..6)
 using sgrid::kWinN;
-constexpr int kVol = 7;       // V window edge (-1..5)
-constexpr int kVolN = kVol * kVol * kVol;
+using sgrid::kVol;            // V window edge (-1..5)
+using sgrid::kVolN;
+using sgrid::kVPlane;
+using sgrid::kVRow;
+using sgrid::kVWinN;
+using sgrid::vidx;
 
 using sgrid::wendland_u;
 using sgrid::wendland_dr_over_r_u;
-
-// LDS layout of the 7^3 cut fractions V (window coordinates -1..5): rows of 8
-// along x (x = 0..5 at 0..5, x = -1 at 7, 6 unused), 8 floats per y step and
-// 60 per z step.  A row is two aligned 16-byte words, and the 32 lanes of a
-// half-wavefront (i, j in 0..3, k in 0..1) read 32 distinct banks at any tap.
-constexpr int kVRow = 8, kVPlane = 60, kVWinN = kVol * kVPlane;
-__device__ __forceinline__ int vidx(int x, int y, int z) { return (x & 7) + kVRow * (y + 1) + kVPlane * (z + 1); }
 
 // The 32 taps of data point (i, j, k) over the LDS window of cut fractions.
 __device__ __forceinline__ void tap_sums(const float *V, int i, int j, int k, float &kw, float &kx, float &ky,
@@ -90,57 +87,6 @@ __device__ __forceinline__ bool window_fractions(const float *f, int lane, float
     return false;
 }
 
-// The 9^3 phi window of a package (x fastest, window coordinates -2..6), one
-// window row of 9 per lane and step (81 rows): x = -2, -1 from the -x
-// neighbour's row (8-byte load), x = 0..3 the package's own row (16-byte load),
-// x = 4..6 from the +x neighbour's row (16-byte load, the fourth value unused).
-// The neighbours through the package's 27-entry row, held by lanes 0..26, with
-// the index shift of Sec. 5.2.
-struct WindowRows {
-    static constexpr int kRows = kWin * kWin, kSteps = (kRows + 63) / 64;
-    int row[kSteps], slot[kSteps];   // the lane's rows: offset in a package, neighbour slot of x = -1
-    float2 m[kSteps];
-    float4 c[kSteps], q[kSteps];
-
-    __device__ __forceinline__ explicit WindowRows(int lane) {
-#pragma unroll
-        for (int u = 0; u < kSteps; ++u) {
-            const int r = min(lane + 64 * u, kRows - 1);
-            const int y = r % kWin - 2, z = r / kWin - 2;
-            const int ky = (y + 4) >> 2, kz = (z + 4) >> 2;
-            row[u] = 4 * ((y + 4 - 4 * ky) + 4 * (z + 4 - 4 * kz));
-            slot[u] = 3 * ky + 9 * kz;
-        }
-    }
-    __device__ __forceinline__ void load(const float *__restrict__ phi, uint32_t id) {
-#pragma unroll
-        for (int u = 0; u < kSteps; ++u) {
-            const uint32_t im = __shfl(id, slot[u]), ic = __shfl(id, slot[u] + 1), ip = __shfl(id, slot[u] + 2);
-            m[u] = *reinterpret_cast<const float2 *>(phi + (int64_t)im * 64 + row[u] + 2);
-            c[u] = *reinterpret_cast<const float4 *>(phi + (int64_t)ic * 64 + row[u]);
-            q[u] = *reinterpret_cast<const float4 *>(phi + (int64_t)ip * 64 + row[u]);
-        }
-    }
-    __device__ __forceinline__ void store(float *f, int lane) const {
-#pragma unroll
-        for (int u = 0; u < kSteps; ++u) {
-            const int r = lane + 64 * u;
-            if (r < kRows) {
-                float *d = f + kWin * r;
-                d[0] = m[u].x;
-                d[1] = m[u].y;
-                d[2] = c[u].x;
-                d[3] = c[u].y;
-                d[4] = c[u].z;
-                d[5] = c[u].w;
-                d[6] = q[u].x;
-                d[7] = q[u].y;
-                d[8] = q[u].z;
-            }
-        }
-    }
-};
-
 // FIELD = false: the core packages of `list`, output [4][n * 64] in list
 // order.  FIELD = true: every activated package (ids 2 .. n + 1, `list`
 // unused), output one float4 (K_W, h K_grad) per data point in the packed
@@ -179,14 +125,24 @@ __global__ __launch_bounds__(256) void integrals_plain_kernel(const float *__res
     };
     auto neighbours = [&](int g) { return nbr[package(g) * 27 + min(lane, 26)]; };
     const int i = lane & 3, j = (lane >> 2) & 3, k = lane >> 4;
-    WindowRows rows(lane);
-    rows.load(phi, neighbours(0));
-    uint32_t id = neighbours(1);
+    sgrid::WindowRows<64> rows(lane);
+    uint32_t id = neighbours(0);
+    auto load = [&](uint32_t ids) { rows.load(phi, [&](int slot) { return __shfl(ids, slot); }); };
+    load(id);
+    id = neighbours(1);
 #pragma unroll 1
     for (int g = 0; g < n_pkgs; ++g) {
-        rows.store(s_phi[w], lane);
+#pragma unroll
+        for (int u = 0; u < rows.kSteps; ++u) {
+            float v[kWin];
+            rows.values(u, v);
+            if (lane + 64 * u < rows.kRows) {
+#pragma unroll
+                for (int x = 0; x < kWin; ++x) s_phi[w][kWin * (lane + 64 * u) + x] = v[x];
+            }
+        }
         __builtin_amdgcn_wave_barrier();
-        rows.load(phi, id);
+        load(id);
         id = neighbours(g + 2);
         float kw, kx, ky, kz, side;
         if (window_fractions(s_phi[w], lane, inv_h, inv_2h, s_v[w], s_cut[w], &side)) {

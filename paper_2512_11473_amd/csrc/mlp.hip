@@ -830,7 +830,8 @@ namespace {
 
 using sgrid::kWin;                     // phi window of a package, local -2..6
 using sgrid::kWinN;
-constexpr int kVol = 7, kVolN = 343;   // points -1..5 whose cut fraction a tap may use
+using sgrid::kVol;
+using sgrid::kVolN;
 
 // Stages the 9^3 phi window of core package p into LDS (all threads of the block).
 __device__ __forceinline__ void stage_window(const float *__restrict__ phi, const uint32_t *__restrict__ nbr,
@@ -908,8 +909,13 @@ struct LearnLds {
     float phi[kWinN + 3];
     uint32_t xhl[kWinN + 3];   // BF16 hi (low half) and lo (high half) parts of the window's phi / h
     uint32_t ids[28];
-    uint8_t sat[kVolN + 13];
+    float v[sgrid::kVWinN];    // V of the saturated tap points (1 or 0), NaN for the others
 };
+
+// The gate's sums over one window row for the four positions along x: r0 and
+// its x moment.  Kept for the 81 rows of both packages in the activation area
+// (past W1's two slices, free until layer 1 ends).
+constexpr int kRowSums = 4 * kWin * kWin;
 
 // The weights of layers 1 and 2 pass through LDS, one 32-input slice (128
 // rows x 32 BF16, 8 KB) per step, so the workgroup's four wavefronts read each
@@ -1096,41 +1102,73 @@ __global__ __launch_bounds__(256, 3) void learned_kernel(MlpDev W, const float *
     const int64_t p = core_list[ci];
     if (t128 < 27) L.ids[t128] = nbr[p * 27 + t128];
     __syncthreads();
-    sgrid::stage_window_part<128>(phi, L.ids, t128, L.phi);
-    __syncthreads();
-    for (int v = t128; v < kVolN; v += 128) {
-        const int x = v % kVol + 1, y = (v / kVol) % kVol + 1, z = v / (kVol * kVol) + 1;
-        const int c = x + kWin * (y + kWin * z);
-        const float gx = (L.phi[c + 1] - L.phi[c - 1]) * inv_2h;
-        const float gy = (L.phi[c + kWin] - L.phi[c - kWin]) * inv_2h;
-        const float gz = (L.phi[c + kWin * kWin] - L.phi[c - kWin * kWin]) * inv_2h;
-        const float a = L.phi[c] * inv_h;
-        const bool sat = sgrid::fraction_saturated(a, gx, gy, gz);
-        L.sat[v] = (uint8_t)((sat ? 1 : 0) | (a > 0.f ? 2 : 0));
+    float2 *sums = reinterpret_cast<float2 *>(s_act + 2 * kWSlice);   // [package][row][x position]
+    static_assert((2 * kWSlice * sizeof(bf16)) % 8 == 0 &&
+                      2 * kWSlice * sizeof(bf16) + kLearnPkgs * kRowSums * sizeof(float2) <=
+                          kLearnPts * kActStride * sizeof(bf16),
+                  "row sums in the activation area");
+    {
+        // one window row per lane (81 of a package's 128): phi, the network
+        // inputs' hi and lo parts and the gate's row sums from its registers
+        sgrid::WindowRows<128> rows(t128);
+        rows.load(phi, [&](int s) { return L.ids[s]; });
+        float v[kWin];
+        rows.values(0, v);
+        if (t128 < rows.kRows) {
+#pragma unroll
+            for (int x = 0; x < kWin; ++x) {
+                L.phi[kWin * t128 + x] = v[x];
+                const float f = v[x] * inv_h;
+                const bf16 hi = (bf16)f;
+                const bf16 lo = (bf16)(f - (float)hi);
+                L.xhl[kWin * t128 + x] =
+                    (uint32_t)__builtin_bit_cast(uint16_t, hi) | ((uint32_t)__builtin_bit_cast(uint16_t, lo) << 16);
+            }
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const float *u = v + x;
+                const float r0 = ((u[0] + u[1]) + (u[2] + u[3])) + (u[4] + u[5]);
+                const float rx = fmaf(2.5f, u[5] - u[0], fmaf(1.5f, u[4] - u[1], 0.5f * (u[3] - u[2])));
+                sums[slot * kRowSums + 4 * t128 + x] = make_float2(r0, rx);
+            }
+        }
     }
-    for (int v = t128; v < kWinN; v += 128) {   // the network inputs, once per window value
-        const float x = L.phi[v] * inv_h;
-        const bf16 hi = (bf16)x;
-        const bf16 lo = (bf16)(x - (float)hi);
-        L.xhl[v] = (uint32_t)__builtin_bit_cast(uint16_t, hi) | ((uint32_t)__builtin_bit_cast(uint16_t, lo) << 16);
+    __syncthreads();
+    {
+        // the tap points' saturation, a row of seven per lane and the package's
+        // two wavefronts sharing its points
+        const int rl = min(lane, kVol * kVol - 1);
+        const int ry = rl % kVol, rz = rl / kVol;
+        const float *c = L.phi + 1 + kWin * ((ry + 1) + kWin * (rz + 1));
+        float *vr = L.v + sgrid::vidx(0, ry - 1, rz - 1);
+        auto point = [&](int x) {   // 0..6: window coordinate x - 1
+            const float gx = (c[x + 1] - c[x - 1]) * inv_2h;
+            const float gy = (c[x + kWin] - c[x - kWin]) * inv_2h;
+            const float gz = (c[x + kWin * kWin] - c[x - kWin * kWin]) * inv_2h;
+            const float a = c[x] * inv_h;
+            const float v = a > 0.f ? 1.f : 0.f;
+            vr[(x + 7) & 7] = sgrid::fraction_saturated(a, gx, gy, gz) ? v : __builtin_nanf("");
+        };
+        if ((w & 1) == 0) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) point(x);
+        } else {
+#pragma unroll
+            for (int x = 4; x < kVol; ++x) point(x);
+        }
     }
     __syncthreads();
     const int64_t stride = n_core * 64;
     // 2. saturated points: one lane per point (the first 64 of each
     // package's 128) sums its 32 taps' fractions, 1 or 0 by the sign of phi,
     // with the plain kernels' tap sums, so the value is the plain one bit for
-    // bit; a point with a cut tap is listed
+    // bit; a point with a cut tap (NaN) is listed
     if (t128 < 64) {
         const int c = t128;
-        bool sat = true;
         float kw, kx, ky, kz;
-        sgrid::tap_sums(
-            [&](int x, int y, int z) {
-                const uint8_t f = L.sat[(x + 1) + kVol * ((y + 1) + kVol * (z + 1))];
-                sat = sat && (f & 1);
-                return (f & 2) ? 1.f : 0.f;
-            },
-            c & 3, (c >> 2) & 3, c >> 4, kw, kx, ky, kz);
+        sgrid::tap_sums([&](int x, int y, int z) { return L.v[sgrid::vidx(x, y, z)]; }, c & 3, (c >> 2) & 3, c >> 4,
+                        kw, kx, ky, kz);
+        const bool sat = kw == kw;   // a cut tap's NaN reaches the sum
         if (live) {
             if (sat) {
                 const int64_t o = ci * 64 + c;
@@ -1170,24 +1208,29 @@ __global__ __launch_bounds__(256, 3) void learned_kernel(MlpDev W, const float *
     const LearnLds &Lp = lds[pt >> 6];
     const int c = pt & 63;
     const int ci_ = c & 3, cj = (c >> 2) & 3, ck = c >> 4;
-    // (per window row: its sum and its x moment, then the row's share of the
-    // y and z moments from its sum; a wavefront without points skips both
-    // passes)
-    const int n_rows = mine > 0 ? 18 : 0;
+    // The first pass takes the rows' sums and x moments from the staging, which
+    // has them once per row and x position; each row adds its share to the y
+    // and z moments.  Fused and separate operations are written out, so that
+    // the decisions do not depend on how the loops are compiled.  A wavefront
+    // without points skips both passes.
+    const float part_f = (float)part;
+    const float ey[3] = {part_f - 2.5f, part_f - 0.5f, part_f + 1.5f};
+    const int planes = mine > 0 ? 6 : 0;
     float s0 = 0.f, sx = 0.f, sy = 0.f, sz = 0.f;
-#pragma unroll 1
-    for (int i = 0; i < n_rows; ++i) {
-        const int ez = (2 * i) / 6, ey = (2 * i) % 6 + part;
-        const float *wrow = Lp.phi + ci_ + kWin * ((cj + ey) + kWin * (ck + ez));
-        float v[6];
+    {
+        const float2 *rs = sums + (pt >> 6) * kRowSums + 4 * ((cj + part) + kWin * ck) + ci_;
+        float ez = -2.5f;
+#pragma unroll 2
+        for (int z = 0; z < planes; ++z, ez += 1.0f, rs += 4 * kWin) {
 #pragma unroll
-        for (int ex = 0; ex < 6; ++ex) v[ex] = wrow[ex];
-        const float r0 = ((v[0] + v[1]) + (v[2] + v[3])) + (v[4] + v[5]);
-        const float rx = 2.5f * (v[5] - v[0]) + (1.5f * (v[4] - v[1]) + 0.5f * (v[3] - v[2]));
-        s0 += r0;
-        sx += rx;
-        sy += (ey - 2.5f) * r0;
-        sz += (ez - 2.5f) * r0;
+            for (int m = 0; m < 3; ++m) {
+                const float2 q = rs[8 * m];
+                s0 += q.x;
+                sx += q.y;
+                sy = fmaf(ey[m], q.x, sy);
+                sz = fmaf(ez, q.x, sz);
+            }
+        }
     }
     s0 += __shfl_xor(s0, 1);
     sx += __shfl_xor(sx, 1);
@@ -1195,15 +1238,26 @@ __global__ __launch_bounds__(256, 3) void learned_kernel(MlpDev W, const float *
     sz += __shfl_xor(sz, 1);
     const float c0 = s0 / 216.f, cx = sx / 630.f, cy = sy / 630.f, cz = sz / 630.f;   // units of phi
     float rr = 0.f;
-#pragma unroll 1
-    for (int i = 0; i < n_rows; ++i) {
-        const int ez = (2 * i) / 6, ey = (2 * i) % 6 + part;
-        const float *wrow = Lp.phi + ci_ + kWin * ((cj + ey) + kWin * (ck + ez));
-        const float pyz = c0 + cy * (ey - 2.5f) + cz * (ez - 2.5f);
+    {
+#pragma clang fp contract(off)
+        float px[6], pm[3];
 #pragma unroll
-        for (int ex = 0; ex < 6; ++ex) {
-            const float e = wrow[ex] - (pyz + cx * (ex - 2.5f));
-            rr += e * e;
+        for (int x = 0; x < 6; ++x) px[x] = cx * (x - 2.5f);
+#pragma unroll
+        for (int m = 0; m < 3; ++m) pm[m] = fmaf(cy, ey[m], c0);
+        const float *wrow = Lp.phi + ci_ + kWin * ((cj + part) + kWin * ck);
+        float ez = -2.5f;
+#pragma unroll 1
+        for (int z = 0; z < planes; ++z, ez += 1.0f, wrow += kWin * kWin) {
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+                const float pyz = fmaf(cz, ez, pm[m]);
+#pragma unroll
+                for (int x = 0; x < 6; ++x) {
+                    const float e = wrow[2 * kWin * m + x] - (pyz + px[x]);
+                    rr = fmaf(e, e, rr);
+                }
+            }
         }
     }
     rr += __shfl_xor(rr, 1);
