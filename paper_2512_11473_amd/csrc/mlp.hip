@@ -928,19 +928,39 @@ constexpr int kWSlice = kH * kWRow;   // BF16 per buffered slice
 constexpr int kW1Steps = kInPad / 32, kW2Steps = kH / 32;
 
 // Thread tid's share of slice s of a [128][row_len] weight matrix: row
-// tid / 2, inputs 32 s + 16 (tid % 2) .. + 15.
+// tid % 128, inputs 32 s + 16 (tid / 128) .. + 15 (consecutive lanes take
+// consecutive rows, 20 words apart in LDS: no bank conflicts).
 struct WPart {
     bf16x8 a, b;
 };
 __device__ __forceinline__ WPart w_load(const bf16 *w, int row_len, int s, int tid) {
-    const bf16 *src = w + (tid >> 1) * row_len + 32 * s + 16 * (tid & 1);
+    const bf16 *src = w + (tid & 127) * row_len + 32 * s + 16 * (tid >> 7);
     return WPart{ld8(src), ld8(src + 8)};
 }
 __device__ __forceinline__ void w_store(bf16 *buf, const WPart &v, int tid) {
-    bf16 *dst = buf + (tid >> 1) * kWRow + 16 * (tid & 1);
+    bf16 *dst = buf + (tid & 127) * kWRow + 16 * (tid >> 7);
     *reinterpret_cast<bf16x8 *>(dst) = v.a;
     *reinterpret_cast<bf16x8 *>(dst + 8) = v.b;
 }
+
+// Activation rows in LDS.  The C layout's four row groups (q) start 4 x 68 =
+// 272 words apart, 16 modulo the 32 banks, so rows 8..15 of a tile hold their
+// 32-byte column pieces swapped in pairs: the 16 x 16 stores of a column tile
+// then cover the banks evenly.  A reader's offset changes by a lane constant.
+__device__ __forceinline__ void act_store(bf16 *s_act, int row0, int col, int q, int r, const floatx4 &z) {
+    bf16 *dst = s_act + row0 * kActStride + r + (q >> 1 ? col ^ 16 : col);
+#pragma unroll
+    for (int i = 0; i < 4; i += 2) {
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        typedef float floatx2 __attribute__((ext_vector_type(2)));
+        const floatx2 g = {gelu(z[i]), gelu(z[i + 1])};
+        const bf16x2 v = __builtin_convertvector(g, bf16x2);   // one instruction for both
+        dst[i * kActStride] = v[0];
+        dst[(i + 1) * kActStride] = v[1];
+    }
+}
+// Columns 8 q .. 8 q + 7 of a 32-column slice of row r (modulo 16).
+__device__ __forceinline__ int act_piece(int q, int r) { return 8 * (q ^ ((r >> 3) << 1)); }
 
 // The network over the listed points of TILES tiles (rows 16 tile + r of the
 // list): layer outputs through the wavefront's own activation rows, the
@@ -1010,10 +1030,7 @@ __device__ __forceinline__ void learned_network(const MlpDev &W, LearnLds *lds, 
 #pragma unroll
     for (int t = 0; t < 8; ++t)
 #pragma unroll
-        for (int m = 0; m < TILES; ++m)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                s_act[(16 * tile[m] + 4 * q + i) * kActStride + 16 * t + r] = (bf16)gelu(acc[m][t][i]);
+        for (int m = 0; m < TILES; ++m) act_store(s_act, 16 * tile[m] + 4 * q, 16 * t, q, r, acc[m][t]);
     // layer 2, W2's slices one at a time in the windows' LDS (a wavefront
     // reads back only activation rows it wrote itself)
     static_assert(sizeof(LearnLds) * kLearnPkgs >= kWSlice * sizeof(bf16), "W2 slice buffer");
@@ -1035,7 +1052,7 @@ __device__ __forceinline__ void learned_network(const MlpDev &W, LearnLds *lds, 
             for (int t = 0; t < 8; ++t) bv[t] = ld8(w2buf + (16 * t + r) * kWRow + 8 * q);
 #pragma unroll
             for (int m = 0; m < TILES; ++m) {
-                const bf16x8 a = ld8(s_act + (16 * tile[m] + r) * kActStride + 32 * s + 8 * q);
+                const bf16x8 a = ld8(s_act + (16 * tile[m] + r) * kActStride + 32 * s + act_piece(q, r));
 #pragma unroll
                 for (int t = 0; t < 8; ++t) acc[m][t] = mfma(a, bv[t], acc[m][t]);
             }
@@ -1046,10 +1063,7 @@ __device__ __forceinline__ void learned_network(const MlpDev &W, LearnLds *lds, 
 #pragma unroll
     for (int t = 0; t < 8; ++t)
 #pragma unroll
-        for (int m = 0; m < TILES; ++m)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                s_act[(16 * tile[m] + 4 * q + i) * kActStride + 16 * t + r] = (bf16)gelu(acc[m][t][i]);
+        for (int m = 0; m < TILES; ++m) act_store(s_act, 16 * tile[m] + 4 * q, 16 * t, q, r, acc[m][t]);
     // layer 3
     floatx4 y[NT];
     const float b3 = r < kOut ? W.w[oB3 + r] : 0.f;
@@ -1060,7 +1074,7 @@ __device__ __forceinline__ void learned_network(const MlpDev &W, LearnLds *lds, 
         const bf16x8 w3 = ld8(W.w3b + r * kH + 32 * s + 8 * q);
 #pragma unroll
         for (int m = 0; m < TILES; ++m)
-            y[m] = mfma(ld8(s_act + (16 * tile[m] + r) * kActStride + 32 * s + 8 * q), w3, y[m]);
+            y[m] = mfma(ld8(s_act + (16 * tile[m] + r) * kActStride + 32 * s + act_piece(q, r)), w3, y[m]);
     }
     if (r < kOut) {
 #pragma unroll
