@@ -764,11 +764,35 @@ SweepConfig current_sweep_config() {
     return c;
 }
 
-// The gradient and the Laplacian visit the packages in the sweep's order:
-// Morton (worklist) order when the configuration's sweep uses it.
-bool stencil_in_worklist_order() {
-    const int v = current_sweep_config().variant;
-    return v == 2 || v == 3 || v == 4 || v == 7;
+// The default configuration (0, 1) keeps package-id order while a field is
+// small and takes Morton order from kWorklistBytes on, where the z neighbours
+// of id order lie too far apart to stay in an XCD's L2: a sweep of the shell at
+// 1024^3 points (142 MiB a field) takes 86 us in id order and 78 in Morton order
+// (Laplacian 83 and 77), of the torus at 2048^3 (439 MiB) 255 and 224 (257 and
+// 235); at 70 MiB 32.7 and 29.3 (42 and 39), at 31 MiB (prism512) they are equal.
+constexpr double kWorklistBytes = 64.0 * 1024 * 1024;
+
+static bool default_takes_worklist(const sgrid_grid *g, const SweepConfig &c, size_t element) {
+    return c.variant == 0 && c.groups == 1 && (double)g->total() * 64.0 * (double)element >= kWorklistBytes;
+}
+
+// What a reinitialisation of n_iter sweeps runs.  The field goes through a
+// worklist-ordered copy (variant 7) in FP32 when there are sweeps enough to
+// pay for the way in and out (at 4 sweeps variant 3 is ahead up to 100 MiB, at
+// 20 variant 7); in FP64 variant 3 (torus at 900^3 points: id order 112 us,
+// variant 3 103, variant 7 110).
+static SweepConfig reinit_config(const sgrid_grid *g, size_t element, int32_t n_iter) {
+    SweepConfig c = current_sweep_config();
+    if (default_takes_worklist(g, c, element)) c.variant = element == 4 && n_iter >= 8 ? 7 : 3;
+    return c;
+}
+
+// Whether a stencil pass visits the packages in Morton (worklist) order: when
+// the configuration's sweep does, or by the rule above.
+static bool stencil_in_worklist_order(const sgrid_grid *g, size_t element) {
+    const SweepConfig c = current_sweep_config();
+    const int v = c.variant;
+    return v == 2 || v == 3 || v == 4 || v == 7 || default_takes_worklist(g, c, element);
 }
 
 // MI355X's Infinity Cache (the last level before HBM)
@@ -891,7 +915,7 @@ sgrid_status launch_cut_fractions(const sgrid_grid *g, const float *phi, float *
         set_error("too many packages for one launch");
         return SGRID_E_INVALID;
     }
-    const bool work = stencil_in_worklist_order();
+    const bool work = stencil_in_worklist_order(g, 4);
     const bool nt_store = 2.0 * (double)nt * 64.0 * 4.0 > kLastLevelCacheBytes;
     const float inv_h = (float)(1.0 / g->h), inv_2h = (float)(0.5 / g->h);
     if (work)
@@ -1002,7 +1026,7 @@ extern "C" sgrid_status sgrid_reinitialize(const sgrid_grid *g, sgrid_dtype dtyp
     SG_REQUIRE(n_iter >= 0, "n_iter must be >= 0 (got %d)", n_iter);
     SG_REQUIRE(dtype == SGRID_F32 || dtype == SGRID_F64, "unknown dtype %d", (int)dtype);
     hipStream_t st = sg_stream(stream);
-    const sgrid::SweepConfig cfg = sgrid::current_sweep_config();
+    const sgrid::SweepConfig cfg = sgrid::reinit_config(g, dtype == SGRID_F32 ? 4 : 8, n_iter);
     if (dtype == SGRID_F32)
         return sgrid::reinit_impl<float>(g, (float *)phi, (float *)scratch, n_iter, st, cfg);
     return sgrid::reinit_impl<double>(g, (double *)phi, (double *)scratch, n_iter, st, cfg);
@@ -1019,7 +1043,12 @@ static sgrid_status gradient_entry(const sgrid_grid *g, sgrid_dtype dtype, const
     hipStream_t st = sg_stream(stream);
     const int64_t nt = g->total();
     const int64_t nb = (nt + 15) / 16;
-    const bool work = sgrid::stencil_in_worklist_order();
+    // by the default's rule only the FP32 SoA gradient (torus at 2048^3: 485 us
+    // in id order, 459 in Morton order): the FP64 one is slower in Morton order
+    // (at 221 MiB a field 150 and 184 us), the packed one now faster, now slower
+    const bool tuned = sgrid::current_sweep_config().variant != 0;
+    const bool work = (tuned || (!PACKED && dtype == SGRID_F32)) &&
+                      sgrid::stencil_in_worklist_order(g, dtype == SGRID_F32 ? 4 : 8);
     // streaming stores when phi and the output together exceed the last-level
     // cache; not for the FP64 packed layout, whose four stores per lane each
     // fill only parts of lines (the cache merges them, streaming writes would
@@ -1084,7 +1113,7 @@ extern "C" sgrid_status sgrid_compute_laplacian(const sgrid_grid *g, sgrid_dtype
     hipStream_t st = sg_stream(stream);
     const int64_t nt = g->total();
     const int64_t nb = (nt + 15) / 16;
-    const bool work = sgrid::stencil_in_worklist_order();
+    const bool work = sgrid::stencil_in_worklist_order(g, dtype == SGRID_F32 ? 4 : 8);
     // streaming stores when phi and the output together exceed the last-level cache
     const bool stream_out = (double)nt * 64.0 * (dtype == SGRID_F32 ? 4.0 : 8.0) * 2.0 > sgrid::kLastLevelCacheBytes;
     if (dtype == SGRID_F32) {
