@@ -7,7 +7,16 @@
 namespace sgrid {
 
 // Precision policy: FP32 uses the hardware square root and reciprocal square
-// root (about 1 ulp); FP64 uses correctly rounded operations.
+// root (about 1 ulp).  FP64 refines the hardware's reciprocal square root y0
+// (some 26 bits) to within an ulp: with e = 1 - x y0^2, 1 / sqrt(x) = y0 (1 - e)^(-1/2)
+// = y0 (1 + e / 2 + 3 e^2 / 8 + ...), and the square root by one coupled step for
+// (sqrt(x), 1 / (2 sqrt(x))) and one residual step.  Zero and infinity keep the
+// hardware's value.  Correctly rounded square roots and division took 111 more
+// of the FP64 sweep's 392 vector instructions (817 k points: 6.4 -> 5.8 us a
+// sweep, prism512 31 -> 28); against an 80-bit evaluation the fields are as far
+// off as with them (relative error after 60 sweeps of sphere64 6.03e-17 and
+// 6.02e-17, 3 of a torus at 128^3 5.717e-17 and 5.719e-17, 100 of a prism at
+// 96^3 8.454e-17 both: the last rounding of the update).
 template <typename T>
 struct Fast;
 template <>
@@ -17,8 +26,21 @@ struct Fast<float> {
 };
 template <>
 struct Fast<double> {
-    static __device__ __forceinline__ double rsqrt(double x) { return 1.0 / ::sqrt(x); }
-    static __device__ __forceinline__ double sqrt(double x) { return ::sqrt(x); }
+    static __device__ __forceinline__ double rsqrt(double x) {
+        const double y = __builtin_amdgcn_rsq(x);
+        const double e = fma(-(x * y), y, 1.0);
+        const double z = fma(y * e, fma(e, 0.375, 0.5), y);
+        return e == e ? z : y;   // e is NaN for 0, infinity and NaN
+    }
+    static __device__ __forceinline__ double sqrt(double x) {
+        const double y = __builtin_amdgcn_rsq(x);
+        double g = x * y, h = 0.5 * y;
+        const double r = fma(-h, g, 0.5);
+        g = fma(g, r, g);
+        h = fma(h, r, h);
+        const double d = fma(-g, g, x);
+        return d == d ? fma(d, h, g) : x;   // d is NaN for 0, infinity and NaN
+    }
 };
 
 // Godunov-upwinded update of one point (Sussman-Smereka-Osher iteration),
