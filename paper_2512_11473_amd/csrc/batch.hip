@@ -54,7 +54,7 @@ __device__ __forceinline__ void st_row(float *__restrict__ p, const Row4<float> 
     if (nt)
         __builtin_nontemporal_store(v, reinterpret_cast<f4v *>(p));
     else
-        *reinterpret_cast<f4v *>(p) = v;
+        store_through(p, v);
 }
 
 struct Halo {

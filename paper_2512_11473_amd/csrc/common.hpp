@@ -149,6 +149,24 @@ __device__ __forceinline__ double row_move_keep(double v, double keep) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// 16-byte store written through the L2 (device scope, sc1) instead of left
+// dirty in it.  The eight XCDs' L2 caches (4 MiB each) do not see each other's
+// lines, so a kernel's dirty lines are written back when it ends, after its last
+// wavefront; a pass whose output the next kernel reads from everywhere pays for
+// that as a tail (prism512's sweep leaves all of its 31 MiB there).  Written
+// through, the rows leave while the kernel runs, and stay in the Infinity Cache
+// (which the streaming hint would bypass).  Sweeps with plain stores and with
+// these: torus at 256^3 points 5.8 and 5.2 us, prism512 14.6 and 13.6, torus at
+// 768^3 26.0 and 25.1, at 1024^3 41.3 and 40.4.  The compiler does not see a
+// store in the asm: it does not count it in its waits for loads, which makes them
+// at most longer, and it does not keep the one wait state that the hardware asks
+// for between a store of more than 8 bytes and a write to its data registers, so
+// the asm ends with it.
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store_through(void *p, f32x4_t v) {
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" : : "v"(p), "v"(v) : "memory");
+}
+
 // Point order of the packed (phi, g) probe field: the 64 points of a package
 // in 2 x 2 x 2 blocks, so the eight corners of a trilinear cell that lies
 // inside one block share one 128-byte line (FP32).
