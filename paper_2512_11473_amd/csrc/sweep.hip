@@ -769,24 +769,32 @@ SweepConfig current_sweep_config() {
 
 // The default configuration (0, 1) keeps package-id order while a field is
 // small and takes Morton order from kWorklistBytes on, where the z neighbours
-// of id order lie too far apart to stay in an XCD's L2: a sweep of the shell at
-// 1024^3 points (142 MiB a field) takes 86 us in id order and 78 in Morton order
-// (Laplacian 83 and 77), of the torus at 2048^3 (439 MiB) 255 and 224 (257 and
-// 235); at 70 MiB 32.7 and 29.3 (42 and 39), at 31 MiB (prism512) they are equal.
-constexpr double kWorklistBytes = 64.0 * 1024 * 1024;
+// of id order lie too far apart to stay in an XCD's L2.  A sweep in id order and
+// in Morton order: prism at 384^3 points (17 MiB a field) 8.4 and 9.0 us, union at
+// 512^3 (25 MiB) 11.5 and 11.5, torus at 512^3 (27 MiB) 13.1 and 12.1, prism512
+// (31 MiB) 13.5 and 13.3, shell at 640^3 (48 MiB) 20.2 and 20.0, sphere at 900^3
+// (70 MiB) 32.7 and 29.3, shell at 1024^3 (142 MiB) 86 and 78, torus at 2048^3
+// (439 MiB) 255 and 224; the Laplacian 14.1 and 13.1 (29 MiB), 42 and 39, 83 and
+// 77, 257 and 235.
+constexpr double kWorklistBytes = 24.0 * 1024 * 1024;
+constexpr double kCopyBytes = 64.0 * 1024 * 1024;
 
 static bool default_takes_worklist(const sgrid_grid *g, const SweepConfig &c, size_t element) {
     return c.variant == 0 && c.groups == 1 && (double)g->total() * 64.0 * (double)element >= kWorklistBytes;
 }
 
 // What a reinitialisation of n_iter sweeps runs.  The field goes through a
-// worklist-ordered copy (variant 7) in FP32 when there are sweeps enough to
-// pay for the way in and out (at 4 sweeps variant 3 is ahead up to 100 MiB, at
-// 20 variant 7); in FP64 variant 3 (torus at 900^3 points: id order 112 us,
-// variant 3 103, variant 7 110).
+// worklist-ordered copy (variant 7) in FP32 from kCopyBytes on, when there are
+// sweeps enough to pay for the way in and out (at 4 sweeps variant 3 is ahead up
+// to 100 MiB, at 20 variant 7; below kCopyBytes they are equal even at 100); in
+// FP64 variant 3 (torus at 900^3 points: id order 112 us, variant 3 103, variant 7
+// 110).
 static SweepConfig reinit_config(const sgrid_grid *g, size_t element, int32_t n_iter) {
     SweepConfig c = current_sweep_config();
-    if (default_takes_worklist(g, c, element)) c.variant = element == 4 && n_iter >= 8 ? 7 : 3;
+    if (default_takes_worklist(g, c, element)) {
+        const bool copy = element == 4 && n_iter >= 8 && (double)g->total() * 64.0 * 4.0 >= kCopyBytes;
+        c.variant = copy ? 7 : 3;
+    }
     return c;
 }
 
