@@ -15,7 +15,7 @@
 //                   popcount below the cell plus word offsets from the scan,
 //                   id = 2 + rank in ascending linear order (no sort needed);
 //                   the cell map in 16-byte stores, the rank map;
-//   nbr_kernel      27 lanes per four packages: the neighbour table and the six
+//   nbr_kernel      nine lanes per package: the neighbour table and the six
 //                   face slots copied into a 32-byte row per package;
 //   morton_*        the sweep worklist in Morton order of the cells, one lane
 //                   per 4 x 4 x 4 box of codes.
@@ -667,62 +667,93 @@ __global__ __launch_bounds__(256) void sweep_face_kernel(const uint32_t *__restr
     }
 }
 
-// One lane per slot for each of kNbrPkgs packages.
-constexpr int kNbrPkgs = 4;   // consecutive packages per 27-lane group of nbr_kernel
+// Neighbour table and face rows: nine lanes per package, one per row (dy, dz)
+// of the 27-entry neighbourhood, whose three cells are adjacent in the map (one
+// 12-byte load) and whose three slots are adjacent in the table (one 12-byte
+// store); seven packages per wavefront and step, kNbrPkgs steps with their loads
+// issued together.  Bound by its scattered map reads and by 140 bytes of table
+// per package: in the torus's chain of layers up to 2048^3 points (three builds) a
+// lane per slot took 72 us a build on average, this takes 47.
+constexpr int kNbrPkgs = 4;                  // steps of a wavefront
+constexpr int kNbrWave = 7;                  // packages per wavefront and step
+constexpr int kNbrBlock = 4 * kNbrWave * kNbrPkgs;
 
+struct Cells3 {
+    uint32_t v[3];
+};
+
+template <bool WIDE>   // M >= 3: a row's three cells as one load
 __global__ __launch_bounds__(256) void nbr_kernel(const uint32_t *__restrict__ cell_pkg,
                                                   const uint32_t *__restrict__ pkg_cell, int M,
                                                   int64_t n_total, uint32_t *__restrict__ nbr,
                                                   uint32_t *__restrict__ face) {
-    // nine groups of 27 lanes per workgroup (lanes 243.. idle), each group
-    // kNbrPkgs consecutive packages, lane s their slot s: the packages' cells,
-    // then their neighbours' map entries, are requested together.  32-bit
-    // index arithmetic, divisions by constants
-    const int tl = (int)threadIdx.x;
-    if (tl >= 9 * 27) return;
-    const int64_t p0 = ((int64_t)blockIdx.x * 9 + tl / 27) * kNbrPkgs;
-    if (p0 >= n_total) return;
-    const int s = tl % 27;
-    const int dx = s % 3 - 1, dy = (s / 3) % 3 - 1, dz = s / 9 - 1;
+    const int lane = threadIdx.x & 63;
+    if (lane >= 9 * kNbrWave) return;
+    const int64_t p0 = (int64_t)blockIdx.x * kNbrBlock + (int64_t)(threadIdx.x >> 6) * (kNbrWave * kNbrPkgs) + lane / 9;
+    const int row = lane % 9;
+    const int dy = row % 3 - 1, dz = row / 3 - 1;
+    const uint32_t um = (uint32_t)M;
     uint32_t c[kNbrPkgs];
 #pragma unroll
     for (int g = 0; g < kNbrPkgs; ++g) {
-        const int64_t p = p0 + g;
+        const int64_t p = p0 + kNbrWave * g;
         c[g] = (p >= 2 && p < n_total) ? pkg_cell[p] : 0u;
     }
-    uint32_t v[kNbrPkgs];
+    Cells3 m[kNbrPkgs];
+    int x[kNbrPkgs];
+    bool in[kNbrPkgs];   // the row lies in the grid
 #pragma unroll
     for (int g = 0; g < kNbrPkgs; ++g) {
-        const int64_t p = p0 + g;
-        const uint32_t um = (uint32_t)M;
         const uint32_t cyz = c[g] / um;
-        const int x = (int)(c[g] - cyz * um) + dx;
-        const int y = (int)(cyz % um) + dy;
-        const int z = (int)(cyz / um) + dz;
-        const bool out = x < 0 || y < 0 || z < 0 || x >= M || y >= M || z >= M;
-        const uint32_t m = cell_pkg[out ? 0 : x + (int64_t)M * y + (int64_t)M * M * z];   // in bounds
-        v[g] = p < 2 ? (uint32_t)p : (out ? sgrid::kFarPos : m);
-    }
-    // face row: -x, +x, -y, +y, -z, +z, then the package itself twice
-    int f = -1;
-    switch (s) {
-        case 12: f = 0; break;
-        case 14: f = 1; break;
-        case 10: f = 2; break;
-        case 16: f = 3; break;
-        case 4: f = 4; break;
-        case 22: f = 5; break;
-        default: break;
+        x[g] = (int)(c[g] - cyz * um);
+        const int y = (int)(cyz % um) + dy, z = (int)(cyz / um) + dz;
+        in[g] = y >= 0 && z >= 0 && y < M && z < M;
+        const int64_t base = in[g] ? (int64_t)M * y + (int64_t)M * M * z : 0;
+        if (WIDE) {   // three cells from x - 1, moved into the row at its ends
+            m[g] = *reinterpret_cast<const Cells3 *>(cell_pkg + base + min(max(x[g] - 1, 0), M - 3));
+        } else {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) m[g].v[k] = cell_pkg[base + min(max(x[g] - 1 + k, 0), M - 1)];
+        }
     }
 #pragma unroll
     for (int g = 0; g < kNbrPkgs; ++g) {
-        const int64_t p = p0 + g;
+        const int64_t p = p0 + kNbrWave * g;
         if (p >= n_total) break;
-        nbr[p * 27 + s] = v[g];
-        if (f >= 0) face[p * 8 + f] = v[g];
-        if (s == 13) {
-            face[p * 8 + 6] = v[g];
-            face[p * 8 + 7] = v[g];
+        uint32_t v[3];
+        if (p < 2) {
+            v[0] = v[1] = v[2] = (uint32_t)p;   // the far-field packages neighbour themselves
+        } else {
+            const bool first = x[g] == 0, last = x[g] == M - 1;
+            const Cells3 &u = m[g];
+            if (WIDE) {
+                v[0] = first ? sgrid::kFarPos : (last ? u.v[1] : u.v[0]);
+                v[1] = first ? u.v[0] : (last ? u.v[2] : u.v[1]);
+                v[2] = last ? sgrid::kFarPos : (first ? u.v[1] : u.v[2]);
+            } else {
+                v[0] = first ? sgrid::kFarPos : u.v[0];
+                v[1] = u.v[1];
+                v[2] = last ? sgrid::kFarPos : u.v[2];
+            }
+            if (!in[g]) v[0] = v[1] = v[2] = sgrid::kFarPos;
+        }
+        uint32_t *o = nbr + p * 27 + 3 * row;
+        o[0] = v[0];
+        o[1] = v[1];
+        o[2] = v[2];
+        // face row: -x, +x, -y, +y, -z, +z, then the package itself twice
+        uint32_t *f = face + p * 8;
+        if (row == 4) {
+            *reinterpret_cast<uint2 *>(f) = make_uint2(v[0], v[2]);
+            *reinterpret_cast<uint2 *>(f + 6) = make_uint2(v[1], v[1]);
+        } else if (row == 3) {
+            f[2] = v[1];
+        } else if (row == 5) {
+            f[3] = v[1];
+        } else if (row == 1) {
+            f[4] = v[1];
+        } else if (row == 7) {
+            f[5] = v[1];
         }
     }
 }
@@ -987,8 +1018,9 @@ sgrid_status fill_grid(sgrid_grid *g, const BuildWs &ws, hipStream_t st) {
                        (int)M, (int)W, n_words, ca, cc, g->cell_pkg, g->pkg_cell, g->pkg_type, g->core_list,
                        g->rank_map, g->W32);
     SG_CHECK_HIP(hipGetLastError());
-    hipLaunchKernelGGL(nbr_kernel, dim3((unsigned)((nt + 9 * kNbrPkgs - 1) / (9 * kNbrPkgs))), dim3(256), 0, st,
-                       g->cell_pkg, g->pkg_cell, (int)M, nt, g->nbr, g->face);
+    hipLaunchKernelGGL(M >= 3 ? nbr_kernel<true> : nbr_kernel<false>,
+                       dim3((unsigned)((nt + kNbrBlock - 1) / kNbrBlock)), dim3(256), 0, st, g->cell_pkg,
+                       g->pkg_cell, (int)M, nt, g->nbr, g->face);
     SG_CHECK_HIP(hipGetLastError());
     SG_TRY_ALLOC(g->work, (g->P > 0 ? g->P : 1) * 4, "sweep worklist");
     SG_TRY_ALLOC(g->wpos, nt * 4, "worklist positions");
