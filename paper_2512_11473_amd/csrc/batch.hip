@@ -48,13 +48,14 @@ __device__ __forceinline__ Row4<float> ld_row(const float *__restrict__ p) {
 // nt: the streaming (non-temporal) hint, for ping-pong buffers larger than the
 // last-level cache (the written rows would only push out lines the running
 // sweep still reads)
-__device__ __forceinline__ void st_row(float *__restrict__ p, const Row4<float> &r, bool nt) {
+template <typename I>
+__device__ __forceinline__ void st_row(float *__restrict__ base, I off, const Row4<float> &r, bool nt) {
     typedef float f4v __attribute__((ext_vector_type(4)));
     const f4v v = {r.v[0], r.v[1], r.v[2], r.v[3]};
     if (nt)
-        __builtin_nontemporal_store(v, reinterpret_cast<f4v *>(p));
+        __builtin_nontemporal_store(v, reinterpret_cast<f4v *>(at_offset(base, off)));
     else
-        store_through(p, v);
+        store_through(base, off, v);
 }
 
 struct Halo {
@@ -64,66 +65,59 @@ struct Halo {
 
 // Loads of worklist entry e: its row of the worklist table (face neighbours,
 // package id g, grid index), then the package row and its halos.
-__device__ __forceinline__ void batch_loads(const float *__restrict__ src, const uint32_t *__restrict__ wrow,
-                                            int64_t e, int r, Halo &l, int64_t &g, uint32_t &shape) {
+template <typename I>
+__device__ __forceinline__ void batch_loads(const float *__restrict__ src, const uint32_t *__restrict__ wrow, I e,
+                                            int r, Halo &l, uint32_t &g, uint32_t &shape) {
     const int j = r & 3, k = r >> 2;
-    const uint4 f0 = *reinterpret_cast<const uint4 *>(wrow + e * 8);
-    const uint4 f1 = *reinterpret_cast<const uint4 *>(wrow + e * 8 + 4);
-    g = (int64_t)f1.z;
+    const uint4 f0 = *reinterpret_cast<const uint4 *>(at_offset(wrow, e * 32));
+    const uint4 f1 = *reinterpret_cast<const uint4 *>(at_offset(wrow, e * 32 + 16));
+    g = f1.z;
     shape = f1.w;
-    l.c = ld_row(src + g * 64 + r * 4);
-    l.xm = src[(int64_t)f0.x * 64 + r * 4 + 3];
-    l.xp = src[(int64_t)f0.y * 64 + r * 4];
+    auto value = [&](uint32_t row, int at) { return at_offset(src, row_offset<float, I>(row, at)); };
+    l.c = ld_row(value(g, r * 4));
+    l.xm = *value(f0.x, r * 4 + 3);
+    l.xp = *value(f0.y, r * 4);
     // unconditional, so the halo loads issue together instead of behind a
     // branch that waits: a lane without a y / z halo loads that of its
     // neighbour lane on the same side (unused), touching no other lines
-    const int64_t fy = j < 2 ? (int64_t)f0.z : (int64_t)f0.w;
-    const int ry = j < 2 ? 3 + 4 * k : 4 * k;
-    l.yh = ld_row(src + fy * 64 + ry * 4);
-    const int64_t fz = k < 2 ? (int64_t)f1.x : (int64_t)f1.y;
-    const int rz = k < 2 ? j + 12 : j;
-    l.zh = ld_row(src + fz * 64 + rz * 4);
+    l.yh = ld_row(value(j < 2 ? f0.z : f0.w, (j < 2 ? 3 + 4 * k : 4 * k) * 4));
+    l.zh = ld_row(value(k < 2 ? f1.x : f1.y, (k < 2 ? j + 12 : j) * 4));
 }
 
-__device__ __forceinline__ Row4<float> update_row_dpp(int r, const Halo &l, const sgrid::SweepParams<float> &sp) {
-    const int j = r & 3;
-    Row4<float> o;
+__device__ __forceinline__ Row4<float> update_row_dpp(const Halo &l, const sgrid::SweepParams<float> &sp) {
+    Row4<float> o, ym, yp, zm, zp;
+    row_neighbours<false>(l.c.v, l.yh.v, ym.v, yp.v);
+    row_neighbours<true>(l.c.v, l.zh.v, zm.v, zp.v);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float v = l.c.v[i];
-        const float a = row_move<kRowShr1>(v), b = row_move<kRowShl1>(v);   // every lane, before the selects
-        const float ym = j == 0 ? l.yh.v[i] : a;
-        const float yp = j == 3 ? l.yh.v[i] : b;
-        const float zm = row_move_keep<kRowShr4, 0xE>(v, l.zh.v[i]);   // k = 0 lanes (bank 0) keep the halo
-        const float zp = row_move_keep<kRowShl4, 0x7>(v, l.zh.v[i]);   // k = 3 lanes (bank 3) keep the halo
         const float xm = i > 0 ? l.c.v[i - 1] : l.xm;
         const float xp = i < 3 ? l.c.v[i + 1] : l.xp;
-        o.v[i] = sgrid::upwind_update(v, xm, xp, ym, yp, zm, zp, sp.h2, sp.inv_h, sp.dt);
+        o.v[i] = sgrid::upwind_update(l.c.v[i], xm, xp, ym.v[i], yp.v[i], zm.v[i], zp.v[i], sp.h2, sp.inv_h, sp.dt);
     }
     return o;
 }
 
 // Persistent worklist sweep, DPP exchange.  Wavefront w processes the sets
 // [w * spw, (w + 1) * spw) of four worklist entries.
+template <typename I>   // byte offsets in the concatenated field
 __global__ __launch_bounds__(256) void batch_dpp_kernel(const float *__restrict__ src, float *__restrict__ dst,
-                                                        const uint32_t *__restrict__ wrow, int64_t n_work,
+                                                        const uint32_t *__restrict__ wrow, I n_work,
                                                         const sgrid::SweepParams<float> *__restrict__ params,
-                                                        int64_t n_blocks, int64_t spw, bool nt) {
-    const int64_t b = xcd_block(blockIdx.x, n_blocks);
+                                                        I n_blocks, I spw, bool nt) {
+    const I b = block_of(n_blocks);
     const int lane = threadIdx.x & 63, r = lane & 15;
-    const int64_t wave = b * 4 + (threadIdx.x >> 6);
-    const int64_t n_sets = (n_work + 3) / 4;
-    const int64_t s0 = wave * spw, s1 = s0 + spw < n_sets ? s0 + spw : n_sets;
-    for (int64_t s = s0; s < s1; ++s) {
-        const int64_t e = 4 * s + (lane >> 4);
+    const I wave = b * 4 + (threadIdx.x >> 6);
+    const I n_sets = (n_work + 3) / 4;
+    const I s0 = wave * spw, s1 = s0 + spw < n_sets ? s0 + spw : n_sets;
+    for (I s = s0; s < s1; ++s) {
+        const I e = 4 * s + (lane >> 4);
         const bool live = e < n_work;
         Halo l;
-        uint32_t shape = 0;
-        int64_t g = 0;
+        uint32_t shape = 0, g = 0;
         if (live) batch_loads(src, wrow, e, r, l, g, shape);
         const sgrid::SweepParams<float> sp = params[shape];
-        const Row4<float> o = update_row_dpp(r, l, sp);
-        if (live) st_row(dst + g * 64 + r * 4, o, nt);
+        const Row4<float> o = update_row_dpp(l, sp);
+        if (live) st_row(dst, row_offset<float, I>(g, r * 4), o, nt);
     }
 }
 
@@ -148,8 +142,7 @@ __global__ __launch_bounds__(256) void batch_lds_kernel(const float *__restrict_
         const int64_t e = 4 * s + (lane >> 4);
         const bool live = s < s1 && e < n_work;
         Halo l;
-        uint32_t shape = 0;
-        int64_t g = 0;
+        uint32_t shape = 0, g = 0;
         if (live) {
             batch_loads(src, wrow, e, r, l, g, shape);
 #pragma unroll
@@ -172,7 +165,7 @@ __global__ __launch_bounds__(256) void batch_lds_kernel(const float *__restrict_
             for (int i = 0; i < 4; ++i)
                 o.v[i] = sgrid::upwind_update(t[at(i, j, k)], t[at(i - 1, j, k)], t[at(i + 1, j, k)], t[at(i, j - 1, k)],
                                 t[at(i, j + 1, k)], t[at(i, j, k - 1)], t[at(i, j, k + 1)], sp.h2, sp.inv_h, sp.dt);
-            st_row(dst + g * 64 + r * 4, o, nt);
+            st_row(dst, row_offset<float, int64_t>(g, r * 4), o, nt);
         }
         __syncthreads();
     }
@@ -267,8 +260,11 @@ sgrid_status launch_batch_sweep(const sgrid_batch *b, const sgrid_batch::Segment
     if (variant == 1)
         hipLaunchKernelGGL(batch_lds_kernel, dim3((unsigned)nb), dim3(256), 0, st, src, dst, wrow, seg.count,
                            b->params, nb, spw, nt);
+    else if ((double)b->n_total * 256.0 <= 4294967296.0)   // 32-bit byte offsets
+        hipLaunchKernelGGL(batch_dpp_kernel<uint32_t>, dim3((unsigned)nb), dim3(256), 0, st, src, dst, wrow,
+                           (uint32_t)seg.count, b->params, (uint32_t)nb, (uint32_t)spw, nt);
     else
-        hipLaunchKernelGGL(batch_dpp_kernel, dim3((unsigned)nb), dim3(256), 0, st, src, dst, wrow, seg.count,
+        hipLaunchKernelGGL(batch_dpp_kernel<int64_t>, dim3((unsigned)nb), dim3(256), 0, st, src, dst, wrow, seg.count,
                            b->params, nb, spw, nt);
     SG_CHECK_LAUNCH("batch sweep");
     return SGRID_OK;

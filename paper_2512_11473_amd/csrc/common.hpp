@@ -110,43 +110,78 @@ constexpr int64_t kMaxGrid = 0x7FFFFFFF;
 // Device utilities
 // ---------------------------------------------------------------------------
 
-// Cross-lane move inside 16-lane rows (DPP).  CTRL is a row_shl / row_shr
-// control: row_shl:n = 0x100 + n (lane l reads lane l + n of its row),
-// row_shr:n = 0x110 + n (lane l reads lane l - n).  row_move: lanes whose
-// source lies outside their 16-lane row read 0 and must not use the result
-// (callers select a halo value for them).  row_move_keep: lanes of the banks
-// (groups of four lanes of a row) left out of BANKS keep `keep` instead, which
-// takes a halo value in without a select.  Both must run in every lane of the
-// row: a lane outside the active mask supplies 0 to its neighbours, so a move
-// written inside a lane-dependent branch (an arm of ?: included) reads wrong
-// values.
-constexpr int kRowShl1 = 0x101, kRowShl4 = 0x104, kRowShr1 = 0x111, kRowShr4 = 0x114;
+// Neighbour values of a package's four-value row in y and z.  A package is one
+// 16-lane DPP row; lane r = j + 4 k holds row (j, k), so its y neighbours are lanes
+// r -+ 1 and its z neighbours lanes r -+ 4.  Lanes at the package's face take the
+// halo value h instead: lo gets it on the lanes of mask LO, hi on those of mask HI.
+// Each neighbour value is one select whose first operand moves between lanes; the
+// compiler, which wants the move and the select (or a copy of h, kept twice) as two
+// instructions, needs 28 for the sixteen of a row.  A sweep with these and with
+// 32-bit offsets, before and now: torus at 256^3 points 4.7 and 4.55 us, prism512
+// 12.2 and 12.05, torus at 768^3 23.5 and 22.2, at 2048^3 221.7 and 217.6.
+//  The select's mask is VCC.  The
+// block's first two instructions give the two wait states that the hardware asks
+// for between a vector write and a DPP read of its result.  Must run in every lane
+// of a package: a lane outside the active mask supplies 0 to its neighbours, so a
+// call inside a lane-dependent branch reads wrong values.
+constexpr uint64_t kLanesJ0 = 0x1111111111111111ull, kLanesJ3 = 0x8888888888888888ull;
+constexpr uint64_t kLanesK0 = 0x000F000F000F000Full, kLanesK3 = 0xF000F000F000F000ull;
 
-template <int CTRL>
-__device__ __forceinline__ float row_move(float v) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+#define SG_DPP_SELECT(D, S, H, CTRL) \
+    "v_cndmask_b32_dpp %" #D ", %" #S ", %" #H ", vcc " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+#define SG_ROW_NEIGHBOURS(DOWN, UP, LO, HI)                                                                       \
+    asm("s_mov_b64 vcc, %16\n\ts_nop 1\n\t"                                                                     \
+        SG_DPP_SELECT(0, 8, 12, DOWN) SG_DPP_SELECT(1, 9, 13, DOWN)                                               \
+        SG_DPP_SELECT(2, 10, 14, DOWN) SG_DPP_SELECT(3, 11, 15, DOWN)                                             \
+        "s_mov_b64 vcc, %17\n\t"                                                                                 \
+        SG_DPP_SELECT(4, 8, 12, UP) SG_DPP_SELECT(5, 9, 13, UP)                                                   \
+        SG_DPP_SELECT(6, 10, 14, UP) SG_DPP_SELECT(7, 11, 15, UP)                                                 \
+        : "=&v"(lo[0]), "=&v"(lo[1]), "=&v"(lo[2]), "=&v"(lo[3]), "=&v"(hi[0]), "=&v"(hi[1]), "=&v"(hi[2]),       \
+          "=&v"(hi[3])                                                                                            \
+        : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]), "v"(h[0]), "v"(h[1]), "v"(h[2]), "v"(h[3]), "s"(LO), "s"(HI) \
+        : "vcc")
+
+__device__ __forceinline__ void neighbours_y(const uint32_t (&c)[4], const uint32_t (&h)[4], uint32_t (&lo)[4],
+                                             uint32_t (&hi)[4]) {
+    SG_ROW_NEIGHBOURS("row_shr:1", "row_shl:1", kLanesJ0, kLanesJ3);
 }
-
-template <int CTRL>
-__device__ __forceinline__ double row_move(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xFFFFFFFFll), CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+__device__ __forceinline__ void neighbours_z(const uint32_t (&c)[4], const uint32_t (&h)[4], uint32_t (&lo)[4],
+                                             uint32_t (&hi)[4]) {
+    SG_ROW_NEIGHBOURS("row_shr:4", "row_shl:4", kLanesK0, kLanesK3);
 }
+#undef SG_ROW_NEIGHBOURS
+#undef SG_DPP_SELECT
 
-template <int CTRL, int BANKS>
-__device__ __forceinline__ float row_move_keep(float v, float keep) {
-    return __int_as_float(
-        __builtin_amdgcn_update_dpp(__float_as_int(keep), __float_as_int(v), CTRL, 0xF, BANKS, false));
-}
-
-template <int CTRL, int BANKS>
-__device__ __forceinline__ double row_move_keep(double v, double keep) {
-    const long long b = __double_as_longlong(v), o = __double_as_longlong(keep);
-    const int lo = __builtin_amdgcn_update_dpp((int)(o & 0xFFFFFFFFll), (int)(b & 0xFFFFFFFFll), CTRL, 0xF, BANKS, false);
-    const int hi = __builtin_amdgcn_update_dpp((int)(o >> 32), (int)(b >> 32), CTRL, 0xF, BANKS, false);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+// The same for four values of type T, by 32-bit words.
+template <bool Z, typename T>
+__device__ __forceinline__ void row_neighbours(const T (&c)[4], const T (&h)[4], T (&lo)[4], T (&hi)[4]) {
+    constexpr int W = sizeof(T) / 4;
+    struct Words { uint32_t w[W]; };
+    uint32_t l[W][4], u[W][4];
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        uint32_t cw[4], hw[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            cw[i] = __builtin_bit_cast(Words, c[i]).w[w];
+            hw[i] = __builtin_bit_cast(Words, h[i]).w[w];
+        }
+        if (Z)
+            neighbours_z(cw, hw, l[w], u[w]);
+        else
+            neighbours_y(cw, hw, l[w], u[w]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        Words a, b;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            a.w[w] = l[w][i];
+            b.w[w] = u[w][i];
+        }
+        lo[i] = __builtin_bit_cast(T, a);
+        hi[i] = __builtin_bit_cast(T, b);
+    }
 }
 
 // 16-byte store written through the L2 (device scope, sc1) instead of left
@@ -166,6 +201,12 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void store_through(void *p, f32x4_t v) {
     asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" : : "v"(p), "v"(v) : "memory");
 }
+__device__ __forceinline__ void store_through(void *base, uint32_t off, f32x4_t v) {
+    asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 0" : : "v"(off), "v"(v), "s"(base) : "memory");
+}
+__device__ __forceinline__ void store_through(void *base, int64_t off, f32x4_t v) {
+    store_through(static_cast<char *>(base) + off, v);
+}
 
 // Point order of the packed (phi, g) probe field: the 64 points of a package
 // in 2 x 2 x 2 blocks, so the eight corners of a trilinear cell that lies
@@ -183,4 +224,30 @@ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nb) {
     const int64_t full = nb % 8 == 0 ? 8 : nb % 8;   // XCDs that receive `per` blocks
     // XCDs 0..full-1 own ranges of length per, the rest ranges of length per - 1
     return x < full ? x * per + r : full * per + (x - full) * (per - 1) + r;
+}
+// A workgroup's block in that order, with arithmetic in I (nb < 2^31, as every
+// grid's: 32 bits do, and take a third of the scalar instructions).
+template <typename I>
+__device__ __forceinline__ I block_of(I nb) {
+    const I per = (nb + 7) / 8, x = blockIdx.x % 8, r = blockIdx.x / 8;
+    const I full = nb % 8 == 0 ? 8 : nb % 8;
+    return x < full ? x * per + r : full * per + (x - full) * (per - 1) + r;
+}
+
+// Byte offset of value `at` of package row `row` in a field, in the index type I.
+// With 32-bit offsets from a base that is the same for every lane an address is
+// one vector instruction (shift and or); with 64-bit ones it takes five or six,
+// and the sweeps form six addresses per lane: 157 vector instructions per
+// wavefront become 134.
+template <typename T, typename I>
+__device__ __forceinline__ I row_offset(uint32_t row, int at) {
+    return (I)row * (I)(64 * sizeof(T)) + (I)(at * (int)sizeof(T));
+}
+template <typename T, typename I>
+__device__ __forceinline__ const T *at_offset(const T *base, I off) {
+    return reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + off);
+}
+template <typename T, typename I>
+__device__ __forceinline__ T *at_offset(T *base, I off) {
+    return reinterpret_cast<T *>(reinterpret_cast<char *>(base) + off);
 }

@@ -85,6 +85,15 @@ __device__ __forceinline__ void store_row(T *__restrict__ p, const Row<T> &r, bo
         store_row(p, r);
 }
 
+// A row stored at a byte offset.
+template <typename T, typename I>
+__device__ __forceinline__ void store_row_at(T *__restrict__ base, I off, const Row<T> &r, bool nt) {
+    if (sizeof(T) == 4 && !nt)
+        store_through(base, off, f32x4_t{(float)r.v[0], (float)r.v[1], (float)r.v[2], (float)r.v[3]});
+    else
+        store_row(at_offset(base, off), r, nt);
+}
+
 // A package row and its stencil neighbours.
 template <typename T>
 struct Stencil {
@@ -100,9 +109,19 @@ struct Loads {
     T xm, xp;
 };
 
-__device__ __forceinline__ void load_face(const uint32_t *__restrict__ face, int64_t p, uint4 &f0, uint2 &f1) {
-    f0 = *reinterpret_cast<const uint4 *>(face + p * 8);
-    f1 = *reinterpret_cast<const uint2 *>(face + p * 8 + 4);
+template <typename I>
+__device__ __forceinline__ void load_face(const uint32_t *__restrict__ face, I p, uint4 &f0, uint2 &f1) {
+    f0 = *reinterpret_cast<const uint4 *>(at_offset(face, p * 32));
+    f1 = *reinterpret_cast<const uint2 *>(at_offset(face, p * 32 + 16));
+}
+
+// A worklist entry's face row: the six neighbours and the package's own id.
+template <typename I>
+__device__ __forceinline__ uint32_t load_work_face(const uint32_t *__restrict__ wface, I e, uint4 &f0, uint2 &f1) {
+    f0 = *reinterpret_cast<const uint4 *>(at_offset(wface, e * 32));
+    const uint4 b = *reinterpret_cast<const uint4 *>(at_offset(wface, e * 32 + 16));
+    f1 = make_uint2(b.x, b.y);
+    return b.z;
 }
 
 // Every lane issues all five loads.  A lane with no y (z) halo row loads the
@@ -112,57 +131,44 @@ __device__ __forceinline__ void load_face(const uint32_t *__restrict__ face, int
 // under a per-lane condition would become branches, and the compiler then
 // waits for every earlier load before the branch's own, adding a memory round
 // trip.
-template <typename T>
-__device__ __forceinline__ void issue_halos(const T *__restrict__ src, int64_t p, int r, const uint4 &f0,
-                                            const uint2 &f1, Loads<T> &l) {
+template <typename T, typename I>
+__device__ __forceinline__ void issue_halos(const T *__restrict__ src, int r, const uint4 &f0, const uint2 &f1,
+                                            Loads<T> &l) {
     const int j = r & 3, k = r >> 2;
-    l.xm = src[(int64_t)f0.x * 64 + r * 4 + 3];
-    l.xp = src[(int64_t)f0.y * 64 + r * 4];
-    const int64_t fy = j < 2 ? (int64_t)f0.z : (int64_t)f0.w;
+    l.xm = *at_offset(src, row_offset<T, I>(f0.x, r * 4 + 3));
+    l.xp = *at_offset(src, row_offset<T, I>(f0.y, r * 4));
     const int ry = j < 2 ? 3 + 4 * k : 4 * k;
-    l.yh = load_row(src + fy * 64 + ry * 4);
-    const int64_t fz = k < 2 ? (int64_t)f1.x : (int64_t)f1.y;
+    l.yh = load_row(at_offset(src, row_offset<T, I>(j < 2 ? f0.z : f0.w, ry * 4)));
     const int rz = k < 2 ? j + 12 : j;
-    l.zh = load_row(src + fz * 64 + rz * 4);
+    l.zh = load_row(at_offset(src, row_offset<T, I>(k < 2 ? f1.x : f1.y, rz * 4)));
 }
 
-template <typename T>
-__device__ __forceinline__ void issue_data(const T *__restrict__ src, int64_t p, int r, const uint4 &f0,
+template <typename T, typename I>
+__device__ __forceinline__ void issue_data(const T *__restrict__ src, uint32_t p, int r, const uint4 &f0,
                                            const uint2 &f1, Loads<T> &l) {
-    l.c = load_row(src + p * 64 + r * 4);
-    issue_halos(src, p, r, f0, f1, l);
+    l.c = load_row(at_offset(src, row_offset<T, I>(p, r * 4)));
+    issue_halos<T, I>(src, r, f0, f1, l);
 }
 
-template <typename T>
-__device__ __forceinline__ void issue_loads(const T *__restrict__ src, const uint32_t *__restrict__ face, int64_t p,
-                                            int r, Loads<T> &l) {
+template <typename T, typename I>
+__device__ __forceinline__ void issue_loads(const T *__restrict__ src, const uint32_t *__restrict__ face, I p, int r,
+                                            Loads<T> &l) {
     uint4 f0;
     uint2 f1;
     load_face(face, p, f0, f1);
-    issue_data(src, p, r, f0, f1, l);
+    issue_data<T, I>(src, (uint32_t)p, r, f0, f1, l);
 }
 
 // Interior y / z neighbours through DPP row shifts (the 16 lanes of a package
 // form one DPP row and execute these together).
 template <typename T>
-__device__ __forceinline__ Stencil<T> assemble(int r, const Loads<T> &l) {
-    const int j = r & 3, k = r >> 2;
+__device__ __forceinline__ Stencil<T> assemble(const Loads<T> &l) {
     Stencil<T> s;
     s.c = l.c;
     s.xm = l.xm;
     s.xp = l.xp;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const T v = l.c.v[i];
-        const T a = row_move<kRowShr1>(v);   // lane - 1: (j - 1, k)
-        const T b = row_move<kRowShl1>(v);   // lane + 1: (j + 1, k)
-        s.ym.v[i] = j == 0 ? l.yh.v[i] : a;
-        s.yp.v[i] = j == 3 ? l.yh.v[i] : b;
-        // lane -+ 4: (j, k -+ 1); the k = 0 (k = 3) lanes are bank 0 (bank 3)
-        // of the row and keep their z halo value
-        s.zm.v[i] = row_move_keep<kRowShr4, 0xE>(v, l.zh.v[i]);
-        s.zp.v[i] = row_move_keep<kRowShl4, 0x7>(v, l.zh.v[i]);
-    }
+    row_neighbours<false>(l.c.v, l.yh.v, s.ym.v, s.yp.v);
+    row_neighbours<true>(l.c.v, l.zh.v, s.zm.v, s.zp.v);
     return s;
 }
 
@@ -181,22 +187,23 @@ __device__ __forceinline__ Row<T> reinit_row(const Stencil<T> &s, T h2, T inv_h,
 // Reinitialisation sweep over the packages [first, end) (all of them: [2,
 // 2 + P)), DPP exchange variant.  A wavefront handles G consecutive sets of
 // four packages and issues all their loads before computing any of them.
-template <typename T, int G>
+template <typename T, int G, typename I>
 __global__ __launch_bounds__(256) void reinit_dpp_kernel(const T *__restrict__ src, T *__restrict__ dst,
-                                                         const uint32_t *__restrict__ face, int64_t first,
-                                                         int64_t end, int64_t n_blocks, T h2, T inv_h, T dt, bool nt) {
-    const int64_t b = xcd_block(blockIdx.x, n_blocks);
+                                                         const uint32_t *__restrict__ face, I first, I end,
+                                                         I n_blocks, T h2, T inv_h, T dt, bool nt) {
+    const I b = block_of(n_blocks);
     const int lane = threadIdx.x & 63;
     const int r = lane & 15;
-    const int64_t p0 = first + (b * 4 + (threadIdx.x >> 6)) * (4 * G) + (lane >> 4);
+    const I p0 = first + (b * 4 + (threadIdx.x >> 6)) * (4 * G) + (lane >> 4);
     Loads<T> l[G];
 #pragma unroll
     for (int g = 0; g < G; ++g)
         if (p0 + 4 * g < end) issue_loads(src, face, p0 + 4 * g, r, l[g]);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        const Stencil<T> s = assemble(r, l[g]);
-        if (p0 + 4 * g < end) store_row(dst + (p0 + 4 * g) * 64 + r * 4, reinit_row(s, h2, inv_h, dt), nt);
+        const Stencil<T> s = assemble(l[g]);
+        if (p0 + 4 * g < end)
+            store_row_at(dst, row_offset<T, I>((uint32_t)(p0 + 4 * g), r * 4), reinit_row(s, h2, inv_h, dt), nt);
     }
 }
 
@@ -206,31 +213,30 @@ __global__ __launch_bounds__(256) void reinit_dpp_kernel(const T *__restrict__ s
 // brings into the caches.  The face rows are read in worklist order (wface:
 // six neighbours and the package's own id), one coalesced 32-byte row per
 // package.  G sets of four packages per wavefront.
-template <typename T, int G>
+template <typename T, int G, typename I>
 __global__ __launch_bounds__(256) void reinit_work_kernel(const T *__restrict__ src, T *__restrict__ dst,
-                                                          const uint32_t *__restrict__ wface, int64_t P,
-                                                          int64_t n_blocks, T h2, T inv_h, T dt, bool nt) {
-    const int64_t b = xcd_block(blockIdx.x, n_blocks);
+                                                          const uint32_t *__restrict__ wface, I P, I n_blocks, T h2,
+                                                          T inv_h, T dt, bool nt) {
+    const I b = block_of(n_blocks);
     const int lane = threadIdx.x & 63;
     const int r = lane & 15;
-    const int64_t e0 = (b * 4 + (threadIdx.x >> 6)) * (4 * G) + (lane >> 4);
+    const I e0 = (b * 4 + (threadIdx.x >> 6)) * (4 * G) + (lane >> 4);
     Loads<T> l[G];
-    int64_t p[G];
+    uint32_t p[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        const int64_t e = e0 + 4 * g;
-        p[g] = -1;
+        const I e = e0 + 4 * g;
         if (e < P) {
-            const uint4 f0 = *reinterpret_cast<const uint4 *>(wface + e * 8);
-            const uint4 f1 = *reinterpret_cast<const uint4 *>(wface + e * 8 + 4);
-            p[g] = (int64_t)f1.z;
-            issue_data(src, p[g], r, f0, make_uint2(f1.x, f1.y), l[g]);
+            uint4 f0;
+            uint2 f1;
+            p[g] = load_work_face(wface, e, f0, f1);
+            issue_data<T, I>(src, p[g], r, f0, f1, l[g]);
         }
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        const Stencil<T> s = assemble(r, l[g]);
-        if (p[g] >= 0) store_row(dst + p[g] * 64 + r * 4, reinit_row(s, h2, inv_h, dt), nt);
+        const Stencil<T> s = assemble(l[g]);
+        if (e0 + 4 * g < P) store_row_at(dst, row_offset<T, I>(p[g], r * 4), reinit_row(s, h2, inv_h, dt), nt);
     }
 }
 
@@ -244,32 +250,29 @@ __global__ __launch_bounds__(256) void reinit_work_kernel(const T *__restrict__ 
 // writes the copy (MODE 0); the following ones go copy to copy (MODE 1); the
 // last writes package-id order again (MODE 2).  The values are those of every
 // other variant.
-template <typename T, int MODE>
+template <typename T, int MODE, typename I>
 __global__ __launch_bounds__(256) void reinit_morton_kernel(const T *__restrict__ src, T *__restrict__ dst,
                                                             const uint32_t *__restrict__ wface,
-                                                            const uint32_t *__restrict__ mface, int64_t P,
-                                                            int64_t n_blocks, T h2, T inv_h, T dt, bool nt) {
-    const int64_t b = xcd_block(blockIdx.x, n_blocks);
-    const int lane = threadIdx.x & 63;
-    const int r = lane & 15;
-    const int64_t e = (b * 4 + (threadIdx.x >> 6)) * 4 + (lane >> 4);
+                                                            const uint32_t *__restrict__ mface, I P, I n_blocks, T h2,
+                                                            T inv_h, T dt, bool nt) {
+    const I b = block_of(n_blocks);
+    const int r = threadIdx.x & 15;
+    const I e = b * 16 + (threadIdx.x >> 4);
     if (e >= P) return;   // whole 16-lane rows (one package each) leave together
     Loads<T> l;
-    int64_t out_row;
+    uint4 f0;
+    uint2 f1;
+    uint32_t out_row = (uint32_t)(2 + e);
     if (MODE == 0) {
-        const uint4 f0 = *reinterpret_cast<const uint4 *>(wface + e * 8);
-        const uint4 f1 = *reinterpret_cast<const uint4 *>(wface + e * 8 + 4);
-        issue_data(src, (int64_t)f1.z, r, f0, make_uint2(f1.x, f1.y), l);
-        out_row = 2 + e;
+        const uint32_t p = load_work_face(wface, e, f0, f1);
+        issue_data<T, I>(src, p, r, f0, f1, l);
     } else {
-        l.c = load_row(src + (2 + e) * 64 + r * 4);
-        const uint4 f0 = *reinterpret_cast<const uint4 *>(mface + e * 8);
-        const uint4 f1 = *reinterpret_cast<const uint4 *>(mface + e * 8 + 4);
-        issue_halos(src, 2 + e, r, f0, make_uint2(f1.x, f1.y), l);
-        out_row = MODE == 1 ? 2 + e : (int64_t)f1.z;
+        l.c = load_row(at_offset(src, row_offset<T, I>(out_row, r * 4)));
+        const uint32_t p = load_work_face(mface, e, f0, f1);
+        issue_halos<T, I>(src, r, f0, f1, l);
+        if (MODE == 2) out_row = p;
     }
-    const Stencil<T> st = assemble(r, l);
-    store_row(dst + out_row * 64 + r * 4, reinit_row(st, h2, inv_h, dt), nt);
+    store_row_at(dst, row_offset<T, I>(out_row, r * 4), reinit_row(assemble(l), h2, inv_h, dt), nt);
 }
 
 // Row-exchange variant: the y / z neighbour rows move through LDS instead of
@@ -292,7 +295,7 @@ __global__ __launch_bounds__(256) void reinit_rows_kernel(const T *__restrict__ 
     Loads<T> l[G];
 #pragma unroll
     for (int g = 0; g < G; ++g)
-        if (p0 + 4 * g < P + 2) issue_loads(src, face, p0 + 4 * g, r, l[g]);
+        if (p0 + 4 * g < P + 2) issue_loads<T, int64_t>(src, face, p0 + 4 * g, r, l[g]);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         const int64_t p = p0 + 4 * g;
@@ -366,7 +369,7 @@ __global__ __launch_bounds__(1024) void reinit_share_kernel(const T *__restrict_
     l.xp = halo_value(src, tile, f0.y, r * 4);
     if (j == 0 || j == 3) l.yh = halo_row(src, tile, j == 0 ? f0.z : f0.w, (j == 0 ? 3 + 4 * k : 4 * k) * 4);
     if (k == 0 || k == 3) l.zh = halo_row(src, tile, k == 0 ? f1.x : f1.y, (k == 0 ? j + 12 : j) * 4);
-    const Stencil<T> s = assemble(r, l);
+    const Stencil<T> s = assemble(l);
     store_row(dst + p * 64 + r * 4, reinit_row(s, h2, inv_h, dt));
 }
 
@@ -410,8 +413,8 @@ __global__ __launch_bounds__(256) void reinit_pipe_kernel(const T *__restrict__ 
         f0 = *reinterpret_cast<const uint4 *>(wface + e * 8);
         f1 = *reinterpret_cast<const uint4 *>(wface + e * 8 + 4);
         Loads<T> l;
-        issue_data(src, p, r, c0, cz, l);
-        const Stencil<T> st = assemble(r, l);
+        issue_data<T, int64_t>(src, (uint32_t)p, r, c0, cz, l);
+        const Stencil<T> st = assemble(l);
         store_row(dst + p * 64 + r * 4, reinit_row(st, h2, inv_h, dt), nt);
     }
 }
@@ -449,8 +452,8 @@ __global__ __launch_bounds__(256) void reinit_pipe_lin_kernel(const T *__restric
         p = pkg(s + stride < n_sets ? s + stride : s);
         load_face(face, p, f0, f1);
         own = load_row(src + p * 64 + r * 4);
-        issue_halos(src, pc, r, c0, c1, l);
-        const Stencil<T> st = assemble(r, l);
+        issue_halos<T, int64_t>(src, r, c0, c1, l);
+        const Stencil<T> st = assemble(l);
         store_row(dst + pc * 64 + r * 4, reinit_row(st, h2, inv_h, dt));
     }
 }
@@ -474,7 +477,7 @@ __global__ __launch_bounds__(256) void reinit_lds_kernel(const T *__restrict__ s
         const bool live = p < P + 2;
         if (live) {
             Loads<T> l;
-            issue_loads(src, face, p, r, l);
+            issue_loads<T, int64_t>(src, face, p, r, l);
 #pragma unroll
             for (int i = 0; i < 4; ++i) t[at(i, j, k)] = l.c.v[i];
             t[at(-1, j, k)] = l.xm;
@@ -504,17 +507,11 @@ __global__ __launch_bounds__(256) void reinit_lds_kernel(const T *__restrict__ s
 // (WORK = false) entry e is package e; in worklist order entries 0 and 1 are
 // the far-field rows and entry e >= 2 is worklist position e - 2, whose face
 // row (wface: six neighbours, own id) comes in the same 32-byte load.
-template <bool WORK>
-__device__ __forceinline__ int64_t stencil_package(int64_t e, const uint32_t *__restrict__ face,
-                                                   const uint32_t *__restrict__ wface, uint4 &f0, uint2 &f1) {
+template <bool WORK, typename I>
+__device__ __forceinline__ I stencil_package(I e, const uint32_t *__restrict__ face,
+                                             const uint32_t *__restrict__ wface, uint4 &f0, uint2 &f1) {
     if (e < 2) return e;
-    if (WORK) {
-        const uint4 a = *reinterpret_cast<const uint4 *>(wface + (e - 2) * 8);
-        const uint4 b = *reinterpret_cast<const uint4 *>(wface + (e - 2) * 8 + 4);
-        f0 = a;
-        f1 = make_uint2(b.x, b.y);
-        return (int64_t)b.z;
-    }
+    if (WORK) return (I)load_work_face(wface, e - 2, f0, f1);
     load_face(face, e, f0, f1);
     return e;
 }
@@ -553,8 +550,8 @@ __global__ __launch_bounds__(256) void gradient_kernel(const T *__restrict__ phi
         for (int i = 0; i < 4; ++i) ox.v[i] = oy.v[i] = oz.v[i] = T(0);
     } else {
         Loads<T> l;
-        issue_data(phi, p, r, f0, f1, l);
-        const Stencil<T> s = assemble(r, l);
+        issue_data<decltype(l.xm), int64_t>(phi, (uint32_t)p, r, f0, f1, l);
+        const Stencil<T> s = assemble(l);
         c = s.c;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -638,8 +635,8 @@ __global__ __launch_bounds__(256) void cut_fraction_kernel(const float *__restri
             for (int i = 0; i < 4; ++i) a[i] = c.v[i] * inv_h;
         } else {
             Loads<float> l;
-            issue_data(phi, p, r, f0, f1, l);
-            const Stencil<float> s = assemble(r, l);
+            issue_data<decltype(l.xm), int64_t>(phi, (uint32_t)p, r, f0, f1, l);
+            const Stencil<float> s = assemble(l);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float xm = i > 0 ? s.c.v[i - 1] : s.xm;
@@ -700,27 +697,26 @@ __global__ __launch_bounds__(256) void add_kernel(T *__restrict__ phi, int64_t n
 // / h^2 at every point of every activated package, neighbours through the
 // neighbour table as in the sweeps (the same lane mapping and halo loads);
 // the far-field rows get 0.
-template <typename T, bool WORK>
+template <typename T, bool WORK, typename I>
 __global__ __launch_bounds__(256) void laplacian_kernel(const T *__restrict__ phi, T *__restrict__ out,
                                                         const uint32_t *__restrict__ face,
-                                                        const uint32_t *__restrict__ wface, int64_t n_total,
-                                                        int64_t n_blocks, T inv_h2, bool nt) {
-    const int64_t b = xcd_block(blockIdx.x, n_blocks);
-    const int lane = threadIdx.x & 63;
-    const int r = lane & 15;
-    const int64_t e = (b * 4 + (threadIdx.x >> 6)) * 4 + (lane >> 4);
+                                                        const uint32_t *__restrict__ wface, I n_total, I n_blocks,
+                                                        T inv_h2, bool nt) {
+    const I b = block_of(n_blocks);
+    const int r = threadIdx.x & 15;
+    const I e = b * 16 + (threadIdx.x >> 4);
     if (e >= n_total) return;
     uint4 f0;
     uint2 f1;
-    const int64_t p = stencil_package<WORK>(e, face, wface, f0, f1);
+    const uint32_t p = (uint32_t)stencil_package<WORK>(e, face, wface, f0, f1);
     Row<T> o;
     if (p < 2) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) o.v[i] = T(0);
     } else {
         Loads<T> l;
-        issue_data(phi, p, r, f0, f1, l);
-        const Stencil<T> s = assemble(r, l);
+        issue_data<T, I>(phi, p, r, f0, f1, l);
+        const Stencil<T> s = assemble(l);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const T xm = i > 0 ? s.c.v[i - 1] : s.xm;
@@ -729,7 +725,7 @@ __global__ __launch_bounds__(256) void laplacian_kernel(const T *__restrict__ ph
             o.v[i] = fma(T(-6), s.c.v[i], sum) * inv_h2;
         }
     }
-    store_row(out + p * 64 + r * 4, o, nt);
+    store_row_at(out, row_offset<T, I>(p, r * 4), o, nt);
 }
 
 template <typename T>
@@ -809,19 +805,62 @@ static bool stencil_in_worklist_order(const sgrid_grid *g, size_t element) {
 // MI355X's Infinity Cache (the last level before HBM)
 constexpr double kLastLevelCacheBytes = 256.0 * 1024 * 1024;
 
+// Whether a field's byte offsets fit 32 bits, which the Laplacian and the sweeps
+// of variants 0, 3 and 7 then compute with: fields of up to 4 GiB (16.7 M packages in FP32).
 template <typename T>
+static bool narrow_offsets(const sgrid_grid *g) {
+    return (double)g->total() * 64.0 * sizeof(T) <= 4294967296.0;
+}
+
+template <typename T, typename I>
 static void launch_dpp_range(const sgrid_grid *g, const T *src, T *dst, int64_t first, int64_t end, int groups,
                              bool nt, hipStream_t st) {
     const int64_t per_block = 16 * (int64_t)groups;
     const int64_t nb = (end - first + per_block - 1) / per_block;
     const T h2 = (T)(g->h * g->h), inv_h = (T)(1.0 / g->h), dt = (T)(0.5 * g->h);
     const dim3 grid((unsigned)nb), block(256);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, st, src, dst, g->face, (I)first, (I)end, (I)nb, h2, inv_h, dt, nt);
+    };
     switch (groups) {
-        case 1: hipLaunchKernelGGL((reinit_dpp_kernel<T, 1>), grid, block, 0, st, src, dst, g->face, first, end, nb, h2, inv_h, dt, nt); break;
-        case 2: hipLaunchKernelGGL((reinit_dpp_kernel<T, 2>), grid, block, 0, st, src, dst, g->face, first, end, nb, h2, inv_h, dt, nt); break;
-        case 3: hipLaunchKernelGGL((reinit_dpp_kernel<T, 3>), grid, block, 0, st, src, dst, g->face, first, end, nb, h2, inv_h, dt, nt); break;
-        case 4: hipLaunchKernelGGL((reinit_dpp_kernel<T, 4>), grid, block, 0, st, src, dst, g->face, first, end, nb, h2, inv_h, dt, nt); break;
-        default: hipLaunchKernelGGL((reinit_dpp_kernel<T, 8>), grid, block, 0, st, src, dst, g->face, first, end, nb, h2, inv_h, dt, nt); break;
+        case 1: launch(reinit_dpp_kernel<T, 1, I>); break;
+        case 2: launch(reinit_dpp_kernel<T, 2, I>); break;
+        case 3: launch(reinit_dpp_kernel<T, 3, I>); break;
+        case 4: launch(reinit_dpp_kernel<T, 4, I>); break;
+        default: launch(reinit_dpp_kernel<T, 8, I>); break;
+    }
+}
+
+template <typename T, typename I>
+static void launch_work(const sgrid_grid *g, const T *src, T *dst, int groups, bool nt, hipStream_t st) {
+    const int64_t per_block = 16 * (int64_t)groups;
+    const int64_t nb = (g->P + per_block - 1) / per_block;
+    const T h2 = (T)(g->h * g->h), inv_h = (T)(1.0 / g->h), dt = (T)(0.5 * g->h);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(256), 0, st, src, dst, g->wface, (I)g->P, (I)nb, h2, inv_h,
+                           dt, nt);
+    };
+    switch (groups) {
+        case 1: launch(reinit_work_kernel<T, 1, I>); break;
+        case 2: launch(reinit_work_kernel<T, 2, I>); break;
+        case 3: launch(reinit_work_kernel<T, 3, I>); break;
+        case 4: launch(reinit_work_kernel<T, 4, I>); break;
+        default: launch(reinit_work_kernel<T, 8, I>); break;
+    }
+}
+
+template <typename T, typename I>
+static void launch_morton(const sgrid_grid *g, const T *src, T *dst, int mode, bool nt, hipStream_t st) {
+    const int64_t nb = (g->P + 15) / 16;
+    const T h2 = (T)(g->h * g->h), inv_h = (T)(1.0 / g->h), dt = (T)(0.5 * g->h);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(256), 0, st, src, dst, g->wface, g->mface, (I)g->P, (I)nb,
+                           h2, inv_h, dt, nt);
+    };
+    switch (mode) {
+        case 0: launch(reinit_morton_kernel<T, 0, I>); break;
+        case 1: launch(reinit_morton_kernel<T, 1, I>); break;
+        default: launch(reinit_morton_kernel<T, 2, I>); break;
     }
 }
 
@@ -838,18 +877,12 @@ static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *ds
     const dim3 grid((unsigned)nb), block(256);
     // streaming stores when the two field buffers exceed the last-level cache
     const bool nt = 2.0 * (double)g->total() * 64.0 * sizeof(T) > kLastLevelCacheBytes;
+    const bool narrow = narrow_offsets<T>(g);
     if (cfg.variant == 7) {
-        const int64_t nb7 = (g->P + 15) / 16;
-        const dim3 grid7((unsigned)nb7);
-        if (mode == 0)
-            hipLaunchKernelGGL((reinit_morton_kernel<T, 0>), grid7, block, 0, st, src, dst, g->wface, g->mface, g->P,
-                               nb7, h2, inv_h, dt, nt);
-        else if (mode == 1)
-            hipLaunchKernelGGL((reinit_morton_kernel<T, 1>), grid7, block, 0, st, src, dst, g->wface, g->mface, g->P,
-                               nb7, h2, inv_h, dt, nt);
+        if (narrow)
+            launch_morton<T, uint32_t>(g, src, dst, mode, nt, st);
         else
-            hipLaunchKernelGGL((reinit_morton_kernel<T, 2>), grid7, block, 0, st, src, dst, g->wface, g->mface, g->P,
-                               nb7, h2, inv_h, dt, nt);
+            launch_morton<T, int64_t>(g, src, dst, mode, nt, st);
     } else if (cfg.variant == 6) {
         const int64_t n_sets = (g->P + 3) / 4;
         const int64_t nbp = std::min<int64_t>((int64_t)cu_count() * cfg.groups, (n_sets + 3) / 4);
@@ -868,13 +901,10 @@ static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *ds
         hipLaunchKernelGGL(reinit_share_kernel<T>, dim3((unsigned)ng), dim3(1024), 0, st, src, dst, g->work, g->sface,
                            g->P, ng, h2, inv_h, dt);
     } else if (cfg.variant == 3) {
-        switch (cfg.groups) {
-            case 1: hipLaunchKernelGGL((reinit_work_kernel<T, 1>), grid, block, 0, st, src, dst, g->wface, g->P, nb, h2, inv_h, dt, nt); break;
-            case 2: hipLaunchKernelGGL((reinit_work_kernel<T, 2>), grid, block, 0, st, src, dst, g->wface, g->P, nb, h2, inv_h, dt, nt); break;
-            case 3: hipLaunchKernelGGL((reinit_work_kernel<T, 3>), grid, block, 0, st, src, dst, g->wface, g->P, nb, h2, inv_h, dt, nt); break;
-            case 4: hipLaunchKernelGGL((reinit_work_kernel<T, 4>), grid, block, 0, st, src, dst, g->wface, g->P, nb, h2, inv_h, dt, nt); break;
-            default: hipLaunchKernelGGL((reinit_work_kernel<T, 8>), grid, block, 0, st, src, dst, g->wface, g->P, nb, h2, inv_h, dt, nt); break;
-        }
+        if (narrow)
+            launch_work<T, uint32_t>(g, src, dst, cfg.groups, nt, st);
+        else
+            launch_work<T, int64_t>(g, src, dst, cfg.groups, nt, st);
     } else if (cfg.variant == 2) {
         const int64_t n_sets = (g->P + 3) / 4;
         const int64_t nbp = std::min<int64_t>((int64_t)cu_count() * cfg.groups, (n_sets + 3) / 4);
@@ -884,7 +914,10 @@ static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *ds
         hipLaunchKernelGGL(reinit_lds_kernel<T>, grid, block, 0, st, src, dst, g->face, g->P, nb, cfg.groups, h2,
                            inv_h, dt);
     } else {
-        launch_dpp_range<T>(g, src, dst, 2, 2 + g->P, cfg.groups, nt, st);
+        if (narrow)
+            launch_dpp_range<T, uint32_t>(g, src, dst, 2, 2 + g->P, cfg.groups, nt, st);
+        else
+            launch_dpp_range<T, int64_t>(g, src, dst, 2, 2 + g->P, cfg.groups, nt, st);
     }
     SG_CHECK_LAUNCH("reinit sweep");
     return SGRID_OK;
@@ -1114,6 +1147,28 @@ extern "C" sgrid_status sgrid_sequential_update(const sgrid_grid *g, sgrid_dtype
     return SGRID_OK;
 }
 
+template <typename T>
+static void launch_laplacian(const sgrid_grid *g, const T *phi, T *out, bool work, bool stream_out, hipStream_t st) {
+    const int64_t nt = g->total(), nb = (nt + 15) / 16;
+    const T inv_h2 = (T)(1.0 / (g->h * g->h));
+    auto launch = [&](auto kernel, auto index) {
+        using I = decltype(index);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(256), 0, st, phi, out, g->face, g->wface, (I)nt, (I)nb,
+                           inv_h2, stream_out);
+    };
+    if (sgrid::narrow_offsets<T>(g)) {
+        if (work)
+            launch(laplacian_kernel<T, true, uint32_t>, uint32_t());
+        else
+            launch(laplacian_kernel<T, false, uint32_t>, uint32_t());
+    } else {
+        if (work)
+            launch(laplacian_kernel<T, true, int64_t>, int64_t());
+        else
+            launch(laplacian_kernel<T, false, int64_t>, int64_t());
+    }
+}
+
 extern "C" sgrid_status sgrid_compute_laplacian(const sgrid_grid *g, sgrid_dtype dtype, const void *phi, void *out,
                                                 void *stream) {
     sgrid::clear_error();
@@ -1123,27 +1178,13 @@ extern "C" sgrid_status sgrid_compute_laplacian(const sgrid_grid *g, sgrid_dtype
     SG_REQUIRE(dtype == SGRID_F32 || dtype == SGRID_F64, "unknown dtype %d", (int)dtype);
     hipStream_t st = sg_stream(stream);
     const int64_t nt = g->total();
-    const int64_t nb = (nt + 15) / 16;
     const bool work = sgrid::stencil_in_worklist_order(g, dtype == SGRID_F32 ? 4 : 8);
     // streaming stores when phi and the output together exceed the last-level cache
     const bool stream_out = (double)nt * 64.0 * (dtype == SGRID_F32 ? 4.0 : 8.0) * 2.0 > sgrid::kLastLevelCacheBytes;
-    if (dtype == SGRID_F32) {
-        if (work)
-            hipLaunchKernelGGL((laplacian_kernel<float, true>), dim3((unsigned)nb), dim3(256), 0, st,
-                               (const float *)phi, (float *)out, g->face, g->wface, nt, nb,
-                               (float)(1.0 / (g->h * g->h)), stream_out);
-        else
-            hipLaunchKernelGGL((laplacian_kernel<float, false>), dim3((unsigned)nb), dim3(256), 0, st,
-                               (const float *)phi, (float *)out, g->face, g->wface, nt, nb,
-                               (float)(1.0 / (g->h * g->h)), stream_out);
-    } else {
-        if (work)
-            hipLaunchKernelGGL((laplacian_kernel<double, true>), dim3((unsigned)nb), dim3(256), 0, st,
-                               (const double *)phi, (double *)out, g->face, g->wface, nt, nb, 1.0 / (g->h * g->h), stream_out);
-        else
-            hipLaunchKernelGGL((laplacian_kernel<double, false>), dim3((unsigned)nb), dim3(256), 0, st,
-                               (const double *)phi, (double *)out, g->face, g->wface, nt, nb, 1.0 / (g->h * g->h), stream_out);
-    }
+    if (dtype == SGRID_F32)
+        launch_laplacian<float>(g, (const float *)phi, (float *)out, work, stream_out, st);
+    else
+        launch_laplacian<double>(g, (const double *)phi, (double *)out, work, stream_out, st);
     SG_CHECK_LAUNCH("laplacian");
     return SGRID_OK;
 }
