@@ -119,7 +119,7 @@ constexpr int64_t kMaxGrid = 0x7FFFFFFF;
 // instructions, needs 28 for the sixteen of a row.  A sweep with these and with
 // 32-bit offsets, before and now: torus at 256^3 points 4.7 and 4.55 us, prism512
 // 12.2 and 12.05, torus at 768^3 23.5 and 22.2, at 2048^3 221.7 and 217.6.
-//  The select's mask is VCC.  The
+// The select's mask is VCC.  The
 // block's first two instructions give the two wait states that the hardware asks
 // for between a vector write and a DPP read of its result.  Must run in every lane
 // of a package: a lane outside the active mask supplies 0 to its neighbours, so a

@@ -1302,47 +1302,88 @@ __global__ __launch_bounds__(256, 3) void learned_kernel(MlpDev W, const float *
     }
 }
 
-// Plain integral of single cells (the fallback): the 32 taps of the cell's
-// dual-cell query, each with its own cut fraction from central differences,
-// with the plain kernels' fractions and tap sums, so the value is the plain
-// one bit for bit.
-__device__ __forceinline__ void fallback_point(const float *__restrict__ phi, const uint32_t *__restrict__ nbr,
-                                               const uint32_t *__restrict__ core_list, int64_t n_core, float inv_h,
-                                               float inv_2h, int64_t o, float *__restrict__ out) {
-    const int64_t ci = o / 64;
-    const int c = (int)(o % 64);
-    const uint32_t *row = nbr + (int64_t)core_list[ci] * 27;
-    auto at = [&](int x, int y, int z) -> float {   // local shift in [-2, 6] per axis
-        const int kx = (x + 4) >> 2, ky = (y + 4) >> 2, kz = (z + 4) >> 2;
-        const int d = (x + 4 - 4 * kx) + 4 * (y + 4 - 4 * ky) + 16 * (z + 4 - 4 * kz);
-        return phi[(int64_t)row[kx + 3 * ky + 9 * kz] * 64 + d];
-    };
-    float kw, kx, ky, kz;
-    sgrid::tap_sums(
-        [&](int x, int y, int z) {
-            const float gx = (at(x + 1, y, z) - at(x - 1, y, z)) * inv_2h;
-            const float gy = (at(x, y + 1, z) - at(x, y - 1, z)) * inv_2h;
-            const float gz = (at(x, y, z + 1) - at(x, y, z - 1)) * inv_2h;
-            return sgrid::plane_cube_fraction(at(x, y, z) * inv_h, gx, gy, gz);
-        },
-        c & 3, (c >> 2) & 3, c >> 4, kw, kx, ky, kz);
-    const int64_t stride = n_core * 64;
-    out[o] = kw;
-    out[stride + o] = kx;
-    out[2 * stride + o] = ky;
-    out[3 * stride + o] = kz;
-}
+// Plain integrals of the listed points, `*fb_count` of them, read on the device:
+// a persistent grid strides over the list, so its size need not be known at
+// launch.  The 32 taps of a point's dual-cell query, each with its own cut
+// fraction from central differences, with the plain kernels' fractions and tap
+// sums, so the value is the plain one bit for bit.  A wavefront takes kFbPts
+// points at a time: one tap per lane, two points per step, kFbStep points' loads
+// issued together; the fractions go to LDS, and one lane per point sums them.
+// Bound by the latency of its scattered reads (list, core package, neighbour
+// row, seven values): 11.6 us for prism512's points and 154 us for torus2048's,
+// 35 and 474 us with a lane per point, which took its 32 taps one after another.
+constexpr int kFbPts = 16, kFbStep = 8;
 
-// The listed points, `*fb_count` of them, read on the device: a persistent
-// grid strides over the list, so its size need not be known at launch.
 __global__ __launch_bounds__(256) void fallback_kernel(const float *__restrict__ phi, const uint32_t *__restrict__ nbr,
                                                        const uint32_t *__restrict__ core_list, int64_t n_core,
                                                        float inv_h, float inv_2h, const uint32_t *__restrict__ fb_list,
                                                        const uint32_t *__restrict__ fb_count, float *__restrict__ out) {
-    const int64_t count = *fb_count;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < count;
-         t += (int64_t)gridDim.x * blockDim.x)
-        fallback_point(phi, nbr, core_list, n_core, inv_h, inv_2h, fb_list[t], out);
+    __shared__ float s_v[4][kFbPts][33];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t count = *fb_count, stride = n_core * 64;
+    // this lane's tap: block 0 the eight nearest, 1 to 3 those two cells apart
+    // along x, y, z (tap_sums); (tx, ty, tz) relative to the point
+    const int half = lane & 32, tap = lane & 31, blk = tap >> 3;
+    const int tx = blk == 1 ? 3 * ((tap >> 2) & 1) - 1 : (tap >> 2) & 1;
+    const int ty = blk == 2 ? 3 * ((tap >> 1) & 1) - 1 : (tap >> 1) & 1;
+    const int tz = blk == 3 ? 3 * (tap & 1) - 1 : tap & 1;
+    for (int64_t base = ((int64_t)blockIdx.x * 4 + w) * kFbPts; base < count; base += (int64_t)gridDim.x * 4 * kFbPts) {
+        const int n = (int)(count - base < kFbPts ? count - base : kFbPts);
+        const int mine = lane % kFbPts;
+        const uint32_t o = fb_list[base + (mine < n ? mine : n - 1)];   // points past the list repeat its last one
+        const uint32_t pkg = core_list[o >> 6];
+#pragma unroll 1
+        for (int q0 = 0; q0 < n; q0 += kFbStep) {
+            uint32_t id[kFbStep / 2];
+            int cell[kFbStep / 2];
+#pragma unroll
+            for (int m = 0; m < kFbStep / 2; ++m) {
+                const int q = q0 + 2 * m + (half >> 5);
+                cell[m] = (int)((uint32_t)__shfl((int)o, q) & 63u);
+                id[m] = nbr[(int64_t)(uint32_t)__shfl((int)pkg, q) * 27 + min(tap, 26)];
+            }
+            float v[kFbStep / 2][7];   // the tap's own value, then -x, +x, -y, +y, -z, +z
+#pragma unroll
+            for (int m = 0; m < kFbStep / 2; ++m) {
+                // package and offset of a window point, local position + 4 per axis
+                const int x = (cell[m] & 3) + tx + 4, y = ((cell[m] >> 2) & 3) + ty + 4, z = (cell[m] >> 4) + tz + 4;
+                auto at = [&](int x, int y, int z) {
+                    const int k = (x >> 2) + 3 * (y >> 2) + 9 * (z >> 2);
+                    const int d = (x & 3) + 4 * (y & 3) + 16 * (z & 3);
+                    return phi[(int64_t)(uint32_t)__shfl((int)id[m], half + k) * 64 + d];
+                };
+                v[m][0] = at(x, y, z);
+                v[m][1] = at(x - 1, y, z);
+                v[m][2] = at(x + 1, y, z);
+                v[m][3] = at(x, y - 1, z);
+                v[m][4] = at(x, y + 1, z);
+                v[m][5] = at(x, y, z - 1);
+                v[m][6] = at(x, y, z + 1);
+            }
+#pragma unroll
+            for (int m = 0; m < kFbStep / 2; ++m)
+                s_v[w][q0 + 2 * m + (half >> 5)][tap] =
+                    sgrid::plane_cube_fraction(v[m][0] * inv_h, (v[m][2] - v[m][1]) * inv_2h,
+                                               (v[m][4] - v[m][3]) * inv_2h, (v[m][6] - v[m][5]) * inv_2h);
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (lane < n) {
+            const float *t = s_v[w][lane];
+            float kw, kx, ky, kz;
+            sgrid::tap_sums(
+                [&](int x, int y, int z) {
+                    auto far = [](int a) { return a < 0 || a > 1; };
+                    const int b = far(x) ? 1 : (far(y) ? 2 : (far(z) ? 3 : 0));
+                    return t[8 * b + 4 * (x > 0) + 2 * (y > 0) + (z > 0)];
+                },
+                0, 0, 0, kw, kx, ky, kz);
+            out[o] = kw;
+            out[stride + o] = kx;
+            out[2 * stride + o] = ky;
+            out[3 * stride + o] = kz;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
 }
 
 // Network inputs (windows of phi / h) and saturation of every core point, in
@@ -1403,7 +1444,7 @@ static sgrid_status learned_launch(const sgrid_grid *g, const float *phi, const 
                        st, m->dev(), phi, g->nbr, g->core_list, g->n_core, ci0, ci_end, inv_h, inv_2h, m->gate_tau,
                        m->kw_lo, m->kw_hi, out, fb_list, count);
     SG_CHECK_LAUNCH("learned integrals");
-    const int64_t fb_blocks = std::min<int64_t>((cells + 255) / 256, 4 * (int64_t)cu_count());
+    const int64_t fb_blocks = std::min<int64_t>((cells + 4 * kFbPts - 1) / (4 * kFbPts), 4 * (int64_t)cu_count());
     hipLaunchKernelGGL(fallback_kernel, dim3((unsigned)fb_blocks), dim3(256), 0, st, phi, g->nbr, g->core_list,
                        g->n_core, inv_h, inv_2h, fb_list, count, out);
     SG_CHECK_LAUNCH("fallback integrals");
