@@ -172,14 +172,20 @@ struct GlobalX {
 // dy 4][Bp], Bp = B rounded up to kTrainChunk (rows past B carry no error).
 // The C layout holds four consecutive samples of a unit per lane, so these
 // rows are written in 8-byte pieces, and the operands of the products over
-// the samples are 16-byte pieces of them.
+// the samples are 16-byte pieces of them.  dY is handed on in FP32 too (the
+// output biases' gradient), with each workgroup's loss.
+//
+// Sums go in a fixed order: the samples of a chunk, then the chunks one by one.
+// Up to kMaxChunks chunks of kTrainChunk samples that is the order of a running
+// sum over partial gradients of 64 samples; a change in it would be an ulp in
+// the gradient, but Adam divides by the gradient's own size, and 16 steps later
+// a batch in ten has its outputs 1e-4 apart.
 // ---------------------------------------------------------------------------
 constexpr int kTrainRows = 16;         // samples per workgroup of the first kernel
 constexpr int kTrainChunk = 64;        // samples per chunk: two MFMA steps, at least
-constexpr int kMaxChunks = 64;         // partial gradients kept
+constexpr int kMaxChunks = 256;        // partial gradients kept (46 MB)
 constexpr int kActUnits = 4 * kH + kOut;
 constexpr int rA1 = 0, rA2 = kH, rD1 = 2 * kH, rD2 = 3 * kH, rDY = 4 * kH;
-constexpr int kTileSums = 8;           // per workgroup: sum of dY (4 outputs), the loss
 constexpr int kActPad = kH + 8;        // LDS row of activations, padded by 16 bytes (banks)
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -193,7 +199,7 @@ __global__ __launch_bounds__(256, 1) void train_rows_kernel(MlpDev W, const floa
                                                             const float *__restrict__ t_in,
                                                             const float *__restrict__ dy_in, float4 lw,
                                                             bf16 *__restrict__ acts, int64_t Bp,
-                                                            float *__restrict__ tile_sums) {
+                                                            float *__restrict__ dys, float *__restrict__ tile_loss) {
     __shared__ __attribute__((aligned(16))) bf16 s_a1[kTrainRows * kActPad];
     __shared__ __attribute__((aligned(16))) bf16 s_a2[kTrainRows * kActPad];
     __shared__ __attribute__((aligned(16))) bf16 s_d2[kTrainRows * kActPad];
@@ -304,19 +310,18 @@ __global__ __launch_bounds__(256, 1) void train_rows_kernel(MlpDev W, const floa
         for (int i = 0; i < 4; ++i) {
             const float e = y[i] - dy[i];
             const bool in = r < kOut && base + 4 * q + i < B;   // rows past B contribute nothing
-            lsum += in ? wo * e * e : 0.f;
+            lsum = in ? fmaf(wo * e, e, lsum) : lsum;
             dy[i] = in ? 2.0f * wo * e / (float)B : 0.f;
         }
     }
     if (w == 0) {
-        float v = r < kOut ? dy[0] + dy[1] + dy[2] + dy[3] : 0.f;
-        v += __shfl_xor(v, 16);
-        v += __shfl_xor(v, 32);
-        if (lane < kOut) tile_sums[(int64_t)blockIdx.x * kTileSums + lane] = v;
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) lsum += __shfl_down(lsum, off);
-        if (lane == 0) tile_sums[(int64_t)blockIdx.x * kTileSums + kOut] = lsum;
-        if (r < kOut) hand_on(dy, r, rDY, nullptr);
+        if (lane == 0) tile_loss[blockIdx.x] = lsum;
+        if (r < kOut) {
+            hand_on(dy, r, rDY, nullptr);
+            *reinterpret_cast<float4 *>(dys + r * Bp + base + 4 * q) = make_float4(dy[0], dy[1], dy[2], dy[3]);
+        }
     }
     // dA2 = dY W3 (K = 4, FP32 masters), dZ2 = dA2 * gelu'(z2)
     {
@@ -355,27 +360,75 @@ __global__ __launch_bounds__(256, 1) void train_rows_kernel(MlpDev W, const floa
 // Weight gradients C[o][i] = sum over a chunk's samples of D[m][o] S[m][i].
 // One wavefront per column tile of 16 inputs i and chunk: it reads its B
 // operand once and the eight A operands of all 128 outputs (roles 0..13: W1,
-// whose inputs are x rounded to BF16 and whose column 216 is the constant 1,
-// the bias; 14..21: W2; 22: W3, one A and eight B operands; 23: b2, with the
-// constant 1 as its only input).
+// whose inputs are x rounded to BF16; 14..21: W2; 22: W3, one A and eight B
+// operands).  Role 23 takes the biases, the errors' sums over the samples in
+// their order, one row of errors per lane.
 constexpr int kRolesW1 = kInPad / 16, kRolesW2 = kH / 16, kRoles = kRolesW1 + kRolesW2 + 2;
-static_assert(kRoles % 4 == 0 && kInPad > kIn, "four roles per workgroup; a padding column for the bias");
+static_assert(kRoles % 4 == 0, "four roles per workgroup");
+
+__device__ __forceinline__ void bias_grad(const bf16 *acts, const float *dys, int64_t Bp, int64_t first, int units,
+                                          float *P, int lane) {
+#pragma unroll 1
+    for (int h = 0; h < kH / 64; ++h) {
+        const int o = 64 * h + lane;
+        const bf16 *d1 = acts + (int64_t)(rD1 + o) * Bp + first, *d2 = acts + (int64_t)(rD2 + o) * Bp + first;
+        float s1 = 0.f, s2 = 0.f;
+        for (int u = 0; u < units; ++u) {
+            bf16x8 a[kTrainChunk / 8], b[kTrainChunk / 8];
+#pragma unroll
+            for (int k = 0; k < kTrainChunk / 8; ++k) {
+                a[k] = ld8(d1 + kTrainChunk * u + 8 * k);
+                b[k] = ld8(d2 + kTrainChunk * u + 8 * k);
+            }
+            float t1 = 0.f, t2 = 0.f;
+#pragma unroll
+            for (int m = 0; m < kTrainChunk; ++m) {
+                t1 += (float)a[m / 8][m % 8];
+                t2 += (float)b[m / 8][m % 8];
+            }
+            s1 += t1;
+            s2 += t2;
+        }
+        P[oB1 + o] = s1;
+        P[oB2 + o] = s2;
+    }
+    if (lane < kOut) {
+        float s3 = 0.f;
+        for (int u = 0; u < units; ++u) {
+            float4 v[kTrainChunk / 4];
+#pragma unroll
+            for (int k = 0; k < kTrainChunk / 4; ++k)
+                v[k] = *reinterpret_cast<const float4 *>(dys + lane * Bp + first + kTrainChunk * u + 4 * k);
+            float t = 0.f;
+#pragma unroll
+            for (int k = 0; k < kTrainChunk / 4; ++k) t = (((t + v[k].x) + v[k].y) + v[k].z) + v[k].w;
+            s3 += t;
+        }
+        P[oB3 + lane] = s3;
+    }
+}
 
 __global__ __launch_bounds__(256) void weight_grad_kernel(const float *__restrict__ x, int64_t B,
-                                                          const bf16 *__restrict__ acts, int64_t Bp, int steps,
+                                                          const bf16 *__restrict__ acts,
+                                                          const float *__restrict__ dys, int64_t Bp, int steps,
                                                           float *__restrict__ part) {
     const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
     const int role = (int)(blockIdx.x % (kRoles / 4)) * 4 + (threadIdx.x >> 6);
     const int64_t chunk = blockIdx.x / (kRoles / 4);
     const int64_t first = chunk * steps * 32;
     float *P = part + chunk * kNParam;
+    if (role == kRoles - 1) {
+        const int64_t left = (Bp - first) / kTrainChunk, mine = steps * 32 / kTrainChunk;
+        bias_grad(acts, dys, Bp, first, (int)(left < mine ? left : mine), P, lane);
+        return;
+    }
     floatx4 acc[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
     bf16x8 zero;
 #pragma unroll
     for (int j = 0; j < 8; ++j) zero[j] = (bf16)0.f;
-    const bool is_w1 = role < kRolesW1, is_w2 = !is_w1 && role < kRolesW1 + kRolesW2, is_w3 = role == kRoles - 2;
+    const bool is_w1 = role < kRolesW1, is_w2 = !is_w1 && role < kRolesW1 + kRolesW2, is_w3 = role == kRolesW1 + kRolesW2;
     const int it = is_w1 ? role : role - kRolesW1;
     const int col = 16 * it + r;
     const bf16 *rows8 = acts + (int64_t)((is_w1 ? rD1 : (is_w3 ? rA2 : rD2)) + r) * Bp;   // eight tiles' operands
@@ -392,13 +445,10 @@ __global__ __launch_bounds__(256) void weight_grad_kernel(const float *__restric
                 v[j] = x[m * kIn + (col < kIn ? col : 0)];
             }
 #pragma unroll
-            for (int j = 0; j < 8; ++j) one[j] = (bf16)(m0 + j >= B ? 0.f : (col < kIn ? v[j] : (col == kIn ? 1.f : 0.f)));
-        } else if (is_w2 || is_w3) {
+            for (int j = 0; j < 8; ++j) one[j] = (bf16)(m0 + j < B && col < kIn ? v[j] : 0.f);
+        } else {
             one = ld8(row1 + m0);
             if (is_w3 && r >= kOut) one = zero;
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) one[j] = (bf16)(r == 0 ? 1.f : 0.f);
         }
         bf16x8 many[8];
 #pragma unroll
@@ -410,16 +460,13 @@ __global__ __launch_bounds__(256) void weight_grad_kernel(const float *__restric
     for (int t = 0; t < 8; ++t)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int o = 16 * t + 4 * q + j;   // output (W1, W2, b2)
+            const int o = 16 * t + 4 * q + j;   // output (W1, W2)
             if (is_w1) {
                 if (col < kIn) P[oW1 + o * kIn + col] = acc[t][j];
-                if (col == kIn) P[oB1 + o] = acc[t][j];
             } else if (is_w2) {
                 P[oW2 + o * kH + col] = acc[t][j];
-            } else if (is_w3) {
-                if (4 * q + j < kOut) P[oW3 + (4 * q + j) * kH + 16 * t + r] = acc[t][j];
-            } else if (r == 0) {
-                P[oB2 + o] = acc[t][j];
+            } else if (4 * q + j < kOut) {
+                P[oW3 + (4 * q + j) * kH + 16 * t + r] = acc[t][j];
             }
         }
 }
@@ -469,39 +516,38 @@ __global__ __launch_bounds__(256) void adam_kernel(AdamArgs A, const float *__re
 
 // Gradient of parameter p = sum over the chunks of part[c][p], in chunk order
 // (deterministic); written to `grad`, or given to Adam at once.  The last
-// workgroup takes the output biases and the loss from the tiles' sums.
-constexpr int kReduceBlocks = (oB3 + 255) / 256 + 1;
+// workgroup sums the loss, four tiles (64 samples) at a time, in their order.
+constexpr int kReduceBlocks = (kNParam + 255) / 256 + 1;
 
 template <bool ADAM>
 __global__ __launch_bounds__(256) void reduce_kernel(const float *__restrict__ part, int n_part,
-                                                     const float *__restrict__ tile_sums, int64_t n_tiles,
+                                                     const float *__restrict__ tile_loss, int64_t n_tiles,
                                                      float *__restrict__ grad, AdamArgs A,
                                                      float *__restrict__ loss_out) {
     if (blockIdx.x == kReduceBlocks - 1) {
-        // lanes 8 k + c of 256: column c of the tiles k, k + 32, ...; the 32
-        // partial sums of a column are added in order
         __shared__ float s[256];
-        const int c = threadIdx.x & (kTileSums - 1);
-        float v = 0.f;
-        if (c <= kOut)
-            for (int64_t k = threadIdx.x / kTileSums; k < n_tiles; k += 256 / kTileSums) v += tile_sums[k * kTileSums + c];
-        s[threadIdx.x] = v;
-        __syncthreads();
-        if (threadIdx.x > kOut) return;
-        v = 0.f;
-        for (int k = 0; k < 256 / kTileSums; ++k) v += s[k * kTileSums + c];
-        if (c < kOut) {
-            if (ADAM)
-                adam_update(A, oB3 + c, v);
-            else
-                grad[oB3 + c] = v;
-        } else if (loss_out) {
-            *loss_out = v;
+        if (loss_out == nullptr) return;
+        const int64_t units = n_tiles / 4;
+        float sum = 0.f;
+        for (int64_t u0 = 0; u0 < units; u0 += 256) {
+            const int64_t u = u0 + threadIdx.x;
+            if (u < units) {
+                const float4 t = reinterpret_cast<const float4 *>(tile_loss)[u];
+                s[threadIdx.x] = ((t.x + t.y) + t.z) + t.w;
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                const int n = (int)(units - u0 < 256 ? units - u0 : 256);
+#pragma unroll 8
+                for (int k = 0; k < n; ++k) sum += s[k];
+            }
+            __syncthreads();
         }
+        if (threadIdx.x == 0) *loss_out = sum;
         return;
     }
     const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= oB3) return;
+    if (p >= kNParam) return;
     float s = 0.f;
 #pragma unroll 8
     for (int g = 0; g < n_part; ++g) s += part[(int64_t)g * kNParam + p];
@@ -537,9 +583,10 @@ struct sgrid_mlp {
     int device = 0;
     float *w = nullptr, *m = nullptr, *v = nullptr;
     bf16 *w1b = nullptr, *w2b = nullptr, *w2tb = nullptr, *w3b = nullptr;
-    // training workspace: partial gradients [chunk][parameter], the tiles'
-    // sums and the rows of activations and errors, for up to train_rows samples
-    float *part = nullptr, *tile_sums = nullptr;
+    // training workspace: partial gradients [chunk][parameter], dY by rows and
+    // the tiles' losses, and the rows of activations and errors, for up to
+    // train_rows samples
+    float *part = nullptr, *dys = nullptr, *tile_loss = nullptr;
     bf16 *acts = nullptr;
     int64_t train_rows = 0;
     int64_t step = 0;
@@ -559,7 +606,7 @@ namespace sgrid {
 
 static void free_mlp(sgrid_mlp *m) {
     if (!m) return;
-    void *ptrs[] = {m->w, m->m, m->v, m->w1b, m->w2b, m->w2tb, m->w3b, m->part, m->tile_sums, m->acts, m->fallback};
+    void *ptrs[] = {m->w, m->m, m->v, m->w1b, m->w2b, m->w2tb, m->w3b, m->part, m->dys, m->tile_loss, m->acts, m->fallback};
     for (void *p : ptrs) dev_free(p);
     if (m->done) (void)hipEventDestroy(m->done);
     delete m;
@@ -602,17 +649,20 @@ struct TrainSplit {
 
 static sgrid_status ensure_train(sgrid_mlp *m, const TrainSplit &t) {
     if (t.rows <= m->train_rows) return SGRID_OK;
-    if (m->part || m->tile_sums || m->acts) SG_CHECK_HIP(hipDeviceSynchronize());
+    if (m->part || m->dys || m->tile_loss || m->acts) SG_CHECK_HIP(hipDeviceSynchronize());
     dev_free(m->part);
-    dev_free(m->tile_sums);
+    dev_free(m->dys);
+    dev_free(m->tile_loss);
     dev_free(m->acts);
-    m->part = m->tile_sums = nullptr;
+    m->part = m->dys = m->tile_loss = nullptr;
     m->acts = nullptr;
     m->train_rows = 0;
     const int64_t chunks = std::min<int64_t>(t.rows / kTrainChunk, kMaxChunks);
     sgrid_status s = dev_alloc((void **)&m->part, (size_t)chunks * kNParam * 4, "MLP partial gradients");
     if (s != SGRID_OK) return s;
-    s = dev_alloc((void **)&m->tile_sums, (size_t)t.tiles * kTileSums * 4, "MLP partial losses");
+    s = dev_alloc((void **)&m->dys, (size_t)t.rows * kOut * 4, "MLP output errors");
+    if (s != SGRID_OK) return s;
+    s = dev_alloc((void **)&m->tile_loss, (size_t)t.tiles * 4, "MLP partial losses");
     if (s != SGRID_OK) return s;
     s = dev_alloc((void **)&m->acts, (size_t)t.rows * kActUnits * sizeof(bf16), "MLP activations");
     if (s != SGRID_OK) return s;
@@ -641,12 +691,12 @@ static sgrid_status run_backward(sgrid_mlp *m, const float *x, int64_t B, const 
     sgrid_status s = ensure_train(m, sp);
     if (s != SGRID_OK) return s;
     hipLaunchKernelGGL(train_rows_kernel, dim3((unsigned)sp.tiles), dim3(256), 0, st, m->dev(), x, B, t, dy,
-                       make_float4(lw[0], lw[1], lw[2], lw[3]), m->acts, sp.rows, m->tile_sums);
+                       make_float4(lw[0], lw[1], lw[2], lw[3]), m->acts, sp.rows, m->dys, m->tile_loss);
     SG_CHECK_LAUNCH("MLP forward and backward");
     hipLaunchKernelGGL(weight_grad_kernel, dim3((unsigned)(sp.chunks * (kRoles / 4))), dim3(256), 0, st, x, B, m->acts,
-                       sp.rows, sp.steps, m->part);
+                       m->dys, sp.rows, sp.steps, m->part);
     SG_CHECK_LAUNCH("MLP weight gradient");
-    hipLaunchKernelGGL(reduce_kernel<ADAM>, dim3(kReduceBlocks), dim3(256), 0, st, m->part, sp.chunks, m->tile_sums,
+    hipLaunchKernelGGL(reduce_kernel<ADAM>, dim3(kReduceBlocks), dim3(256), 0, st, m->part, sp.chunks, m->tile_loss,
                        sp.tiles, grad, A, loss);
     SG_CHECK_LAUNCH("MLP gradient reduction");
     return SGRID_OK;

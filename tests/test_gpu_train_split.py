@@ -1,5 +1,5 @@
 """Training batches at the edges of the kernels' split: sixteen-sample tiles,
-chunks of 64 samples, and (above 4096 samples) longer chunks with a shorter
+chunks of 64 samples, and (above 16384 samples) longer chunks with a shorter
 last one.  The gradient against the FP64 oracle within the propagated
 rounding error (tests/mlp_bounds.py), the output biases and the loss within
 FP32 summation error, and a train step bit for bit equal to its parts."""
@@ -23,7 +23,7 @@ def sg():
     return sg
 
 
-@pytest.mark.parametrize("B", [15, 16, 17, 63, 65, 129, 4096, 4097, 4161])
+@pytest.mark.parametrize("B", [15, 16, 17, 63, 65, 129, 4096, 4097, 4161, 16385])
 def test_gradient_at_split_edges(sg, B):
     w = init_params(40)
     model = sg.Mlp(w)
@@ -42,7 +42,7 @@ def test_gradient_at_split_edges(sg, B):
     assert np.all(np.abs(got[-4:] - dy.astype(np.float64).sum(0)) <= 2.0 ** -23 * np.abs(dy).sum(0, dtype=np.float64))
 
 
-@pytest.mark.parametrize("B", [1, 70, 4161])
+@pytest.mark.parametrize("B", [1, 70, 4161, 16449])
 def test_train_step_equals_its_parts(sg, B):
     rng = np.random.default_rng(B + 1)
     x = torch.from_numpy((rng.standard_normal((B, 216)) * 2.0).astype(np.float32)).cuda()
@@ -55,7 +55,8 @@ def test_train_step_equals_its_parts(sg, B):
     e = y - t
     wo = torch.from_numpy(lw).cuda()
     g = torch.empty(sg.MLP_N_PARAMS, device="cuda")
-    b.backward(x, (2.0 * wo * e) / float(B), g)
+    # (a device tensor: by a host number torch multiplies with the reciprocal)
+    b.backward(x, (2.0 * wo * e) / torch.full((1,), float(B), device="cuda"), g)
     b.apply_gradient(g, 1e-3)
     for p, r in zip(a.state(), b.state()):
         assert np.array_equal(p, r)
