@@ -42,6 +42,14 @@ __device__ __forceinline__ Row<double> load_row<double>(const double *__restrict
     return Row<double>{{a.x, a.y, b.x, b.y}};
 }
 
+__device__ __forceinline__ void store_row_plain(float *__restrict__ p, const Row<float> &r) {
+    *reinterpret_cast<float4 *>(p) = make_float4(r.v[0], r.v[1], r.v[2], r.v[3]);
+}
+__device__ __forceinline__ void store_row_plain(double *__restrict__ p, const Row<double> &r) {
+    reinterpret_cast<double2 *>(p)[0] = make_double2(r.v[0], r.v[1]);
+    reinterpret_cast<double2 *>(p)[1] = make_double2(r.v[2], r.v[3]);
+}
+
 template <typename T>
 __device__ __forceinline__ void store_row(T *__restrict__ p, const Row<T> &r);
 template <>
@@ -50,8 +58,7 @@ __device__ __forceinline__ void store_row<float>(float *__restrict__ p, const Ro
 }
 template <>
 __device__ __forceinline__ void store_row<double>(double *__restrict__ p, const Row<double> &r) {
-    reinterpret_cast<double2 *>(p)[0] = make_double2(r.v[0], r.v[1]);
-    reinterpret_cast<double2 *>(p)[1] = make_double2(r.v[2], r.v[3]);
+    store_row_plain(p, r);
 }
 
 // The same row written with the streaming (non-temporal) hint: used by the
@@ -682,6 +689,8 @@ __global__ __launch_bounds__(256) void cut_fraction_kernel(const float *__restri
 // The operations of the paper's timing test (Sec. 9, Tab. 1).  Sequential
 // access: a small change to every value of every activated package, phi +=
 // delta, streamed as 16-byte rows (rows 0 and 1, the far field, untouched).
+// Plain stores: the lines are in the L2 already, and written through it a band of
+// 4 to 7 MB took 7 to 10 us instead of 4.
 template <typename T>
 __global__ __launch_bounds__(256) void add_kernel(T *__restrict__ phi, int64_t n_rows, T delta) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -690,7 +699,7 @@ __global__ __launch_bounds__(256) void add_kernel(T *__restrict__ phi, int64_t n
     Row<T> r = load_row(p);
 #pragma unroll
     for (int k = 0; k < 4; ++k) r.v[k] += delta;
-    store_row(p, r);
+    store_row_plain(p, r);
 }
 
 // Stencil: the seven-point Laplacian (sum of the six face neighbours - 6 phi)
