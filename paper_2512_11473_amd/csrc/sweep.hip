@@ -191,14 +191,29 @@ __device__ __forceinline__ Row<T> reinit_row(const Stencil<T> &s, T h2, T inv_h,
     return o;
 }
 
+// How a sweep of a field passes through memory: which end it starts from, and how
+// many of a workgroup row's blocks (an XCD's, in the order of their execution)
+// store with the streaming hint, the later ones staying in the Infinity Cache.
+struct SweepPass {
+    bool back;
+    uint32_t stream_rows;
+};
+
+template <typename I>
+__device__ __forceinline__ I sweep_block(I n_blocks, bool back) {
+    const I b = block_of(n_blocks);
+    return back ? n_blocks - 1 - b : b;
+}
+
 // Reinitialisation sweep over the packages [first, end) (all of them: [2,
 // 2 + P)), DPP exchange variant.  A wavefront handles G consecutive sets of
 // four packages and issues all their loads before computing any of them.
 template <typename T, int G, typename I>
 __global__ __launch_bounds__(256) void reinit_dpp_kernel(const T *__restrict__ src, T *__restrict__ dst,
                                                          const uint32_t *__restrict__ face, I first, I end,
-                                                         I n_blocks, T h2, T inv_h, T dt, bool nt) {
-    const I b = block_of(n_blocks);
+                                                         I n_blocks, T h2, T inv_h, T dt, SweepPass pass) {
+    const I b = sweep_block(n_blocks, pass.back);
+    const bool nt = blockIdx.x / 8 < pass.stream_rows;
     const int lane = threadIdx.x & 63;
     const int r = lane & 15;
     const I p0 = first + (b * 4 + (threadIdx.x >> 6)) * (4 * G) + (lane >> 4);
@@ -223,8 +238,9 @@ __global__ __launch_bounds__(256) void reinit_dpp_kernel(const T *__restrict__ s
 template <typename T, int G, typename I>
 __global__ __launch_bounds__(256) void reinit_work_kernel(const T *__restrict__ src, T *__restrict__ dst,
                                                           const uint32_t *__restrict__ wface, I P, I n_blocks, T h2,
-                                                          T inv_h, T dt, bool nt) {
-    const I b = block_of(n_blocks);
+                                                          T inv_h, T dt, SweepPass pass) {
+    const I b = sweep_block(n_blocks, pass.back);
+    const bool nt = blockIdx.x / 8 < pass.stream_rows;
     const int lane = threadIdx.x & 63;
     const int r = lane & 15;
     const I e0 = (b * 4 + (threadIdx.x >> 6)) * (4 * G) + (lane >> 4);
@@ -261,8 +277,9 @@ template <typename T, int MODE, typename I>
 __global__ __launch_bounds__(256) void reinit_morton_kernel(const T *__restrict__ src, T *__restrict__ dst,
                                                             const uint32_t *__restrict__ wface,
                                                             const uint32_t *__restrict__ mface, I P, I n_blocks, T h2,
-                                                            T inv_h, T dt, bool nt) {
-    const I b = block_of(n_blocks);
+                                                            T inv_h, T dt, SweepPass pass) {
+    const I b = sweep_block(n_blocks, pass.back);
+    const bool nt = blockIdx.x / 8 < pass.stream_rows;
     const int r = threadIdx.x & 15;
     const I e = b * 16 + (threadIdx.x >> 4);
     if (e >= P) return;   // whole 16-lane rows (one package each) leave together
@@ -774,13 +791,12 @@ SweepConfig current_sweep_config() {
 
 // The default configuration (0, 1) keeps package-id order while a field is
 // small and takes Morton order from kWorklistBytes on, where the z neighbours
-// of id order lie too far apart to stay in an XCD's L2.  A sweep in id order and
-// in Morton order: prism at 384^3 points (17 MiB a field) 8.4 and 9.0 us, union at
-// 512^3 (25 MiB) 11.5 and 11.5, torus at 512^3 (27 MiB) 13.1 and 12.1, prism512
-// (31 MiB) 13.5 and 13.3, shell at 640^3 (48 MiB) 20.2 and 20.0, sphere at 900^3
-// (70 MiB) 32.7 and 29.3, shell at 1024^3 (142 MiB) 86 and 78, torus at 2048^3
-// (439 MiB) 255 and 224; the Laplacian 14.1 and 13.1 (29 MiB), 42 and 39, 83 and
-// 77, 257 and 235.
+// of id order lie too far apart to stay in an XCD's L2.  A sweep of one field into
+// another in id order and in Morton order: torus at 256^3 points (7 MiB a field) 4.2
+// and 4.2 us, prism at 384^3 (17 MiB) 7.7 and 8.1, union at 512^3 (25 MiB) 10.8 and
+// 10.5, prism512 (31 MiB) 13.0 and 12.4, torus at 768^3 (62 MiB) 24.3 and 23.4, at
+// 1024^3 (110 MiB) 42.3 and 39.1, at 2048^3 (439 MiB) 242 and 230; the Laplacian 13.0
+// and 12.3 (31 MiB), 42.6 and 39.6, 256 and 234.
 constexpr double kWorklistBytes = 24.0 * 1024 * 1024;
 constexpr double kCopyBytes = 64.0 * 1024 * 1024;
 
@@ -790,10 +806,10 @@ static bool default_takes_worklist(const sgrid_grid *g, const SweepConfig &c, si
 
 // What a reinitialisation of n_iter sweeps runs.  The field goes through a
 // worklist-ordered copy (variant 7) in FP32 from kCopyBytes on, when there are
-// sweeps enough to pay for the way in and out (at 4 sweeps variant 3 is ahead up
-// to 100 MiB, at 20 variant 7; below kCopyBytes they are equal even at 100); in
-// FP64 variant 3 (torus at 900^3 points: id order 112 us, variant 3 103, variant 7
-// 110).
+// sweeps enough to pay for the way in and out: at 4 sweeps variant 3 is ahead
+// (torus at 1024^3 points 39.5 us a sweep, variant 7 46.6), at 100 variant 7 (torus
+// at 2048^3 225 and 214; equal below kCopyBytes, prism512 12.1 and 12.1).  In FP64
+// variant 3 (prism512 24.4 us, variant 7 24.3; id order 26.4).
 static SweepConfig reinit_config(const sgrid_grid *g, size_t element, int32_t n_iter) {
     SweepConfig c = current_sweep_config();
     if (default_takes_worklist(g, c, element)) {
@@ -823,13 +839,13 @@ static bool narrow_offsets(const sgrid_grid *g) {
 
 template <typename T, typename I>
 static void launch_dpp_range(const sgrid_grid *g, const T *src, T *dst, int64_t first, int64_t end, int groups,
-                             bool nt, hipStream_t st) {
+                             SweepPass pass, hipStream_t st) {
     const int64_t per_block = 16 * (int64_t)groups;
     const int64_t nb = (end - first + per_block - 1) / per_block;
     const T h2 = (T)(g->h * g->h), inv_h = (T)(1.0 / g->h), dt = (T)(0.5 * g->h);
     const dim3 grid((unsigned)nb), block(256);
     auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, st, src, dst, g->face, (I)first, (I)end, (I)nb, h2, inv_h, dt, nt);
+        hipLaunchKernelGGL(kernel, grid, block, 0, st, src, dst, g->face, (I)first, (I)end, (I)nb, h2, inv_h, dt, pass);
     };
     switch (groups) {
         case 1: launch(reinit_dpp_kernel<T, 1, I>); break;
@@ -841,13 +857,13 @@ static void launch_dpp_range(const sgrid_grid *g, const T *src, T *dst, int64_t 
 }
 
 template <typename T, typename I>
-static void launch_work(const sgrid_grid *g, const T *src, T *dst, int groups, bool nt, hipStream_t st) {
+static void launch_work(const sgrid_grid *g, const T *src, T *dst, int groups, SweepPass pass, hipStream_t st) {
     const int64_t per_block = 16 * (int64_t)groups;
     const int64_t nb = (g->P + per_block - 1) / per_block;
     const T h2 = (T)(g->h * g->h), inv_h = (T)(1.0 / g->h), dt = (T)(0.5 * g->h);
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(256), 0, st, src, dst, g->wface, (I)g->P, (I)nb, h2, inv_h,
-                           dt, nt);
+                           dt, pass);
     };
     switch (groups) {
         case 1: launch(reinit_work_kernel<T, 1, I>); break;
@@ -859,12 +875,12 @@ static void launch_work(const sgrid_grid *g, const T *src, T *dst, int groups, b
 }
 
 template <typename T, typename I>
-static void launch_morton(const sgrid_grid *g, const T *src, T *dst, int mode, bool nt, hipStream_t st) {
+static void launch_morton(const sgrid_grid *g, const T *src, T *dst, int mode, SweepPass pass, hipStream_t st) {
     const int64_t nb = (g->P + 15) / 16;
     const T h2 = (T)(g->h * g->h), inv_h = (T)(1.0 / g->h), dt = (T)(0.5 * g->h);
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(256), 0, st, src, dst, g->wface, g->mface, (I)g->P, (I)nb,
-                           h2, inv_h, dt, nt);
+                           h2, inv_h, dt, pass);
     };
     switch (mode) {
         case 0: launch(reinit_morton_kernel<T, 0, I>); break;
@@ -873,25 +889,46 @@ static void launch_morton(const sgrid_grid *g, const T *src, T *dst, int mode, b
     }
 }
 
+// The pass of one sweep.  Where the two buffers exceed the Infinity Cache the
+// sweeps of a call alternate in direction, so that a sweep starts on the rows that
+// the one before it ended on, and the last kKeepBytes of rows read and written in a
+// sweep are stored without the streaming hint, so that they are there.  (Keeping
+// more pushes out what is kept: the shell at 1024^3 points takes 71.4 us a sweep
+// with 100 MiB, 71.9 with 150, 73.7 with 250 and 78 with 300; the torus at 1200^3
+// 74.1, 72.4, 78.3 and 81.4.)  All forward and all streaming before: 72.6 and 75.6
+// us; the torus at 2048^3 218 us then and 214 now, at 900^3 in FP64 103 and 95.
+constexpr double kKeepBytes = 144.0 * 1024 * 1024;
+
+template <typename T>
+static SweepPass sweep_pass(const sgrid_grid *g, const SweepConfig &cfg, bool exceeds_cache, bool back) {
+    if (!exceeds_cache) return SweepPass{false, 0u};
+    const int64_t per_block = 16 * (int64_t)(cfg.variant == 7 ? 1 : cfg.groups);
+    const int64_t rows = ((g->P + per_block - 1) / per_block + 7) / 8;
+    const double streamed = 1.0 - kKeepBytes / (2.0 * (double)g->total() * 64.0 * sizeof(T));
+    return SweepPass{back, (uint32_t)(streamed * (double)rows)};
+}
+
 // One sweep src -> dst.  For variant 7, `mode` says which orders the two
 // buffers hold: 0 package-id order -> worklist order, 1 worklist -> worklist
 // (the autotuner times this one), 2 worklist -> package-id order.
 template <typename T>
 static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *dst, hipStream_t st,
-                                        const SweepConfig &cfg, int mode = 1) {
+                                        const SweepConfig &cfg, int mode = 1, bool back = false) {
     if (g->P == 0) return SGRID_OK;
     const int64_t per_block = 16 * (int64_t)cfg.groups;
     const int64_t nb = (g->P + per_block - 1) / per_block;
     const T h2 = (T)(g->h * g->h), inv_h = (T)(1.0 / g->h), dt = (T)(0.5 * g->h);
     const dim3 grid((unsigned)nb), block(256);
     // streaming stores when the two field buffers exceed the last-level cache
+    // (variants 0, 3 and 7: but for the last rows, see sweep_pass)
     const bool nt = 2.0 * (double)g->total() * 64.0 * sizeof(T) > kLastLevelCacheBytes;
     const bool narrow = narrow_offsets<T>(g);
+    const SweepPass pass = sweep_pass<T>(g, cfg, nt, back);
     if (cfg.variant == 7) {
         if (narrow)
-            launch_morton<T, uint32_t>(g, src, dst, mode, nt, st);
+            launch_morton<T, uint32_t>(g, src, dst, mode, pass, st);
         else
-            launch_morton<T, int64_t>(g, src, dst, mode, nt, st);
+            launch_morton<T, int64_t>(g, src, dst, mode, pass, st);
     } else if (cfg.variant == 6) {
         const int64_t n_sets = (g->P + 3) / 4;
         const int64_t nbp = std::min<int64_t>((int64_t)cu_count() * cfg.groups, (n_sets + 3) / 4);
@@ -911,9 +948,9 @@ static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *ds
                            g->P, ng, h2, inv_h, dt);
     } else if (cfg.variant == 3) {
         if (narrow)
-            launch_work<T, uint32_t>(g, src, dst, cfg.groups, nt, st);
+            launch_work<T, uint32_t>(g, src, dst, cfg.groups, pass, st);
         else
-            launch_work<T, int64_t>(g, src, dst, cfg.groups, nt, st);
+            launch_work<T, int64_t>(g, src, dst, cfg.groups, pass, st);
     } else if (cfg.variant == 2) {
         const int64_t n_sets = (g->P + 3) / 4;
         const int64_t nbp = std::min<int64_t>((int64_t)cu_count() * cfg.groups, (n_sets + 3) / 4);
@@ -924,9 +961,9 @@ static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *ds
                            inv_h, dt);
     } else {
         if (narrow)
-            launch_dpp_range<T, uint32_t>(g, src, dst, 2, 2 + g->P, cfg.groups, nt, st);
+            launch_dpp_range<T, uint32_t>(g, src, dst, 2, 2 + g->P, cfg.groups, pass, st);
         else
-            launch_dpp_range<T, int64_t>(g, src, dst, 2, 2 + g->P, cfg.groups, nt, st);
+            launch_dpp_range<T, int64_t>(g, src, dst, 2, 2 + g->P, cfg.groups, pass, st);
     }
     SG_CHECK_LAUNCH("reinit sweep");
     return SGRID_OK;
@@ -945,7 +982,7 @@ sgrid_status reinit_impl(const sgrid_grid *g, T *phi, T *scratch, int32_t n_iter
     if (cfg.variant == 7 && n_iter == 1) one.variant = 3;
     for (int32_t it = 0; it < n_iter; ++it) {
         const int mode = it == 0 ? 0 : (it == n_iter - 1 ? 2 : 1);
-        sgrid_status s = launch_reinit_sweep<T>(g, a, b, st, one, mode);
+        sgrid_status s = launch_reinit_sweep<T>(g, a, b, st, one, mode, (it & 1) != 0);
         if (s != SGRID_OK) return s;
         T *t = a;
         a = b;
