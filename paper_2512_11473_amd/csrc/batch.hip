@@ -16,7 +16,7 @@
 // grids that fit it, each through all its iterations before the next (the grids
 // do not depend on each other), so that a sweep finds the rows that the one
 // before it wrote.  24 random unions of up to 512^3 points (594 k packages, 318
-// MB with the worklist) take 54 us per iteration over all in two segments,
+// MB with the worklist) take 53 us per iteration over all in two segments,
 // from 78 in one.
 //
 // The per-point update is the same function as the single-grid sweep with the
