@@ -14,6 +14,7 @@
 // 16-lane DPP row).  The LDS-staged variant writes the same rows and halos
 // into a per-package tile in LDS and reads the neighbours back from there.
 #include <atomic>
+#include <type_traits>
 
 #include "common.hpp"
 #include "fraction.hpp"
@@ -208,12 +209,12 @@ __device__ __forceinline__ I sweep_block(I n_blocks, bool back) {
 // Reinitialisation sweep over the packages [first, end) (all of them: [2,
 // 2 + P)), DPP exchange variant.  A wavefront handles G consecutive sets of
 // four packages and issues all their loads before computing any of them.
-template <typename T, int G, typename I>
+template <typename T, int G, typename I, bool BIG>
 __global__ __launch_bounds__(256) void reinit_dpp_kernel(const T *__restrict__ src, T *__restrict__ dst,
                                                          const uint32_t *__restrict__ face, I first, I end,
                                                          I n_blocks, T h2, T inv_h, T dt, SweepPass pass) {
-    const I b = sweep_block(n_blocks, pass.back);
-    const bool nt = blockIdx.x / 8 < pass.stream_rows;
+    const I b = BIG ? sweep_block(n_blocks, pass.back) : block_of(n_blocks);
+    const bool nt = BIG && blockIdx.x / 8 < pass.stream_rows;
     const int lane = threadIdx.x & 63;
     const int r = lane & 15;
     const I p0 = first + (b * 4 + (threadIdx.x >> 6)) * (4 * G) + (lane >> 4);
@@ -235,12 +236,12 @@ __global__ __launch_bounds__(256) void reinit_dpp_kernel(const T *__restrict__ s
 // brings into the caches.  The face rows are read in worklist order (wface:
 // six neighbours and the package's own id), one coalesced 32-byte row per
 // package.  G sets of four packages per wavefront.
-template <typename T, int G, typename I>
+template <typename T, int G, typename I, bool BIG>
 __global__ __launch_bounds__(256) void reinit_work_kernel(const T *__restrict__ src, T *__restrict__ dst,
                                                           const uint32_t *__restrict__ wface, I P, I n_blocks, T h2,
                                                           T inv_h, T dt, SweepPass pass) {
-    const I b = sweep_block(n_blocks, pass.back);
-    const bool nt = blockIdx.x / 8 < pass.stream_rows;
+    const I b = BIG ? sweep_block(n_blocks, pass.back) : block_of(n_blocks);
+    const bool nt = BIG && blockIdx.x / 8 < pass.stream_rows;
     const int lane = threadIdx.x & 63;
     const int r = lane & 15;
     const I e0 = (b * 4 + (threadIdx.x >> 6)) * (4 * G) + (lane >> 4);
@@ -273,13 +274,13 @@ __global__ __launch_bounds__(256) void reinit_work_kernel(const T *__restrict__ 
 // writes the copy (MODE 0); the following ones go copy to copy (MODE 1); the
 // last writes package-id order again (MODE 2).  The values are those of every
 // other variant.
-template <typename T, int MODE, typename I>
+template <typename T, int MODE, typename I, bool BIG>
 __global__ __launch_bounds__(256) void reinit_morton_kernel(const T *__restrict__ src, T *__restrict__ dst,
                                                             const uint32_t *__restrict__ wface,
                                                             const uint32_t *__restrict__ mface, I P, I n_blocks, T h2,
                                                             T inv_h, T dt, SweepPass pass) {
-    const I b = sweep_block(n_blocks, pass.back);
-    const bool nt = blockIdx.x / 8 < pass.stream_rows;
+    const I b = BIG ? sweep_block(n_blocks, pass.back) : block_of(n_blocks);
+    const bool nt = BIG && blockIdx.x / 8 < pass.stream_rows;
     const int r = threadIdx.x & 15;
     const I e = b * 16 + (threadIdx.x >> 4);
     if (e >= P) return;   // whole 16-lane rows (one package each) leave together
@@ -837,7 +838,7 @@ static bool narrow_offsets(const sgrid_grid *g) {
     return (double)g->total() * 64.0 * sizeof(T) <= 4294967296.0;
 }
 
-template <typename T, typename I>
+template <typename T, typename I, bool BIG>
 static void launch_dpp_range(const sgrid_grid *g, const T *src, T *dst, int64_t first, int64_t end, int groups,
                              SweepPass pass, hipStream_t st) {
     const int64_t per_block = 16 * (int64_t)groups;
@@ -848,15 +849,15 @@ static void launch_dpp_range(const sgrid_grid *g, const T *src, T *dst, int64_t 
         hipLaunchKernelGGL(kernel, grid, block, 0, st, src, dst, g->face, (I)first, (I)end, (I)nb, h2, inv_h, dt, pass);
     };
     switch (groups) {
-        case 1: launch(reinit_dpp_kernel<T, 1, I>); break;
-        case 2: launch(reinit_dpp_kernel<T, 2, I>); break;
-        case 3: launch(reinit_dpp_kernel<T, 3, I>); break;
-        case 4: launch(reinit_dpp_kernel<T, 4, I>); break;
-        default: launch(reinit_dpp_kernel<T, 8, I>); break;
+        case 1: launch(reinit_dpp_kernel<T, 1, I, BIG>); break;
+        case 2: launch(reinit_dpp_kernel<T, 2, I, BIG>); break;
+        case 3: launch(reinit_dpp_kernel<T, 3, I, BIG>); break;
+        case 4: launch(reinit_dpp_kernel<T, 4, I, BIG>); break;
+        default: launch(reinit_dpp_kernel<T, 8, I, BIG>); break;
     }
 }
 
-template <typename T, typename I>
+template <typename T, typename I, bool BIG>
 static void launch_work(const sgrid_grid *g, const T *src, T *dst, int groups, SweepPass pass, hipStream_t st) {
     const int64_t per_block = 16 * (int64_t)groups;
     const int64_t nb = (g->P + per_block - 1) / per_block;
@@ -866,15 +867,15 @@ static void launch_work(const sgrid_grid *g, const T *src, T *dst, int groups, S
                            dt, pass);
     };
     switch (groups) {
-        case 1: launch(reinit_work_kernel<T, 1, I>); break;
-        case 2: launch(reinit_work_kernel<T, 2, I>); break;
-        case 3: launch(reinit_work_kernel<T, 3, I>); break;
-        case 4: launch(reinit_work_kernel<T, 4, I>); break;
-        default: launch(reinit_work_kernel<T, 8, I>); break;
+        case 1: launch(reinit_work_kernel<T, 1, I, BIG>); break;
+        case 2: launch(reinit_work_kernel<T, 2, I, BIG>); break;
+        case 3: launch(reinit_work_kernel<T, 3, I, BIG>); break;
+        case 4: launch(reinit_work_kernel<T, 4, I, BIG>); break;
+        default: launch(reinit_work_kernel<T, 8, I, BIG>); break;
     }
 }
 
-template <typename T, typename I>
+template <typename T, typename I, bool BIG>
 static void launch_morton(const sgrid_grid *g, const T *src, T *dst, int mode, SweepPass pass, hipStream_t st) {
     const int64_t nb = (g->P + 15) / 16;
     const T h2 = (T)(g->h * g->h), inv_h = (T)(1.0 / g->h), dt = (T)(0.5 * g->h);
@@ -883,9 +884,9 @@ static void launch_morton(const sgrid_grid *g, const T *src, T *dst, int mode, S
                            h2, inv_h, dt, pass);
     };
     switch (mode) {
-        case 0: launch(reinit_morton_kernel<T, 0, I>); break;
-        case 1: launch(reinit_morton_kernel<T, 1, I>); break;
-        default: launch(reinit_morton_kernel<T, 2, I>); break;
+        case 0: launch(reinit_morton_kernel<T, 0, I, BIG>); break;
+        case 1: launch(reinit_morton_kernel<T, 1, I, BIG>); break;
+        default: launch(reinit_morton_kernel<T, 2, I, BIG>); break;
     }
 }
 
@@ -922,13 +923,21 @@ static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *ds
     // streaming stores when the two field buffers exceed the last-level cache
     // (variants 0, 3 and 7: but for the last rows, see sweep_pass)
     const bool nt = 2.0 * (double)g->total() * 64.0 * sizeof(T) > kLastLevelCacheBytes;
-    const bool narrow = narrow_offsets<T>(g);
     const SweepPass pass = sweep_pass<T>(g, cfg, nt, back);
-    if (cfg.variant == 7) {
-        if (narrow)
-            launch_morton<T, uint32_t>(g, src, dst, mode, pass, st);
+    // (the offsets of a field whose buffers the cache holds are narrow; a sweep of
+    // one is a few microseconds, and 3 % of that with the pass decided in the kernel)
+    auto sized = [&](auto launch) {
+        if (!nt)
+            launch(uint32_t(), std::false_type());
+        else if (narrow_offsets<T>(g))
+            launch(uint32_t(), std::true_type());
         else
-            launch_morton<T, int64_t>(g, src, dst, mode, pass, st);
+            launch(int64_t(), std::true_type());
+    };
+    if (cfg.variant == 7) {
+        sized([&](auto index, auto big) {
+            launch_morton<T, decltype(index), decltype(big)::value>(g, src, dst, mode, pass, st);
+        });
     } else if (cfg.variant == 6) {
         const int64_t n_sets = (g->P + 3) / 4;
         const int64_t nbp = std::min<int64_t>((int64_t)cu_count() * cfg.groups, (n_sets + 3) / 4);
@@ -947,10 +956,9 @@ static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *ds
         hipLaunchKernelGGL(reinit_share_kernel<T>, dim3((unsigned)ng), dim3(1024), 0, st, src, dst, g->work, g->sface,
                            g->P, ng, h2, inv_h, dt);
     } else if (cfg.variant == 3) {
-        if (narrow)
-            launch_work<T, uint32_t>(g, src, dst, cfg.groups, pass, st);
-        else
-            launch_work<T, int64_t>(g, src, dst, cfg.groups, pass, st);
+        sized([&](auto index, auto big) {
+            launch_work<T, decltype(index), decltype(big)::value>(g, src, dst, cfg.groups, pass, st);
+        });
     } else if (cfg.variant == 2) {
         const int64_t n_sets = (g->P + 3) / 4;
         const int64_t nbp = std::min<int64_t>((int64_t)cu_count() * cfg.groups, (n_sets + 3) / 4);
@@ -960,10 +968,9 @@ static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *ds
         hipLaunchKernelGGL(reinit_lds_kernel<T>, grid, block, 0, st, src, dst, g->face, g->P, nb, cfg.groups, h2,
                            inv_h, dt);
     } else {
-        if (narrow)
-            launch_dpp_range<T, uint32_t>(g, src, dst, 2, 2 + g->P, cfg.groups, pass, st);
-        else
-            launch_dpp_range<T, int64_t>(g, src, dst, 2, 2 + g->P, cfg.groups, pass, st);
+        sized([&](auto index, auto big) {
+            launch_dpp_range<T, decltype(index), decltype(big)::value>(g, src, dst, 2, 2 + g->P, cfg.groups, pass, st);
+        });
     }
     SG_CHECK_LAUNCH("reinit sweep");
     return SGRID_OK;
