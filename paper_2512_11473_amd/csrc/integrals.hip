@@ -96,7 +96,7 @@ __device__ __forceinline__ bool window_fractions(const float *f, int lane, float
 // 352 vector instructions a package took), and a package's rows are requested
 // before the one before it is evaluated.  Bound by vector issue (288
 // instructions a package, 71 % of the issue slots): the field of the torus at
-// 1024^3 points (580 k packages) takes 300 us, from 390 with one package per
+// 1024^3 points (452 k packages) takes 300 us, from 390 with one package per
 // wavefront, a window point per lane and step, and the taps of one-sided
 // windows summed; workgroups in XCD-aware order took 337 instead of 330.
 // A plane stride that frees the tests' reads of bank conflicts cost registers
