@@ -896,13 +896,15 @@ static void launch_morton(const sgrid_grid *g, const T *src, T *dst, int mode, S
 // sweep are stored without the streaming hint, so that they are there.  (Keeping
 // more pushes out what is kept: the shell at 1024^3 points takes 71.4 us a sweep
 // with 100 MiB, 71.9 with 150, 73.7 with 250 and 78 with 300; the torus at 1200^3
-// 74.1, 72.4, 78.3 and 81.4.)  All forward and all streaming before: 72.6 and 75.6
+// 74.1, 72.4, 78.3 and 81.4.)  Not by a call's last sweep: a single FP64 sweep of the
+// shell at 800^3 with the copy after it took 174 us instead of 152.  All forward and all streaming before: 72.6 and 75.6
 // us; the torus at 2048^3 218 us then and 214 now, at 900^3 in FP64 103 and 95.
 constexpr double kKeepBytes = 144.0 * 1024 * 1024;
 
 template <typename T>
-static SweepPass sweep_pass(const sgrid_grid *g, const SweepConfig &cfg, bool exceeds_cache, bool back) {
+static SweepPass sweep_pass(const sgrid_grid *g, const SweepConfig &cfg, bool exceeds_cache, bool back, bool last) {
     if (!exceeds_cache) return SweepPass{false, 0u};
+    if (last) return SweepPass{back, ~0u};
     const int64_t per_block = 16 * (int64_t)(cfg.variant == 7 ? 1 : cfg.groups);
     const int64_t rows = ((g->P + per_block - 1) / per_block + 7) / 8;
     const double streamed = 1.0 - kKeepBytes / (2.0 * (double)g->total() * 64.0 * sizeof(T));
@@ -914,7 +916,8 @@ static SweepPass sweep_pass(const sgrid_grid *g, const SweepConfig &cfg, bool ex
 // (the autotuner times this one), 2 worklist -> package-id order.
 template <typename T>
 static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *dst, hipStream_t st,
-                                        const SweepConfig &cfg, int mode = 1, bool back = false) {
+                                        const SweepConfig &cfg, int mode = 1, bool back = false,
+                                        bool last = false) {
     if (g->P == 0) return SGRID_OK;
     const int64_t per_block = 16 * (int64_t)cfg.groups;
     const int64_t nb = (g->P + per_block - 1) / per_block;
@@ -923,7 +926,7 @@ static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *ds
     // streaming stores when the two field buffers exceed the last-level cache
     // (variants 0, 3 and 7: but for the last rows, see sweep_pass)
     const bool nt = 2.0 * (double)g->total() * 64.0 * sizeof(T) > kLastLevelCacheBytes;
-    const SweepPass pass = sweep_pass<T>(g, cfg, nt, back);
+    const SweepPass pass = sweep_pass<T>(g, cfg, nt, back, last);
     // (the offsets of a field whose buffers the cache holds are narrow; a sweep of
     // one is a few microseconds, and 3 % of that with the pass decided in the kernel)
     auto sized = [&](auto launch) {
@@ -989,7 +992,7 @@ sgrid_status reinit_impl(const sgrid_grid *g, T *phi, T *scratch, int32_t n_iter
     if (cfg.variant == 7 && n_iter == 1) one.variant = 3;
     for (int32_t it = 0; it < n_iter; ++it) {
         const int mode = it == 0 ? 0 : (it == n_iter - 1 ? 2 : 1);
-        sgrid_status s = launch_reinit_sweep<T>(g, a, b, st, one, mode, (it & 1) != 0);
+        sgrid_status s = launch_reinit_sweep<T>(g, a, b, st, one, mode, (it & 1) != 0, it == n_iter - 1);
         if (s != SGRID_OK) return s;
         T *t = a;
         a = b;
@@ -1012,7 +1015,10 @@ sgrid_status launch_cut_fractions(const sgrid_grid *g, const float *phi, float *
         set_error("too many packages for one launch");
         return SGRID_E_INVALID;
     }
-    const bool work = stencil_in_worklist_order(g, 4);
+    // by the default's rule in id order: Morton order takes 2 us off 94 to 177 us of
+    // both passes (torus at 768^3 to 1024^3 points), but adds 2 to the prism's 124 at
+    // 820^3
+    const bool work = current_sweep_config().variant != 0 && stencil_in_worklist_order(g, 4);
     const bool nt_store = 2.0 * (double)nt * 64.0 * 4.0 > kLastLevelCacheBytes;
     const float inv_h = (float)(1.0 / g->h), inv_2h = (float)(0.5 / g->h);
     if (work)
@@ -1140,12 +1146,16 @@ static sgrid_status gradient_entry(const sgrid_grid *g, sgrid_dtype dtype, const
     hipStream_t st = sg_stream(stream);
     const int64_t nt = g->total();
     const int64_t nb = (nt + 15) / 16;
-    // by the default's rule only the FP32 SoA gradient (torus at 2048^3: 485 us
-    // in id order, 459 in Morton order): the FP64 one is slower in Morton order
-    // (at 221 MiB a field 150 and 184 us), the packed one now faster, now slower
+    // by default only the FP32 SoA gradient of a field of kGradientBytes and more:
+    // torus at 1024^3 points (110 MiB) 77.2 us in id order and 70.5 in Morton order,
+    // shell at 1024^3 (142 MiB) 157 and 150, torus at 2048^3 485 and 459, but sphere
+    // at 900^3 (70 MiB) 42.4 and 45.4, prism at 820^3 (79 MiB) 48.9 and 50.8; the FP64
+    // one is slower in Morton order (at 221 MiB a field 150 and 184 us), the packed one
+    // now faster, now slower
+    constexpr double kGradientBytes = 96.0 * 1024 * 1024;
     const bool tuned = sgrid::current_sweep_config().variant != 0;
-    const bool work = (tuned || (!PACKED && dtype == SGRID_F32)) &&
-                      sgrid::stencil_in_worklist_order(g, dtype == SGRID_F32 ? 4 : 8);
+    const bool large = !PACKED && dtype == SGRID_F32 && (double)nt * 256.0 >= kGradientBytes;
+    const bool work = (tuned || large) && sgrid::stencil_in_worklist_order(g, dtype == SGRID_F32 ? 4 : 8);
     // streaming stores when phi and the output together exceed the last-level
     // cache; not for the FP64 packed layout, whose four stores per lane each
     // fill only parts of lines (the cache merges them, streaming writes would

@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("N,dtype,large", [(400, torch.float32, False), (560, torch.float32, True),
-                                           (864, torch.float32, True), (608, torch.float64, True)])
+                                           (864, torch.float32, True), (1120, torch.float32, True),
+                                           (608, torch.float64, True)])
 def test_default_order_same_bits(N, dtype, large):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
