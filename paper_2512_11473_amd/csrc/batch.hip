@@ -45,17 +45,28 @@ __device__ __forceinline__ Row4<float> ld_row(const float *__restrict__ p) {
     const float4 a = *reinterpret_cast<const float4 *>(p);
     return Row4<float>{{a.x, a.y, a.z, a.w}};
 }
-// nt: the streaming (non-temporal) hint, for ping-pong buffers larger than the
-// last-level cache (the written rows would only push out lines the running
-// sweep still reads)
+// How a sweep stores its rows.  Streamed (non-temporal hint): ping-pong buffers
+// larger than the last-level cache, where the written rows would only push out
+// lines the running sweep still reads.  Through: written through the L2, by sweeps
+// of one set per wavefront over kThroughPackages and more (23 unions, 56 k
+// packages: 9.6 -> 8.9 us an iteration).  A wavefront that goes on to its next set
+// waits for such a store with the set's loads (one workgroup per CU: 16.9 and
+// 19.5 us, four: 10.4 and 11.1), and a small sweep leaves little to write back (5.8 k
+// packages: 3.76 and 3.86 us): plain stores there.
+enum class Store : int { kPlain, kThrough, kStreamed };
+constexpr int64_t kThroughPackages = 16384;
+
 template <typename I>
-__device__ __forceinline__ void st_row(float *__restrict__ base, I off, const Row4<float> &r, bool nt) {
+__device__ __forceinline__ void st_row(float *__restrict__ base, I off, const Row4<float> &r, Store mode) {
     typedef float f4v __attribute__((ext_vector_type(4)));
     const f4v v = {r.v[0], r.v[1], r.v[2], r.v[3]};
-    if (nt)
-        __builtin_nontemporal_store(v, reinterpret_cast<f4v *>(at_offset(base, off)));
-    else
+    f4v *p = reinterpret_cast<f4v *>(at_offset(base, off));
+    if (mode == Store::kStreamed)
+        __builtin_nontemporal_store(v, p);
+    else if (mode == Store::kThrough)
         store_through(base, off, v);
+    else
+        *p = v;
 }
 
 struct Halo {
@@ -103,7 +114,7 @@ template <typename I>   // byte offsets in the concatenated field
 __global__ __launch_bounds__(256) void batch_dpp_kernel(const float *__restrict__ src, float *__restrict__ dst,
                                                         const uint32_t *__restrict__ wrow, I n_work,
                                                         const sgrid::SweepParams<float> *__restrict__ params,
-                                                        I n_blocks, I spw, bool nt) {
+                                                        I n_blocks, I spw, Store mode) {
     const I b = block_of(n_blocks);
     const int lane = threadIdx.x & 63, r = lane & 15;
     const I wave = b * 4 + (threadIdx.x >> 6);
@@ -117,7 +128,7 @@ __global__ __launch_bounds__(256) void batch_dpp_kernel(const float *__restrict_
         if (live) batch_loads(src, wrow, e, r, l, g, shape);
         const sgrid::SweepParams<float> sp = params[shape];
         const Row4<float> o = update_row_dpp(l, sp);
-        if (live) st_row(dst, row_offset<float, I>(g, r * 4), o, nt);
+        if (live) st_row(dst, row_offset<float, I>(g, r * 4), o, mode);
     }
 }
 
@@ -125,7 +136,7 @@ __global__ __launch_bounds__(256) void batch_dpp_kernel(const float *__restrict_
 __global__ __launch_bounds__(256) void batch_lds_kernel(const float *__restrict__ src, float *__restrict__ dst,
                                                         const uint32_t *__restrict__ wrow, int64_t n_work,
                                                         const sgrid::SweepParams<float> *__restrict__ params,
-                                                        int64_t n_blocks, int64_t spw, bool nt) {
+                                                        int64_t n_blocks, int64_t spw, Store mode) {
     __shared__ float tile[16][216];
     const int64_t b = xcd_block(blockIdx.x, n_blocks);
     const int lane = threadIdx.x & 63, r = lane & 15, j = r & 3, k = r >> 2;
@@ -165,7 +176,7 @@ __global__ __launch_bounds__(256) void batch_lds_kernel(const float *__restrict_
             for (int i = 0; i < 4; ++i)
                 o.v[i] = sgrid::upwind_update(t[at(i, j, k)], t[at(i - 1, j, k)], t[at(i + 1, j, k)], t[at(i, j - 1, k)],
                                 t[at(i, j + 1, k)], t[at(i, j, k - 1)], t[at(i, j, k + 1)], sp.h2, sp.inv_h, sp.dt);
-            st_row(dst, row_offset<float, int64_t>(g, r * 4), o, nt);
+            st_row(dst, row_offset<float, int64_t>(g, r * 4), o, mode);
         }
         __syncthreads();
     }
@@ -207,7 +218,10 @@ struct sgrid_batch {
     // worklist ranges of whole grids, each swept through all its iterations
     struct Segment { int64_t first, count; };
     std::vector<Segment> segments;
-    int32_t variant = 0, blocks_per_cu = 4;   // tuned configuration
+    // the configuration; until it is set or tuned, one wavefront per four packages
+    // (against four workgroups per CU: 23 unions up to 128^3 9.0 and 10.5 us an
+    // iteration, 64 up to 512^3 107 and 129)
+    int32_t variant = 0, blocks_per_cu = 0;
     bool tuned = false;
     // captured iteration loop
     hipGraphExec_t exec = nullptr;
@@ -255,17 +269,19 @@ sgrid_status launch_batch_sweep(const sgrid_batch *b, const sgrid_batch::Segment
     int64_t nb = bpc > 0 ? (int64_t)sgrid::cu_count() * bpc : (n_sets + 3) / 4;
     const int64_t spw = (n_sets + nb * 4 - 1) / (nb * 4);
     nb = (n_sets + spw * 4 - 1) / (spw * 4);
-    const bool nt = 2.0 * (double)seg.count * 64.0 * sizeof(float) > kCacheBytes;
+    const bool streamed = 2.0 * (double)seg.count * 64.0 * sizeof(float) > kCacheBytes;
+    const Store mode = streamed ? Store::kStreamed
+                                : (spw == 1 && seg.count >= kThroughPackages ? Store::kThrough : Store::kPlain);
     const uint32_t *wrow = b->wrow + seg.first * 8;
     if (variant == 1)
         hipLaunchKernelGGL(batch_lds_kernel, dim3((unsigned)nb), dim3(256), 0, st, src, dst, wrow, seg.count,
-                           b->params, nb, spw, nt);
+                           b->params, nb, spw, mode);
     else if ((double)b->n_total * 256.0 <= 4294967296.0)   // 32-bit byte offsets
         hipLaunchKernelGGL(batch_dpp_kernel<uint32_t>, dim3((unsigned)nb), dim3(256), 0, st, src, dst, wrow,
-                           (uint32_t)seg.count, b->params, (uint32_t)nb, (uint32_t)spw, nt);
+                           (uint32_t)seg.count, b->params, (uint32_t)nb, (uint32_t)spw, mode);
     else
         hipLaunchKernelGGL(batch_dpp_kernel<int64_t>, dim3((unsigned)nb), dim3(256), 0, st, src, dst, wrow, seg.count,
-                           b->params, nb, spw, nt);
+                           b->params, nb, spw, mode);
     SG_CHECK_LAUNCH("batch sweep");
     return SGRID_OK;
 }
