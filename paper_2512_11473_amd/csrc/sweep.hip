@@ -93,6 +93,20 @@ __device__ __forceinline__ void store_row(T *__restrict__ p, const Row<T> &r, bo
         store_row(p, r);
 }
 
+// For kernels that keep a set's stores in flight with the next set's loads, or whose
+// workgroups meet at a barrier: a wavefront waits for rows written through the L2
+// with those loads, so with few wavefronts per CU, or little to write back, plain
+// stores are faster (variant 2, prism512: 28.4 us a sweep at one workgroup per CU
+// and 30.0 written through, but 15.6 and 14.4 at four; variant 4, torus at 128^3: 4.4
+// and 4.7).
+template <typename T>
+__device__ __forceinline__ void store_row(T *__restrict__ p, const Row<T> &r, bool nt, bool through) {
+    if (nt || through)
+        store_row(p, r, nt);
+    else
+        store_row_plain(p, r);
+}
+
 // A row stored at a byte offset.
 template <typename T, typename I>
 __device__ __forceinline__ void store_row_at(T *__restrict__ base, I off, const Row<T> &r, bool nt) {
@@ -366,7 +380,7 @@ template <typename T>
 __global__ __launch_bounds__(1024) void reinit_share_kernel(const T *__restrict__ src, T *__restrict__ dst,
                                                             const uint32_t *__restrict__ work,
                                                             const uint32_t *__restrict__ sface, int64_t P,
-                                                            int64_t n_blocks, T h2, T inv_h, T dt) {
+                                                            int64_t n_blocks, T h2, T inv_h, T dt, bool through) {
     __shared__ T tile[kGroup][64];
     const int64_t b = xcd_block(blockIdx.x, n_blocks);
     const int lane = threadIdx.x & 63;
@@ -395,7 +409,7 @@ __global__ __launch_bounds__(1024) void reinit_share_kernel(const T *__restrict_
     if (j == 0 || j == 3) l.yh = halo_row(src, tile, j == 0 ? f0.z : f0.w, (j == 0 ? 3 + 4 * k : 4 * k) * 4);
     if (k == 0 || k == 3) l.zh = halo_row(src, tile, k == 0 ? f1.x : f1.y, (k == 0 ? j + 12 : j) * 4);
     const Stencil<T> s = assemble(l);
-    store_row(dst + p * 64 + r * 4, reinit_row(s, h2, inv_h, dt));
+    store_row(dst + p * 64 + r * 4, reinit_row(s, h2, inv_h, dt), false, through);
 }
 
 // Persistent worklist variant: a fixed grid of `groups` workgroups per CU
@@ -414,7 +428,7 @@ __global__ __launch_bounds__(1024) void reinit_share_kernel(const T *__restrict_
 template <typename T>
 __global__ __launch_bounds__(256) void reinit_pipe_kernel(const T *__restrict__ src, T *__restrict__ dst,
                                                           const uint32_t *__restrict__ wface, int64_t P,
-                                                          int64_t n_blocks, T h2, T inv_h, T dt, bool nt) {
+                                                          int64_t n_blocks, T h2, T inv_h, T dt, bool nt, bool through) {
     const int64_t b = xcd_block(blockIdx.x, n_blocks);
     const int lane = threadIdx.x & 63;
     const int r = lane & 15;
@@ -440,7 +454,7 @@ __global__ __launch_bounds__(256) void reinit_pipe_kernel(const T *__restrict__ 
         Loads<T> l;
         issue_data<T, int64_t>(src, (uint32_t)p, r, c0, cz, l);
         const Stencil<T> st = assemble(l);
-        store_row(dst + p * 64 + r * 4, reinit_row(st, h2, inv_h, dt), nt);
+        store_row(dst + p * 64 + r * 4, reinit_row(st, h2, inv_h, dt), nt, through);
     }
 }
 
@@ -451,7 +465,7 @@ __global__ __launch_bounds__(256) void reinit_pipe_kernel(const T *__restrict__ 
 template <typename T>
 __global__ __launch_bounds__(256) void reinit_pipe_lin_kernel(const T *__restrict__ src, T *__restrict__ dst,
                                                               const uint32_t *__restrict__ face, int64_t P,
-                                                              int64_t n_blocks, T h2, T inv_h, T dt) {
+                                                              int64_t n_blocks, T h2, T inv_h, T dt, bool through) {
     const int64_t b = xcd_block(blockIdx.x, n_blocks);
     const int lane = threadIdx.x & 63;
     const int r = lane & 15;
@@ -479,7 +493,7 @@ __global__ __launch_bounds__(256) void reinit_pipe_lin_kernel(const T *__restric
         own = load_row(src + p * 64 + r * 4);
         issue_halos<T, int64_t>(src, r, c0, c1, l);
         const Stencil<T> st = assemble(l);
-        store_row(dst + pc * 64 + r * 4, reinit_row(st, h2, inv_h, dt));
+        store_row(dst + pc * 64 + r * 4, reinit_row(st, h2, inv_h, dt), false, through);
     }
 }
 
@@ -522,7 +536,10 @@ __global__ __launch_bounds__(256) void reinit_lds_kernel(const T *__restrict__ s
             for (int i = 0; i < 4; ++i)
                 o.v[i] = upwind_update(t[at(i, j, k)], t[at(i - 1, j, k)], t[at(i + 1, j, k)], t[at(i, j - 1, k)],
                                        t[at(i, j + 1, k)], t[at(i, j, k - 1)], t[at(i, j, k + 1)], h2, inv_h, dt);
-            store_row(dst + p * 64 + r * 4, o);
+            if (groups > 1)
+                store_row_plain(dst + p * 64 + r * 4, o);
+            else
+                store_row(dst + p * 64 + r * 4, o);
         }
         __syncthreads();
     }
@@ -897,14 +914,15 @@ static void launch_morton(const sgrid_grid *g, const T *src, T *dst, int mode, S
 // more pushes out what is kept: the shell at 1024^3 points takes 71.4 us a sweep
 // with 100 MiB, 71.9 with 150, 73.7 with 250 and 78 with 300; the torus at 1200^3
 // 74.1, 72.4, 78.3 and 81.4.)  Not by a call's last sweep: a single FP64 sweep of the
-// shell at 800^3 with the copy after it took 174 us instead of 152.  All forward and all streaming before: 72.6 and 75.6
+// shell at 800^3 with the copy after it took 174 us instead of 152; nor in id order
+// (variant 0, two sets per wavefront, torus at 1200^3: 86.4 and 88.5).  All forward and all streaming before: 72.6 and 75.6
 // us; the torus at 2048^3 218 us then and 214 now, at 900^3 in FP64 103 and 95.
 constexpr double kKeepBytes = 144.0 * 1024 * 1024;
 
 template <typename T>
 static SweepPass sweep_pass(const sgrid_grid *g, const SweepConfig &cfg, bool exceeds_cache, bool back, bool last) {
     if (!exceeds_cache) return SweepPass{false, 0u};
-    if (last) return SweepPass{back, ~0u};
+    if (last || cfg.variant == 0) return SweepPass{back && cfg.variant != 0, ~0u};
     const int64_t per_block = 16 * (int64_t)(cfg.variant == 7 ? 1 : cfg.groups);
     const int64_t rows = ((g->P + per_block - 1) / per_block + 7) / 8;
     const double streamed = 1.0 - kKeepBytes / (2.0 * (double)g->total() * 64.0 * sizeof(T));
@@ -945,7 +963,7 @@ static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *ds
         const int64_t n_sets = (g->P + 3) / 4;
         const int64_t nbp = std::min<int64_t>((int64_t)cu_count() * cfg.groups, (n_sets + 3) / 4);
         hipLaunchKernelGGL(reinit_pipe_lin_kernel<T>, dim3((unsigned)nbp), block, 0, st, src, dst, g->face, g->P, nbp,
-                           h2, inv_h, dt);
+                           h2, inv_h, dt, cfg.groups >= 4);
     } else if (cfg.variant == 5) {
         switch (cfg.groups) {
             case 1: hipLaunchKernelGGL((reinit_rows_kernel<T, 1>), grid, block, 0, st, src, dst, g->face, g->P, nb, h2, inv_h, dt, nt); break;
@@ -957,7 +975,7 @@ static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *ds
     } else if (cfg.variant == 4) {
         const int64_t ng = (g->P + kGroup - 1) / kGroup;
         hipLaunchKernelGGL(reinit_share_kernel<T>, dim3((unsigned)ng), dim3(1024), 0, st, src, dst, g->work, g->sface,
-                           g->P, ng, h2, inv_h, dt);
+                           g->P, ng, h2, inv_h, dt, g->P >= 16384);
     } else if (cfg.variant == 3) {
         sized([&](auto index, auto big) {
             launch_work<T, decltype(index), decltype(big)::value>(g, src, dst, cfg.groups, pass, st);
@@ -966,7 +984,7 @@ static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *ds
         const int64_t n_sets = (g->P + 3) / 4;
         const int64_t nbp = std::min<int64_t>((int64_t)cu_count() * cfg.groups, (n_sets + 3) / 4);
         hipLaunchKernelGGL(reinit_pipe_kernel<T>, dim3((unsigned)nbp), block, 0, st, src, dst, g->wface, g->P, nbp,
-                           h2, inv_h, dt, nt);
+                           h2, inv_h, dt, nt, cfg.groups >= 4);
     } else if (cfg.variant == 1) {
         hipLaunchKernelGGL(reinit_lds_kernel<T>, grid, block, 0, st, src, dst, g->face, g->P, nb, cfg.groups, h2,
                            inv_h, dt);
