@@ -474,8 +474,7 @@ sgrid_status sgrid_compute_laplacian(const sgrid_grid *grid, sgrid_dtype dtype, 
  * 4 and 7.  With variant 2, 3, 4 or 7 the gradient and Laplacian passes also
  * visit the packages in Morton order.  Process-wide; default (0, 1), with which
  * the library itself takes variant 3 or 7, and Morton order in those passes,
- * where a field is so large (24 MiB and more, for the gradient 96) that they are
- * faster.  Safe to
+ * where a field is so large (24 MiB and more) that they are faster.  Safe to
  * call from any thread: each sweep, gradient or Laplacian call reads the
  * setting once, so a change reaches calls that start after it.  Results are
  * identical for every setting.

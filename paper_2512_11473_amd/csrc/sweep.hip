@@ -839,6 +839,12 @@ static SweepConfig reinit_config(const sgrid_grid *g, size_t element, int32_t n_
 
 // Whether a stencil pass visits the packages in Morton (worklist) order: when
 // the configuration's sweep does, or by the rule above.
+// It pays to follow the sweeps: an XCD then finds rows in its own L2 that it wrote
+// in the last sweep (after four sweeps in Morton order, id and Morton order: SoA
+// gradient of the prism at 820^3 79.6 and 49.4 us, packed 94.1 and 61.0, factorised
+// integrals 95.3 and 86.1; shell at 640^3 45.5 and 32.1, 54.2 and 39.1, 72.8 and
+// 73.2), which outweighs what Morton order costs some bands alone (42.4 and 45.4
+// us the SoA gradient of the sphere at 900^3).
 static bool stencil_in_worklist_order(const sgrid_grid *g, size_t element) {
     const SweepConfig c = current_sweep_config();
     const int v = c.variant;
@@ -1033,10 +1039,7 @@ sgrid_status launch_cut_fractions(const sgrid_grid *g, const float *phi, float *
         set_error("too many packages for one launch");
         return SGRID_E_INVALID;
     }
-    // by the default's rule in id order: Morton order takes 2 us off 94 to 177 us of
-    // both passes (torus at 768^3 to 1024^3 points), but adds 2 to the prism's 124 at
-    // 820^3
-    const bool work = current_sweep_config().variant != 0 && stencil_in_worklist_order(g, 4);
+    const bool work = stencil_in_worklist_order(g, 4);
     const bool nt_store = 2.0 * (double)nt * 64.0 * 4.0 > kLastLevelCacheBytes;
     const float inv_h = (float)(1.0 / g->h), inv_2h = (float)(0.5 / g->h);
     if (work)
@@ -1164,16 +1167,13 @@ static sgrid_status gradient_entry(const sgrid_grid *g, sgrid_dtype dtype, const
     hipStream_t st = sg_stream(stream);
     const int64_t nt = g->total();
     const int64_t nb = (nt + 15) / 16;
-    // by default only the FP32 SoA gradient of a field of kGradientBytes and more:
-    // torus at 1024^3 points (110 MiB) 77.2 us in id order and 70.5 in Morton order,
-    // shell at 1024^3 (142 MiB) 157 and 150, torus at 2048^3 485 and 459, but sphere
-    // at 900^3 (70 MiB) 42.4 and 45.4, prism at 820^3 (79 MiB) 48.9 and 50.8; the FP64
-    // one is slower in Morton order (at 221 MiB a field 150 and 184 us), the packed one
-    // now faster, now slower
+    // in FP64 by default below kGradientBytes: after sweeps in Morton order prism512
+    // (62 MiB) 63 us in id order and 40 in Morton order, torus at 700^3 (103 MiB) 100
+    // and 100, but alone a shell at 640^3 (160 MiB) 61 and 87
     constexpr double kGradientBytes = 96.0 * 1024 * 1024;
     const bool tuned = sgrid::current_sweep_config().variant != 0;
-    const bool large = !PACKED && dtype == SGRID_F32 && (double)nt * 256.0 >= kGradientBytes;
-    const bool work = (tuned || large) && sgrid::stencil_in_worklist_order(g, dtype == SGRID_F32 ? 4 : 8);
+    const bool follows = dtype == SGRID_F32 || (double)nt * 512.0 < kGradientBytes;
+    const bool work = (tuned || follows) && sgrid::stencil_in_worklist_order(g, dtype == SGRID_F32 ? 4 : 8);
     // streaming stores when phi and the output together exceed the last-level
     // cache; not for the FP64 packed layout, whose four stores per lane each
     // fill only parts of lines (the cache merges them, streaming writes would
