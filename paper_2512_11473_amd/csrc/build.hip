@@ -8,9 +8,9 @@
 //                   one ballot each;
 //   dilate_kernel   one lane per word: activated = core dilated by one cell in
 //                   x, y, z (word shifts and ORs); per-group counts;
-//   scan_counts     exclusive scan of the counts (block sums, one workgroup
-//                   over them, block scans);
-//   (host)          read back P and n_core once, allocate the package tables;
+//   scan_counts     exclusive scan of the counts (one workgroup while it can,
+//                   else block sums, one workgroup over them, block scans);
+//   (host)          P and n_core once, from a pinned word; the package tables;
 //   scatter_kernel  16 words per wavefront in steps of four, four cells per lane: rank by
 //                   popcount below the cell plus word offsets from the scan,
 //                   id = 2 + rank in ascending linear order (no sort needed);

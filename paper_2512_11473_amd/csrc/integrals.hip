@@ -1,7 +1,7 @@
 // Near-surface kernel integrals over the core packages (Sec. 8: the integral
 // with an SPH smoothing kernel evaluated on the sparse grid).
 //
-// One wavefront per core package.  The package's 9 x 9 x 9 phi window (local
+// A wavefront takes one to four core packages in turn.  A package's 9 x 9 x 9 phi window (local
 // coordinates -2..6 per axis, reached through the 27-entry neighbour table and
 // the index shift of Sec. 5.2) is staged in LDS; the cut fractions V of the
 // 7 x 7 x 7 points -1..5 are computed once per point into LDS; then every lane
