@@ -194,15 +194,15 @@ __device__ __forceinline__ void row_neighbours(const T (&c)[4], const T (&h)[4],
 // these: torus at 256^3 points 5.8 and 5.2 us, prism512 14.6 and 13.6, torus at
 // 768^3 26.0 and 25.1, at 1024^3 41.3 and 40.4.  The compiler does not see a
 // store in the asm: it does not count it in its waits for loads, which makes them
-// at most longer, and it does not keep the one wait state that the hardware asks
-// for between a store of more than 8 bytes and a write to its data registers, so
-// the asm ends with it.
+// at most longer, and it does not keep the two wait states that gfx940 and later
+// (earlier chips: one) ask for between a store of more than 8 bytes and a vector
+// write to its data registers, so the asm ends with them.
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void store_through(void *p, f32x4_t v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" : : "v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }
 __device__ __forceinline__ void store_through(void *base, uint32_t off, f32x4_t v) {
-    asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 0" : : "v"(off), "v"(v), "s"(base) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 1" : : "v"(off), "v"(v), "s"(base) : "memory");
 }
 __device__ __forceinline__ void store_through(void *base, int64_t off, f32x4_t v) {
     store_through(static_cast<char *>(base) + off, v);
