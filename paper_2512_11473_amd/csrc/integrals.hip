@@ -146,10 +146,11 @@ __global__ __launch_bounds__(256) void integrals_plain_kernel(const float *__res
         id = neighbours(g + 2);
         float kw, kx, ky, kz, side;
         if (window_fractions(s_phi[w], lane, inv_h, inv_2h, s_v[w], s_cut[w], &side)) {
-            // a window on one side of the surface (most inner packages'): its sums without its taps
+            // a window on one side of the surface (most inner packages'): its sums
+            // without its taps.  The gradient sums of equal fractions, 1 or 0, are
+            // zeros with the sign of their weights (negative), as the taps give them.
             sgrid::tap_sums([](int, int, int) { return 1.0f; }, 0, 0, 0, kw, kx, ky, kz);
             kw = side > 0.0f ? kw : 0.0f;
-            kx = ky = kz = 0.0f;
         } else {
             __builtin_amdgcn_wave_barrier();
             tap_sums(s_v[w], i, j, k, kw, kx, ky, kz);
