@@ -282,7 +282,7 @@ constexpr int kSortTile = kSortThreads * kSortRounds;   // 4096 elements per til
 constexpr int kMaxBits = 9;                             // of a digit: one digit per thread
 static_assert((1 << kMaxBits) <= kSortThreads && kSortTile <= 65536, "16-bit counts and places in the tile");
 
-__device__ __forceinline__ uint32_t spread3(uint32_t v) {   // bit b of v (b < 10) to bit 3b
+__device__ __forceinline__ uint32_t spread3(uint32_t v) {   // bit b of v to bit 3b, for the ten lowest
     v &= 0x3FFu;
     v = (v | (v << 16)) & 0x030000FFu;
     v = (v | (v << 8)) & 0x0300F00Fu;
@@ -291,10 +291,21 @@ __device__ __forceinline__ uint32_t spread3(uint32_t v) {   // bit b of v (b < 1
     return v;
 }
 
-// Morton code of the particle's home coarse cell (x in the lowest bit).
-__device__ __forceinline__ uint32_t home_key(const float *x, int M, float inv_h) {
-    const int cx = home_coord(x[0] * inv_h, M), cy = home_coord(x[1] * inv_h, M), cz = home_coord(x[2] * inv_h, M);
-    return spread3((uint32_t)cx) | (spread3((uint32_t)cy) << 1) | (spread3((uint32_t)cz) << 2);
+// The digit of BITS bits from `shift` on of a particle's key, the Morton code of
+// its home coarse cell (x in the lowest bit).  Grids of more than 1024 cells per
+// axis (at most 1625: the package ids' limit) have keys of 33 bits: those above
+// the low 30 are the cells' bits 10, and only the fourth pass of nine bits takes
+// them.
+constexpr int kKeyBits = 30;   // of spread3's three tens
+
+template <int BITS>
+__device__ __forceinline__ uint32_t home_digit(const float *x, int M, float inv_h, int shift) {
+    const uint32_t cx = (uint32_t)home_coord(x[0] * inv_h, M), cy = (uint32_t)home_coord(x[1] * inv_h, M),
+                   cz = (uint32_t)home_coord(x[2] * inv_h, M);
+    uint32_t d = (spread3(cx) | (spread3(cy) << 1) | (spread3(cz) << 2)) >> shift;
+    if (BITS == kMaxBits && shift + BITS > kKeyBits)   // the same for every lane
+        d |= ((cx >> 10) | ((cy >> 10) << 1) | ((cz >> 10) << 2)) << (kKeyBits - shift);
+    return d & ((1u << BITS) - 1u);
 }
 
 // Where a pass reads from and writes to.
@@ -339,7 +350,7 @@ __global__ __launch_bounds__(256) void radix_count_kernel(SortBuffers buf, int64
         float x[3];
         uint32_t idx;
         sort_load<SRC>(buf, e < n ? e : n - 1, x, idx);
-        const uint32_t d = (home_key(x, M, inv_h) >> shift) & (kBins - 1);
+        const uint32_t d = home_digit<BITS>(x, M, inv_h, shift);
         if (e < n) atomicAdd(&s_hist[d], 1u);
     }
     __syncthreads();
@@ -447,7 +458,7 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(SortBuffers
 #pragma unroll
     for (int j = 0; j < kSortRounds; ++j) {
         const bool valid = w0 + 64 * j + lane < n;
-        const uint32_t d = (home_key(x[j], M, inv_h) >> shift) & (kBins - 1);
+        const uint32_t d = home_digit<BITS>(x[j], M, inv_h, shift);
         // lanes of this round with the same digit (the valid ones)
         uint64_t peers = __ballot(valid);
 #pragma unroll
