@@ -472,9 +472,10 @@ sgrid_status sgrid_compute_laplacian(const sgrid_grid *grid, sgrid_dtype dtype, 
  * 5, the number of four-package sets one wavefront processes, for variants 2
  * and 6 the number of workgroups per compute unit, and is ignored by variants
  * 4 and 7.  With variant 2, 3, 4 or 7 the gradient and Laplacian passes also
- * visit the packages in Morton order.  Process-wide; default (0, 1), with which
- * the library itself takes variant 3 or 7, and Morton order in those passes,
- * where a field is so large (24 MiB and more) that they are faster.  Safe to
+ * visit the packages in Morton order.  Process-wide; (0, 1) is the default, with
+ * which the library itself takes variant 3 or 7, and Morton order in those
+ * passes, where a field is so large (24 MiB and more) that they are faster (id
+ * order at every size: (0, 2)).  Safe to
  * call from any thread: each sweep, gradient or Laplacian call reads the
  * setting once, so a change reaches calls that start after it.  Results are
  * identical for every setting.
@@ -483,14 +484,16 @@ sgrid_status sgrid_set_sweep_config(int32_t variant, int32_t groups);
 
 /*
  * Autotuner of sgrid_reinitialize on the caller's grid: times the candidates
- * (variant, groups) = (0, 1), (0, 2), (2, 4), (3, 1), (3, 2), (5, 1), (7, 1)
- * with `reps` sweeps each (1..1000) that read phi and write scratch (phi is
- * not modified; scratch rows 2.. are overwritten; variant 7 is timed on its
- * steady-state sweep, worklist order to worklist order), makes the fastest
- * the process-wide configuration (as sgrid_set_sweep_config) and returns it.
- * us_table [7] (nullable) receives the microseconds per sweep in that order.
- * Synchronises the stream.  Results are identical for every candidate, so
- * tuning changes only speed.
+ * (variant, groups) = (0, 1), (0, 2), (2, 4), (3, 1), (3, 2), (5, 1), (7, 1),
+ * the first as the library runs it by default, with `reps` sweeps each
+ * (1..1000) as a call makes them, to and fro between scratch and a buffer of
+ * its size that the tuner allocates and frees (where that fails, from phi to
+ * scratch).  phi is only read; scratch rows 2.. are overwritten.  Variant 7 is
+ * timed on its steady-state sweep, worklist order to worklist order.  Makes the
+ * fastest the process-wide configuration (as sgrid_set_sweep_config) and
+ * returns it.  us_table [7] (nullable) receives the microseconds per sweep in
+ * that order.  Synchronises the stream.  Results are identical for every
+ * candidate, so tuning changes only speed.
  */
 sgrid_status sgrid_autotune_sweep(const sgrid_grid *grid, sgrid_dtype dtype, const void *phi_dev,
                                   void *scratch_dev, int32_t reps, void *stream, int32_t *variant_out,

@@ -784,7 +784,7 @@ namespace sgrid {
 
 // Sweep variants: 0 DPP exchange, 1 LDS tile, 2 persistent Morton walk,
 // 3 Morton worklist, 4 group-shared LDS, 5 LDS row exchange, 6 persistent
-// walk in package-id order.
+// walk in package-id order, 7 Morton-ordered copy.
 struct SweepConfig {
     int variant = 0;
     int groups = 1;   // sets of four packages per wavefront, or workgroups per CU (2, 6)
@@ -822,14 +822,14 @@ static bool default_takes_worklist(const sgrid_grid *g, const SweepConfig &c, si
     return c.variant == 0 && c.groups == 1 && (double)g->total() * 64.0 * (double)element >= kWorklistBytes;
 }
 
-// What a reinitialisation of n_iter sweeps runs.  The field goes through a
-// worklist-ordered copy (variant 7) in FP32 from kCopyBytes on, when there are
-// sweeps enough to pay for the way in and out: at 4 sweeps variant 3 is ahead
-// (torus at 1024^3 points 39.5 us a sweep, variant 7 46.6), at 100 variant 7 (torus
-// at 2048^3 225 and 214; equal below kCopyBytes, prism512 12.1 and 12.1).  In FP64
-// variant 3 (prism512 24.4 us, variant 7 24.3; id order 26.4).
-static SweepConfig reinit_config(const sgrid_grid *g, size_t element, int32_t n_iter) {
-    SweepConfig c = current_sweep_config();
+// What a reinitialisation of n_iter sweeps runs under configuration c.  By default
+// the field goes through a worklist-ordered copy (variant 7) in FP32 from
+// kCopyBytes on, when there are sweeps enough to pay for the way in and out: at 4
+// sweeps variant 3 is ahead (torus at 1024^3 points 39.5 us a sweep, variant 7
+// 46.6), at 100 variant 7 (torus at 2048^3 225 and 214; equal below kCopyBytes,
+// prism512 12.1 and 12.1).  In FP64 variant 3 (prism512 24.4 us, variant 7 24.3;
+// id order 26.4).
+static SweepConfig reinit_config(const sgrid_grid *g, SweepConfig c, size_t element, int32_t n_iter) {
     if (default_takes_worklist(g, c, element)) {
         const bool copy = element == 4 && n_iter >= 8 && (double)g->total() * 64.0 * 4.0 >= kCopyBytes;
         c.variant = copy ? 7 : 3;
@@ -872,7 +872,9 @@ static void launch_dpp_range(const sgrid_grid *g, const T *src, T *dst, int64_t 
         hipLaunchKernelGGL(kernel, grid, block, 0, st, src, dst, g->face, (I)first, (I)end, (I)nb, h2, inv_h, dt, pass);
     };
     switch (groups) {
-        case 1: launch(reinit_dpp_kernel<T, 1, I, BIG>); break;
+        case 1:   // (0, 1) is the default, which takes variant 3 or 7 for larger fields
+            if constexpr (!BIG) launch(reinit_dpp_kernel<T, 1, I, BIG>);
+            break;
         case 2: launch(reinit_dpp_kernel<T, 2, I, BIG>); break;
         case 3: launch(reinit_dpp_kernel<T, 3, I, BIG>); break;
         case 4: launch(reinit_dpp_kernel<T, 4, I, BIG>); break;
@@ -1062,46 +1064,84 @@ extern "C" sgrid_status sgrid_set_sweep_config(int32_t variant, int32_t groups) 
     return SGRID_OK;
 }
 
-// Candidates of the sweep autotuner: (variant, groups).
+// Candidates of the sweep autotuner: (variant, groups).  The first is the default,
+// timed as a call of many sweeps runs it (reinit_config), as it is if picked.
 constexpr int kNumTune = 7;
 static const int kTuneCandidates[kNumTune][2] = {{0, 1}, {0, 2}, {2, 4}, {3, 1}, {3, 2}, {5, 1}, {7, 1}};
 
+// Times the candidates as a call's sweeps run: from one buffer to the other and back,
+// in alternating directions.  phi is only read, so the second buffer is made here and
+// given back.  (Sweeps that all read phi and write scratch find phi in the Infinity
+// Cache in place of the rows they wrote: for the shell at 1024^3 points id order, two
+// sets per wavefront, then looked the fastest with 49 us, where a call takes 80 us a
+// sweep and the default 72; the torus at 1200^3 60, 88 and 73.)  Where there is no
+// memory for it they do read phi, and stream all their rows.
 template <typename T>
-static sgrid_status autotune_sweep(const sgrid_grid *g, const T *phi, T *scratch, int32_t reps, hipStream_t st,
-                                   int32_t *variant_out, int32_t *groups_out, float *us_table) {
-    hipEvent_t e0, e1;
-    SG_CHECK_HIP(hipEventCreate(&e0));
-    SG_CHECK_HIP(hipEventCreate(&e1));
+static sgrid_status time_sweeps(const sgrid_grid *g, const T *phi, T *scratch, T *other, int32_t reps, hipStream_t st,
+                                hipEvent_t e0, hipEvent_t e1, sgrid::SweepConfig &pick, float *us_table) {
     float best = 1e30f;
-    sgrid::SweepConfig pick;
     for (int c = 0; c < kNumTune; ++c) {
-        sgrid::SweepConfig cfg;
-        cfg.variant = kTuneCandidates[c][0];
-        cfg.groups = kTuneCandidates[c][1];
-        // phi is only read: every timed sweep writes scratch
-        sgrid_status s = sgrid::launch_reinit_sweep<T>(g, phi, scratch, st, cfg);
-        if (s == SGRID_OK && hipEventRecord(e0, st) != hipSuccess) s = SGRID_E_HIP;
-        for (int32_t k = 0; s == SGRID_OK && k < reps; ++k) s = sgrid::launch_reinit_sweep<T>(g, phi, scratch, st, cfg);
+        sgrid::SweepConfig named, cfg;
+        named.variant = kTuneCandidates[c][0];
+        named.groups = kTuneCandidates[c][1];
+        cfg = sgrid::reinit_config(g, named, sizeof(T), INT32_MAX);
+        // the call's first sweep (variant 7: into worklist order), then its steady state
+        sgrid_status s = sgrid::launch_reinit_sweep<T>(g, phi, scratch, st, cfg, 0, false, other == nullptr);
+        if (s != SGRID_OK) return s;
+        if (other != nullptr) s = sgrid::launch_reinit_sweep<T>(g, scratch, other, st, cfg, 1, true);
+        if (s != SGRID_OK) return s;
+        SG_CHECK_HIP(hipEventRecord(e0, st));
+        for (int32_t k = 0; k < reps; ++k) {
+            if (other != nullptr)
+                s = sgrid::launch_reinit_sweep<T>(g, k & 1 ? scratch : other, k & 1 ? other : scratch, st, cfg, 1,
+                                                  (k & 1) != 0);
+            else
+                s = sgrid::launch_reinit_sweep<T>(g, phi, scratch, st, cfg, 1, false, true);
+            if (s != SGRID_OK) return s;
+        }
         float ms = 0.f;
-        if (s == SGRID_OK && (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-                              hipEventElapsedTime(&ms, e0, e1) != hipSuccess)) {
-            sgrid::set_error("sweep autotune timing failed");
-            s = SGRID_E_HIP;
-        }
-        if (s != SGRID_OK) {
-            (void)hipEventDestroy(e0);
-            (void)hipEventDestroy(e1);
-            return s;
-        }
+        SG_CHECK_HIP(hipEventRecord(e1, st));
+        SG_CHECK_HIP(hipEventSynchronize(e1));
+        SG_CHECK_HIP(hipEventElapsedTime(&ms, e0, e1));
         const float us = 1e3f * ms / reps;
         if (us_table) us_table[c] = us;
         if (us < best) {
             best = us;
-            pick = cfg;
+            pick = named;
         }
     }
+    return SGRID_OK;
+}
+
+template <typename T>
+static sgrid_status autotune_sweep(const sgrid_grid *g, const T *phi, T *scratch, int32_t reps, hipStream_t st,
+                                   int32_t *variant_out, int32_t *groups_out, float *us_table) {
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    SG_CHECK_HIP(hipEventCreate(&e0));
+    if (hipError_t e = hipEventCreate(&e1); e != hipSuccess) {
+        (void)hipEventDestroy(e0);
+        SG_CHECK_HIP(e);
+    }
+    T *other = nullptr;
+    if (hipMalloc((void **)&other, (size_t)g->total() * 64 * sizeof(T)) != hipSuccess) {
+        (void)hipGetLastError();
+        other = nullptr;
+    }
+    sgrid::SweepConfig pick;
+    sgrid_status s = SGRID_OK;
+    if (other != nullptr &&
+        hipMemcpyAsync(other, phi, 2 * 64 * sizeof(T), hipMemcpyDeviceToDevice, st) != hipSuccess) {   // far-field rows
+        sgrid::set_error("far-field rows could not be copied");
+        s = SGRID_E_HIP;
+    }
+    if (s == SGRID_OK) s = time_sweeps<T>(g, phi, scratch, other, reps, st, e0, e1, pick, us_table);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
+    if (other != nullptr) {
+        (void)hipStreamSynchronize(st);
+        (void)hipFree(other);
+    }
+    if (s != SGRID_OK) return s;
     sgrid::set_sweep_config(pick.variant, pick.groups);
     if (variant_out) *variant_out = pick.variant;
     if (groups_out) *groups_out = pick.groups;
@@ -1150,7 +1190,8 @@ extern "C" sgrid_status sgrid_reinitialize(const sgrid_grid *g, sgrid_dtype dtyp
     SG_REQUIRE(n_iter >= 0, "n_iter must be >= 0 (got %d)", n_iter);
     SG_REQUIRE(dtype == SGRID_F32 || dtype == SGRID_F64, "unknown dtype %d", (int)dtype);
     hipStream_t st = sg_stream(stream);
-    const sgrid::SweepConfig cfg = sgrid::reinit_config(g, dtype == SGRID_F32 ? 4 : 8, n_iter);
+    const sgrid::SweepConfig cfg =
+        sgrid::reinit_config(g, sgrid::current_sweep_config(), dtype == SGRID_F32 ? 4 : 8, n_iter);
     if (dtype == SGRID_F32)
         return sgrid::reinit_impl<float>(g, (float *)phi, (float *)scratch, n_iter, st, cfg);
     return sgrid::reinit_impl<double>(g, (double *)phi, (double *)scratch, n_iter, st, cfg);
