@@ -184,6 +184,33 @@ __device__ __forceinline__ void row_neighbours(const T (&c)[4], const T (&h)[4],
     }
 }
 
+// The same moves as the compiler's own instructions, two per neighbour: for kernels
+// that keep a set's loads in flight with the one before it or behind a barrier,
+// where the block above, which waits for all its operands at once, is the slower.
+// row_move: lanes whose source lies outside their 16-lane row read 0 and must not
+// use the result.  row_move_keep: lanes of the banks (groups of four lanes of a row)
+// left out of BANKS keep `keep`.
+constexpr int kRowShl1 = 0x101, kRowShl4 = 0x104, kRowShr1 = 0x111, kRowShr4 = 0x114;
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t row_move(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL, int BANKS>
+__device__ __forceinline__ uint32_t row_move_keep(uint32_t v, uint32_t keep) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)keep, (int)v, CTRL, 0xF, BANKS, false);
+}
+// `op` on a value's 32-bit words.
+template <typename T, class Op>
+__device__ __forceinline__ T by_words(T a, T b, Op op) {
+    struct Words { uint32_t w[sizeof(T) / 4]; };
+    Words x = __builtin_bit_cast(Words, a);
+    const Words y = __builtin_bit_cast(Words, b);
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(T) / 4; ++i) x.w[i] = op(x.w[i], y.w[i]);
+    return __builtin_bit_cast(T, x);
+}
+
 // 16-byte store written through the L2 (device scope, sc1) instead of left
 // dirty in it.  The eight XCDs' L2 caches (4 MiB each) do not see each other's
 // lines, so a kernel's dirty lines are written back when it ends, after its last

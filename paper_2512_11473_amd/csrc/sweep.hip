@@ -98,7 +98,8 @@ __device__ __forceinline__ void store_row(T *__restrict__ p, const Row<T> &r, bo
 // with those loads, so with few wavefronts per CU, or little to write back, plain
 // stores are faster (variant 2, prism512: 28.4 us a sweep at one workgroup per CU
 // and 30.0 written through, but 15.6 and 14.4 at four; variant 4, torus at 128^3: 4.4
-// and 4.7).
+// and 4.7).  Which one is the kernels' template parameter: with both in its loop
+// variant 6 at two workgroups per CU took 18.7 us for prism512 instead of 17.0.
 template <typename T>
 __device__ __forceinline__ void store_row(T *__restrict__ p, const Row<T> &r, bool nt, bool through) {
     if (nt || through)
@@ -107,7 +108,9 @@ __device__ __forceinline__ void store_row(T *__restrict__ p, const Row<T> &r, bo
         store_row_plain(p, r);
 }
 
-// A row stored at a byte offset.
+// A row stored at a byte offset (written through at every size of field: one-set
+// sweeps with plain stores and with these, sphere64 2.33 and 2.31 us, torus at 128^3
+// 3.12 and 2.80, sphere at 200^3 3.56 and 3.41, torus at 256^3 5.42 and 4.88).
 template <typename T, typename I>
 __device__ __forceinline__ void store_row_at(T *__restrict__ base, I off, const Row<T> &r, bool nt) {
     if (sizeof(T) == 4 && !nt)
@@ -191,6 +194,33 @@ __device__ __forceinline__ Stencil<T> assemble(const Loads<T> &l) {
     s.xp = l.xp;
     row_neighbours<false>(l.c.v, l.yh.v, s.ym.v, s.yp.v);
     row_neighbours<true>(l.c.v, l.zh.v, s.zm.v, s.zp.v);
+    return s;
+}
+
+// The same with the compiler's moves, for the kernels whose loads are in flight over
+// a round of their loop or a barrier (variants 2, 4 and 6; the torus at 768^3 points
+// with these and with the block's: variant 2 at one workgroup per CU 55.0 and 55.6 us a
+// sweep, variant 4 30.3 and 31.4, variant 6 at two 29.8 and 30.5).  In FP64 variant 2
+// takes the block (prism512 35.6 us at one workgroup per CU, with these 40.0), variants
+// 4 and 6 these (30.1 and 29.0; 36.6 and 34.8).
+template <typename T>
+__device__ __forceinline__ Stencil<T> assemble_apart(int r, const Loads<T> &l) {
+    const int j = r & 3;
+    Stencil<T> s;
+    s.c = l.c;
+    s.xm = l.xm;
+    s.xp = l.xp;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const T v = l.c.v[i], yh = l.yh.v[i], zh = l.zh.v[i];
+        const T a = by_words(v, v, [](uint32_t x, uint32_t) { return row_move<kRowShr1>(x); });
+        const T b = by_words(v, v, [](uint32_t x, uint32_t) { return row_move<kRowShl1>(x); });
+        s.ym.v[i] = j == 0 ? yh : a;
+        s.yp.v[i] = j == 3 ? yh : b;
+        // the k = 0 (k = 3) lanes are bank 0 (bank 3) of the row
+        s.zm.v[i] = by_words(v, zh, [](uint32_t x, uint32_t y) { return row_move_keep<kRowShr4, 0xE>(x, y); });
+        s.zp.v[i] = by_words(v, zh, [](uint32_t x, uint32_t y) { return row_move_keep<kRowShl4, 0x7>(x, y); });
+    }
     return s;
 }
 
@@ -376,11 +406,11 @@ __device__ __forceinline__ Row<T> halo_row(const T *__restrict__ src, const T (*
     return load_row(src + (int64_t)f * 64 + off);
 }
 
-template <typename T>
+template <typename T, bool THROUGH>
 __global__ __launch_bounds__(1024) void reinit_share_kernel(const T *__restrict__ src, T *__restrict__ dst,
                                                             const uint32_t *__restrict__ work,
                                                             const uint32_t *__restrict__ sface, int64_t P,
-                                                            int64_t n_blocks, T h2, T inv_h, T dt, bool through) {
+                                                            int64_t n_blocks, T h2, T inv_h, T dt) {
     __shared__ T tile[kGroup][64];
     const int64_t b = xcd_block(blockIdx.x, n_blocks);
     const int lane = threadIdx.x & 63;
@@ -408,8 +438,8 @@ __global__ __launch_bounds__(1024) void reinit_share_kernel(const T *__restrict_
     l.xp = halo_value(src, tile, f0.y, r * 4);
     if (j == 0 || j == 3) l.yh = halo_row(src, tile, j == 0 ? f0.z : f0.w, (j == 0 ? 3 + 4 * k : 4 * k) * 4);
     if (k == 0 || k == 3) l.zh = halo_row(src, tile, k == 0 ? f1.x : f1.y, (k == 0 ? j + 12 : j) * 4);
-    const Stencil<T> s = assemble(l);
-    store_row(dst + p * 64 + r * 4, reinit_row(s, h2, inv_h, dt), false, through);
+    const Stencil<T> s = assemble_apart(r, l);
+    store_row(dst + p * 64 + r * 4, reinit_row(s, h2, inv_h, dt), false, THROUGH);
 }
 
 // Persistent worklist variant: a fixed grid of `groups` workgroups per CU
@@ -425,10 +455,10 @@ __global__ __launch_bounds__(1024) void reinit_share_kernel(const T *__restrict_
 // same package as its own lanes: the store stays unconditional, because a
 // conditional one lets the compiler sink the halo loads into the branch,
 // behind the DPP exchange, adding a memory round trip.
-template <typename T>
+template <typename T, bool THROUGH>
 __global__ __launch_bounds__(256) void reinit_pipe_kernel(const T *__restrict__ src, T *__restrict__ dst,
                                                           const uint32_t *__restrict__ wface, int64_t P,
-                                                          int64_t n_blocks, T h2, T inv_h, T dt, bool nt, bool through) {
+                                                          int64_t n_blocks, T h2, T inv_h, T dt, bool nt) {
     const int64_t b = xcd_block(blockIdx.x, n_blocks);
     const int lane = threadIdx.x & 63;
     const int r = lane & 15;
@@ -453,8 +483,12 @@ __global__ __launch_bounds__(256) void reinit_pipe_kernel(const T *__restrict__ 
         f1 = *reinterpret_cast<const uint4 *>(wface + e * 8 + 4);
         Loads<T> l;
         issue_data<T, int64_t>(src, (uint32_t)p, r, c0, cz, l);
-        const Stencil<T> st = assemble(l);
-        store_row(dst + p * 64 + r * 4, reinit_row(st, h2, inv_h, dt), nt, through);
+        Stencil<T> st;
+        if constexpr (sizeof(T) == 4)
+            st = assemble_apart(r, l);
+        else
+            st = assemble(l);
+        store_row(dst + p * 64 + r * 4, reinit_row(st, h2, inv_h, dt), nt, THROUGH);
     }
 }
 
@@ -462,10 +496,10 @@ __global__ __launch_bounds__(256) void reinit_pipe_kernel(const T *__restrict__ 
 // packages in id order, where a set's package ids are known without a table:
 // each wavefront loads the next set's face row and own rows while the current
 // set's halo rows are in flight, so a set costs one memory round trip.
-template <typename T>
+template <typename T, bool THROUGH>
 __global__ __launch_bounds__(256) void reinit_pipe_lin_kernel(const T *__restrict__ src, T *__restrict__ dst,
                                                               const uint32_t *__restrict__ face, int64_t P,
-                                                              int64_t n_blocks, T h2, T inv_h, T dt, bool through) {
+                                                              int64_t n_blocks, T h2, T inv_h, T dt) {
     const int64_t b = xcd_block(blockIdx.x, n_blocks);
     const int lane = threadIdx.x & 63;
     const int r = lane & 15;
@@ -492,8 +526,8 @@ __global__ __launch_bounds__(256) void reinit_pipe_lin_kernel(const T *__restric
         load_face(face, p, f0, f1);
         own = load_row(src + p * 64 + r * 4);
         issue_halos<T, int64_t>(src, r, c0, c1, l);
-        const Stencil<T> st = assemble(l);
-        store_row(dst + pc * 64 + r * 4, reinit_row(st, h2, inv_h, dt), false, through);
+        const Stencil<T> st = assemble_apart(r, l);
+        store_row(dst + pc * 64 + r * 4, reinit_row(st, h2, inv_h, dt), false, THROUGH);
     }
 }
 
@@ -970,8 +1004,8 @@ static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *ds
     } else if (cfg.variant == 6) {
         const int64_t n_sets = (g->P + 3) / 4;
         const int64_t nbp = std::min<int64_t>((int64_t)cu_count() * cfg.groups, (n_sets + 3) / 4);
-        hipLaunchKernelGGL(reinit_pipe_lin_kernel<T>, dim3((unsigned)nbp), block, 0, st, src, dst, g->face, g->P, nbp,
-                           h2, inv_h, dt, cfg.groups >= 4);
+        hipLaunchKernelGGL((cfg.groups >= 4 ? reinit_pipe_lin_kernel<T, true> : reinit_pipe_lin_kernel<T, false>),
+                           dim3((unsigned)nbp), block, 0, st, src, dst, g->face, g->P, nbp, h2, inv_h, dt);
     } else if (cfg.variant == 5) {
         switch (cfg.groups) {
             case 1: hipLaunchKernelGGL((reinit_rows_kernel<T, 1>), grid, block, 0, st, src, dst, g->face, g->P, nb, h2, inv_h, dt, nt); break;
@@ -982,8 +1016,8 @@ static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *ds
         }
     } else if (cfg.variant == 4) {
         const int64_t ng = (g->P + kGroup - 1) / kGroup;
-        hipLaunchKernelGGL(reinit_share_kernel<T>, dim3((unsigned)ng), dim3(1024), 0, st, src, dst, g->work, g->sface,
-                           g->P, ng, h2, inv_h, dt, g->P >= 16384);
+        hipLaunchKernelGGL((g->P >= 16384 ? reinit_share_kernel<T, true> : reinit_share_kernel<T, false>),
+                           dim3((unsigned)ng), dim3(1024), 0, st, src, dst, g->work, g->sface, g->P, ng, h2, inv_h, dt);
     } else if (cfg.variant == 3) {
         sized([&](auto index, auto big) {
             launch_work<T, decltype(index), decltype(big)::value>(g, src, dst, cfg.groups, pass, st);
@@ -991,8 +1025,8 @@ static sgrid_status launch_reinit_sweep(const sgrid_grid *g, const T *src, T *ds
     } else if (cfg.variant == 2) {
         const int64_t n_sets = (g->P + 3) / 4;
         const int64_t nbp = std::min<int64_t>((int64_t)cu_count() * cfg.groups, (n_sets + 3) / 4);
-        hipLaunchKernelGGL(reinit_pipe_kernel<T>, dim3((unsigned)nbp), block, 0, st, src, dst, g->wface, g->P, nbp,
-                           h2, inv_h, dt, nt, cfg.groups >= 4);
+        hipLaunchKernelGGL((cfg.groups >= 4 ? reinit_pipe_kernel<T, true> : reinit_pipe_kernel<T, false>),
+                           dim3((unsigned)nbp), block, 0, st, src, dst, g->wface, g->P, nbp, h2, inv_h, dt, nt);
     } else if (cfg.variant == 1) {
         hipLaunchKernelGGL(reinit_lds_kernel<T>, grid, block, 0, st, src, dst, g->face, g->P, nb, cfg.groups, h2,
                            inv_h, dt);
