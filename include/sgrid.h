@@ -471,14 +471,14 @@ sgrid_status sgrid_compute_laplacian(const sgrid_grid *grid, sgrid_dtype dtype, 
  * contiguous rows.  `groups` (1, 2, 3, 4 or 8) is, for variants 0, 1, 3 and
  * 5, the number of four-package sets one wavefront processes, for variants 2
  * and 6 the number of workgroups per compute unit, and is ignored by variants
- * 4 and 7.  With variant 2, 3, 4 or 7 the gradient and Laplacian passes also
- * visit the packages in Morton order.  Process-wide; (0, 1) is the default, with
- * which the library itself takes variant 3 or 7, and Morton order in those
- * passes, where a field is so large (24 MiB and more) that they are faster (id
- * order at every size: (0, 2)).  Safe to
- * call from any thread: each sweep, gradient or Laplacian call reads the
- * setting once, so a change reaches calls that start after it.  Results are
- * identical for every setting.
+ * 4 and 7.  With variant 2, 3, 4 or 7 the gradient and Laplacian passes and the
+ * first pass of the factorised integrals also visit the packages in Morton
+ * order.  Process-wide; (0, 1) is the default, with which the library itself
+ * takes variant 3 or 7, and Morton order in those passes, where a field is so
+ * large (24 MiB and more) that they are faster (id order at every size: (0, 2)).
+ * Safe to call from any thread: each call of these passes reads the setting
+ * once, so a change reaches calls that start after it.  Results are identical
+ * for every setting.
  */
 sgrid_status sgrid_set_sweep_config(int32_t variant, int32_t groups);
 

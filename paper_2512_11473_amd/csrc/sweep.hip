@@ -879,8 +879,7 @@ static SweepConfig reinit_config(const sgrid_grid *g, SweepConfig c, size_t elem
 // integrals 95.3 and 86.1; shell at 640^3 45.5 and 32.1, 54.2 and 39.1, 72.8 and
 // 73.2), which outweighs what Morton order costs some bands alone (42.4 and 45.4
 // us the SoA gradient of the sphere at 900^3).
-static bool stencil_in_worklist_order(const sgrid_grid *g, size_t element) {
-    const SweepConfig c = current_sweep_config();
+static bool stencil_in_worklist_order(const sgrid_grid *g, const SweepConfig &c, size_t element) {
     const int v = c.variant;
     return v == 2 || v == 3 || v == 4 || v == 7 || default_takes_worklist(g, c, element);
 }
@@ -1075,7 +1074,7 @@ sgrid_status launch_cut_fractions(const sgrid_grid *g, const float *phi, float *
         set_error("too many packages for one launch");
         return SGRID_E_INVALID;
     }
-    const bool work = stencil_in_worklist_order(g, 4);
+    const bool work = stencil_in_worklist_order(g, current_sweep_config(), 4);
     const bool nt_store = 2.0 * (double)nt * 64.0 * 4.0 > kLastLevelCacheBytes;
     const float inv_h = (float)(1.0 / g->h), inv_2h = (float)(0.5 / g->h);
     if (work)
@@ -1246,9 +1245,9 @@ static sgrid_status gradient_entry(const sgrid_grid *g, sgrid_dtype dtype, const
     // (62 MiB) 63 us in id order and 40 in Morton order, torus at 700^3 (103 MiB) 100
     // and 100, but alone a shell at 640^3 (160 MiB) 61 and 87
     constexpr double kGradientBytes = 96.0 * 1024 * 1024;
-    const bool tuned = sgrid::current_sweep_config().variant != 0;
+    const sgrid::SweepConfig cfg = sgrid::current_sweep_config();
     const bool follows = dtype == SGRID_F32 || (double)nt * 512.0 < kGradientBytes;
-    const bool work = (tuned || follows) && sgrid::stencil_in_worklist_order(g, dtype == SGRID_F32 ? 4 : 8);
+    const bool work = (cfg.variant != 0 || follows) && sgrid::stencil_in_worklist_order(g, cfg, dtype == SGRID_F32 ? 4 : 8);
     // streaming stores when phi and the output together exceed the last-level
     // cache; not for the FP64 packed layout, whose four stores per lane each
     // fill only parts of lines (the cache merges them, streaming writes would
@@ -1334,7 +1333,8 @@ extern "C" sgrid_status sgrid_compute_laplacian(const sgrid_grid *g, sgrid_dtype
     SG_REQUIRE(dtype == SGRID_F32 || dtype == SGRID_F64, "unknown dtype %d", (int)dtype);
     hipStream_t st = sg_stream(stream);
     const int64_t nt = g->total();
-    const bool work = sgrid::stencil_in_worklist_order(g, dtype == SGRID_F32 ? 4 : 8);
+    const bool work =
+        sgrid::stencil_in_worklist_order(g, sgrid::current_sweep_config(), dtype == SGRID_F32 ? 4 : 8);
     // streaming stores when phi and the output together exceed the last-level cache
     const bool stream_out = (double)nt * 64.0 * (dtype == SGRID_F32 ? 4.0 : 8.0) * 2.0 > sgrid::kLastLevelCacheBytes;
     if (dtype == SGRID_F32)
