@@ -514,27 +514,44 @@ __global__ __launch_bounds__(256) void scatter_kernel(const uint64_t *__restrict
 // and reads the package id of its activated cells only.
 constexpr int kBoxesPerGroup = 64;   // boxes per count, and per workgroup of the scatter
 
-__device__ __forceinline__ void morton_decode(int64_t code, int bits, int &x, int &y, int &z) {
-    x = y = z = 0;
-    for (int b = 0; b < bits; ++b) {
-        x |= (int)((code >> (3 * b)) & 1) << b;
-        y |= (int)((code >> (3 * b + 1)) & 1) << b;
-        z |= (int)((code >> (3 * b + 2)) & 1) << b;
-    }
+// Bits 0, 3, 6, .. of v (at most ten of them) together.
+__device__ __forceinline__ uint32_t every_third(uint32_t v) {
+    v &= 0x09249249u;
+    v = (v | (v >> 2)) & 0x030C30C3u;
+    v = (v | (v >> 4)) & 0x0300F00Fu;
+    v = (v | (v >> 8)) & 0x030000FFu;
+    return (v | (v >> 16)) & 0x3FFu;
 }
 
-// Activation mask of the box of codes 64 box .. 64 box + 63 and its origin
-// cell; 0 when the box lies past the codes or the grid.
-__device__ __forceinline__ uint64_t box_mask(const uint64_t *__restrict__ act, int M, int W, int bits,
-                                             int64_t box, int64_t n_codes, int &ox, int &oy, int &oz) {
-    ox = oy = oz = 0;
-    if (box * 64 >= n_codes) return 0ull;
-    if (bits > 2) {
-        morton_decode(box, bits - 2, ox, oy, oz);
-        ox *= 4;
-        oy *= 4;
-        oz *= 4;
-    }
+// The 64 boxes of a group, consecutive in code order, are a 4 x 4 x 4 block too; its
+// origin in groups (at most seven bits per axis).
+__device__ __forceinline__ void group_origin(uint32_t group, int &gx, int &gy, int &gz) {
+    gx = (int)every_third(group);
+    gy = (int)every_third(group >> 1);
+    gz = (int)every_third(group >> 2);
+}
+// The place of a group's masks, -1 when it lies past the grid (of ng groups per axis).
+// The masks hold the groups that meet the grid: in code order where these fill the
+// enclosing cube of codes, else x fastest, for the cube has up to eight times as many
+// (1 GiB of masks at 1025 cells per axis, where these take 0.14 GiB).  The same for the
+// wavefront that asks.
+__device__ __forceinline__ int64_t group_masks(uint32_t group, int64_t n_groups, int ng) {
+    if ((int64_t)ng * ng * ng == n_groups) return (int64_t)group * kBoxesPerGroup;
+    int gx, gy, gz;
+    group_origin(group, gx, gy, gz);
+    if (gx >= ng || gy >= ng || gz >= ng) return -1;
+    return (gx + (int64_t)ng * (gy + (int64_t)ng * gz)) * kBoxesPerGroup;
+}
+// Place t in code order of a 4 x 4 x 4 block: x = t0 + 2 t3, y = t1 + 2 t4, z = t2 + 2 t5.
+__device__ __forceinline__ void block_place(int t, int &x, int &y, int &z) {
+    x = (t & 1) | ((t >> 2) & 2);
+    y = ((t >> 1) & 1) | ((t >> 3) & 2);
+    z = ((t >> 2) & 1) | ((t >> 4) & 2);
+}
+
+// Activation mask of the box at (bx, by, bz); 0 when it lies past the grid.
+__device__ __forceinline__ uint64_t box_mask(const uint64_t *__restrict__ act, int M, int W, int bx, int by, int bz) {
+    const int ox = 4 * bx, oy = 4 * by, oz = 4 * bz;
     if (ox >= M || oy >= M || oz >= M) return 0ull;
     const int nx = M - ox;
     const uint64_t xm = nx >= 4 ? 0xFull : ((1ull << nx) - 1ull);
@@ -552,17 +569,25 @@ __device__ __forceinline__ uint64_t box_mask(const uint64_t *__restrict__ act, i
 
 // Every box's mask, and the activated cells of every 64 boxes.
 __global__ __launch_bounds__(kTagBlock) void morton_count_kernel(const uint64_t *__restrict__ act, int M, int W,
-                                                                 int bits, int64_t n_codes,
-                                                                 uint64_t *__restrict__ mask,
+                                                                 int64_t n_groups, int ng, uint64_t *__restrict__ mask,
                                                                  uint32_t *__restrict__ cnt) {
-    const int64_t box = (int64_t)blockIdx.x * kTagBlock + threadIdx.x;
-    int ox, oy, oz;
-    const uint64_t m = box_mask(act, M, W, bits, box, n_codes, ox, oy, oz);
-    if (box * 64 < n_codes) mask[box] = m;
+    const int lane = threadIdx.x & 63;
+    const uint32_t group = blockIdx.x * (kTagBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (group >= n_groups) return;   // whole wavefronts
+    const int64_t at = group_masks(group, n_groups, ng);
+    if (at < 0) {
+        if (lane == 0) cnt[group] = 0u;
+        return;
+    }
+    int gx, gy, gz, bx, by, bz;
+    group_origin(group, gx, gy, gz);
+    block_place(lane, bx, by, bz);
+    const uint64_t m = box_mask(act, M, W, 4 * gx + bx, 4 * gy + by, 4 * gz + bz);
+    mask[at + lane] = m;
     uint32_t n = (uint32_t)__popcll(m);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d);
-    if ((threadIdx.x & 63) == 0 && box * 64 < n_codes) cnt[box / kBoxesPerGroup] = n;
+    if (lane == 0) cnt[group] = n;
 }
 
 // Writes the worklist and every package's position in it: a workgroup takes
@@ -580,23 +605,25 @@ constexpr int kScatterFewGroups = 2048;   // eight per CU: below, more wavefront
 
 __global__ __launch_bounds__(64 * kScatterWaves) void morton_scatter_kernel(const uint32_t *__restrict__ cell_pkg,
                                                                             const uint64_t *__restrict__ mask, int M,
-                                                                            int bits, int64_t n_boxes,
+                                                                            int64_t n_groups, int ng,
                                                                             const uint32_t *__restrict__ off,
                                                                             uint32_t *__restrict__ work,
                                                                             uint32_t *__restrict__ wpos) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
-    const int64_t box = (int64_t)blockIdx.x * kBoxesPerGroup + lane;
-    const uint64_t m = box < n_boxes ? mask[box] : 0ull;
+    const int64_t masks = group_masks(blockIdx.x, n_groups, ng);
+    if (masks < 0) return;
+    const uint64_t m = mask[masks + lane];
     uint64_t todo = __ballot(m != 0ull);
     if (!todo) return;   // the same for the whole workgroup
     const uint32_t n = (uint32_t)__popcll(m);
     const uint32_t pos = off[blockIdx.x] + wave_scan(n, lane) - n;
-    int ox = 0, oy = 0, oz = 0;
-    if (bits > 2) morton_decode(box, bits - 2, ox, oy, oz);
-    // code t of a box has lx = t0 + 2 t3, ly = t1 + 2 t4, lz = t2 + 2 t5
-    const int lx = (lane & 1) | ((lane >> 2) & 2), ly = ((lane >> 1) & 1) | ((lane >> 3) & 2),
-              lz = ((lane >> 2) & 1) | ((lane >> 4) & 2);
-    const int bit = lx + 4 * ly + 16 * lz;
+    int gx, gy, gz, bx, by, bz;
+    group_origin(blockIdx.x, gx, gy, gz);
+    block_place(lane, bx, by, bz);   // of a box in the group, and of a cell in its box
+    const int lx = bx, ly = by, lz = bz, bit = lx + 4 * ly + 16 * lz;
+    bx += 4 * gx;
+    by += 4 * gy;
+    bz += 4 * gz;
     for (int k = 0; k < wv * kBoxes && todo; ++k) todo &= todo - 1ull;
     while (todo) {   // the same for the whole wavefront
         uint32_t id[kBoxes], at[kBoxes];
@@ -610,7 +637,7 @@ __global__ __launch_bounds__(64 * kScatterWaves) void morton_scatter_kernel(cons
             on[k] = live && ((mk >> bit) & 1ull);
             const uint64_t placed = __ballot(on[k]);
             at[k] = (uint32_t)__shfl((int)pos, src) + (uint32_t)__popcll(placed & lanemask_lt());
-            const int x = 4 * __shfl(ox, src) + lx, y = 4 * __shfl(oy, src) + ly, z = 4 * __shfl(oz, src) + lz;
+            const int x = 4 * __shfl(bx, src) + lx, y = 4 * __shfl(by, src) + ly, z = 4 * __shfl(bz, src) + lz;
             id[k] = on[k] ? cell_pkg[x + (int64_t)M * (y + (int64_t)M * z)] : 0u;
         }
 #pragma unroll
@@ -925,8 +952,9 @@ namespace {
 // bitmaps (core, negative sign, activated), the per-group counts and the scan's
 // block sums; the masks, counts and block sums of the worklist's boxes.
 struct BuildWs {
-    int64_t W, n_words, n_groups, n_boxes;
-    int bits;   // of a Morton code per axis
+    int64_t W, n_words, n_groups;
+    int64_t n_box_groups;   // of the enclosing cube of codes
+    int ng;                 // box groups that meet the grid per axis
     uint64_t *core_bits, *neg_bits, *act_bits, *box_masks;
     uint32_t *ca, *cc, *part, *box_counts, *box_part;
 };
@@ -949,13 +977,13 @@ sgrid_status new_grid(int64_t M, double h, sgrid_grid **out, BuildWs &ws) {
     const size_t ws_bits = ((size_t)ws.n_words * 8 + 255) / 256 * 256;
     const size_t ws_counts = ((size_t)ws.n_groups * 4 + 255) / 256 * 256;
     const size_t ws_part = ((size_t)n_sblocks * 8 + 255) / 256 * 256;
-    ws.bits = 0;
-    while ((1ll << ws.bits) < M) ++ws.bits;
-    ws.n_boxes = ws.bits > 2 ? (int64_t)1 << (3 * (ws.bits - 2)) : 1;
-    const int64_t n_box_groups = (ws.n_boxes + kBoxesPerGroup - 1) / kBoxesPerGroup;
-    const size_t ws_masks = ((size_t)ws.n_boxes * 8 + 255) / 256 * 256;
-    const size_t ws_boxes = ((size_t)n_box_groups * 4 + 255) / 256 * 256;
-    const size_t ws_box_part = (size_t)((n_box_groups + kScanBlock - 1) / kScanBlock) * 4;
+    ws.ng = (int)((M + 15) / 16);
+    int64_t cube = 1;   // groups per axis of the enclosing cube of codes
+    while (cube < ws.ng) cube *= 2;
+    ws.n_box_groups = cube * cube * cube;
+    const size_t ws_masks = (size_t)ws.ng * ws.ng * ws.ng * kBoxesPerGroup * 8;
+    const size_t ws_boxes = ((size_t)ws.n_box_groups * 4 + 255) / 256 * 256;
+    const size_t ws_box_part = (size_t)((ws.n_box_groups + kScanBlock - 1) / kScanBlock) * 4;
     SG_ALLOC(g->workspace, 3 * ws_bits + 2 * ws_counts + ws_part + ws_masks + ws_boxes + ws_box_part, "build workspace");
     ws.core_bits = (uint64_t *)g->workspace;
     ws.neg_bits = (uint64_t *)((uint8_t *)ws.core_bits + ws_bits);
@@ -996,11 +1024,10 @@ sgrid_status fill_grid(sgrid_grid *g, const BuildWs &ws, hipStream_t st) {
     scan_counts(Counts<2>{{ca, cc}}, n_groups, part, host, st);
     SG_CHECK_HIP(hipGetLastError());
     // the worklist's boxes need no package ids: counted while the host waits
-    const int64_t n_box_groups = (ws.n_boxes + kBoxesPerGroup - 1) / kBoxesPerGroup;
-    hipLaunchKernelGGL(morton_count_kernel, dim3((unsigned)((ws.n_boxes + kTagBlock - 1) / kTagBlock)), dim3(kTagBlock),
-                       0, st, act_bits, (int)M, (int)W, ws.bits, ws.n_boxes * 64, ws.box_masks, ws.box_counts);
+    hipLaunchKernelGGL(morton_count_kernel, dim3((unsigned)((ws.n_box_groups * 64 + kTagBlock - 1) / kTagBlock)),
+                       dim3(kTagBlock), 0, st, act_bits, (int)M, (int)W, ws.n_box_groups, ws.ng, ws.box_masks, ws.box_counts);
     SG_CHECK_HIP(hipGetLastError());
-    scan_counts(Counts<1>{{ws.box_counts}}, n_box_groups, ws.box_part, nullptr, st);
+    scan_counts(Counts<1>{{ws.box_counts}}, ws.n_box_groups, ws.box_part, nullptr, st);
     SG_CHECK_HIP(hipGetLastError());
     SG_CHECK_HIP(wait_totals(host, st));
     g->P = (int64_t)host[0];
@@ -1024,9 +1051,9 @@ sgrid_status fill_grid(sgrid_grid *g, const BuildWs &ws, hipStream_t st) {
     SG_CHECK_HIP(hipGetLastError());
     SG_TRY_ALLOC(g->work, (g->P > 0 ? g->P : 1) * 4, "sweep worklist");
     SG_TRY_ALLOC(g->wpos, nt * 4, "worklist positions");
-    hipLaunchKernelGGL(morton_scatter_kernel, dim3((unsigned)n_box_groups),
-                       dim3(n_box_groups < kScatterFewGroups ? 64 * kScatterWaves : 32 * kScatterWaves), 0, st,
-                       g->cell_pkg, ws.box_masks, (int)M, ws.bits, ws.n_boxes, ws.box_counts, g->work, g->wpos);
+    hipLaunchKernelGGL(morton_scatter_kernel, dim3((unsigned)ws.n_box_groups),
+                       dim3(ws.n_box_groups < kScatterFewGroups ? 64 * kScatterWaves : 32 * kScatterWaves), 0, st,
+                       g->cell_pkg, ws.box_masks, (int)M, ws.n_box_groups, ws.ng, ws.box_counts, g->work, g->wpos);
     SG_CHECK_HIP(hipGetLastError());
     // group-relative face rows of the sweep order, through the position of
     // every package in the worklist (kept with the handle)
