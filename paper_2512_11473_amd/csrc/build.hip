@@ -912,10 +912,13 @@ uint64_t *pinned_totals() {
 // stream run, which a copy and a stream synchronisation would wait for (and
 // cost about 10 us more).  When the flag stays away the stream itself is
 // asked, so a failed launch or a stream being captured ends the wait with the
-// runtime's error.
+// runtime's error.  The thread looks for as long as the stream's earlier work
+// takes, as in the runtime's own synchronisation (behind 429 ms of products either
+// takes 429 ms of processor time).
 hipError_t wait_totals(uint64_t *host, hipStream_t st) {
     for (int spin = 0;; ++spin) {
         if (__atomic_load_n(host + 2, __ATOMIC_ACQUIRE) != 0) return hipSuccess;
+        __builtin_ia32_pause();
         if ((spin & 16383) == 16383) {
             const hipError_t e = hipStreamQuery(st);
             if (e != hipErrorNotReady) {
