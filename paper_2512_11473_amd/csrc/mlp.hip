@@ -629,9 +629,6 @@ static sgrid_status end_use(const sgrid_mlp *mc, hipStream_t st) {
     return SGRID_OK;
 }
 
-// Growing a buffer frees the old block, which kernels queued by earlier calls
-// (on any stream) may still use: wait for the device before handing it back
-// to the allocator, which may give it to the next request of that size.
 // How a batch is split: rounded up to whole chunks of kTrainChunk samples, at
 // most kMaxChunks of them (then longer ones).
 struct TrainSplit {
@@ -647,6 +644,10 @@ struct TrainSplit {
     }
 };
 
+// The training workspace for t, and the fallback list below: growing a buffer frees
+// the old block, which kernels queued by earlier calls (on any stream) may still use,
+// so the device is waited for before it goes back to the allocator, which may give it
+// to the next request of that size.
 static sgrid_status ensure_train(sgrid_mlp *m, const TrainSplit &t) {
     if (t.rows <= m->train_rows) return SGRID_OK;
     if (m->part || m->dys || m->tile_loss || m->acts) SG_CHECK_HIP(hipDeviceSynchronize());
