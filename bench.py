@@ -84,6 +84,11 @@ def sweep_source_hash() -> str:
     return h.hexdigest()[:16]
 
 
+def sweep_name(variant: int, groups: int) -> str:
+    """(0, 1) is the library's default, which takes variant 3 or 7 for large fields."""
+    return f"variant {variant}, groups {groups}" + (" (the default)" if (variant, groups) == (0, 1) else "")
+
+
 def measured_traffic(summary: str, key: str):
     """HBM bytes per launch of one kernel configuration (`key`) from a committed
     rocprofv3 counter summary under profiles/, when the summary was taken on
@@ -365,7 +370,7 @@ def bench_single(args, log):
         tv, tg = (int(x) for x in args.sweep.split(","))
         sg.set_sweep_config(tv, tg)
         tuned = {"variant": tv, "groups": tg, "source": "--sweep"}
-    log(f"sweep configuration: variant {tv}, groups {tg}")
+    log(f"sweep configuration: {sweep_name(tv, tg)}")
     P = wl.grid.n_packages
     n_core = wl.grid.n_core
     n_part = int(wl.pos.shape[0])
@@ -526,7 +531,7 @@ def bench_single(args, log):
                            "probe_ms": fprobe_ms, "probes_per_s": n_part / (fprobe_ms * 1e-3),
                            "note": "(K_W, h K_grad) at every activated point, then interpolated to the particles "
                                    "(generated order); measured outside the step"},
-        "roofline": {"bound": "hbm", "kernel": f"reinit sweep (variant {tv}, groups {tg})", "achieved": achieved,
+        "roofline": {"bound": "hbm", "kernel": f"reinit sweep ({sweep_name(tv, tg)})", "achieved": achieved,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": measured_traffic(f"reinit_sweep_{cfg['name']}_counters.txt", f"v{tv}g{tg}"),
                      "avg_launch_us": sweep_ms * 1e3, "algorithmic_bytes_per_launch": bytes_launch,
@@ -661,7 +666,7 @@ def bench_shell(args, log):
                      "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": lap_bytes / (lap_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                      "traffic": measured_traffic("laplacian_shell1024_counters.txt",
-                                                 "worklist" if tv in (3, 4) else "linear"),
+                                                 "worklist" if (tv, tg) == (0, 1) or tv in (2, 3, 4, 7) else "linear"),
                      "algorithmic_bytes_per_launch": lap_bytes},
         "sequential_roofline": {"achieved": seq_bytes / (seq_ms * 1e-3) / 1e9, "unit": "GB/s",
                                 "frac": seq_bytes / (seq_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,

@@ -642,9 +642,10 @@ SWEEP_TUNE_CANDIDATES = ((0, 1), (0, 2), (2, 4), (3, 1), (3, 2), (5, 1), (7, 1))
 
 
 def autotune_sweep(grid: "Grid", phi: torch.Tensor, scratch: torch.Tensor, reps: int = 10, stream=None):
-    """Times the sweep candidates on this grid (phi is read, scratch written),
-    makes the fastest the configuration and returns (variant, groups, us per
-    sweep for each of SWEEP_TUNE_CANDIDATES)."""
+    """Times the sweep candidates on this grid as calls run them (phi is read,
+    scratch written, and a buffer of its size taken meanwhile), the first one the
+    default; makes the fastest the configuration and returns (variant, groups, us
+    per sweep for each of SWEEP_TUNE_CANDIDATES)."""
     import numpy as np
     if scratch.dtype != phi.dtype or scratch.numel() != phi.numel() or phi.numel() != grid.n_total * 64:
         raise ValueError("phi and scratch must both be [P+2, 64] of one dtype")
@@ -657,6 +658,7 @@ def autotune_sweep(grid: "Grid", phi: torch.Tensor, scratch: torch.Tensor, reps:
 
 
 def set_sweep_config(variant: int, groups: int):
-    """Select the sweep kernel variant (0 = DPP exchange, 1 = LDS tile) and the
-    number of four-package sets each wavefront processes."""
+    """Select the sweep kernel variant (0 = DPP exchange, 1 = LDS tile, up to 7; see
+    sgrid.h) and the number of four-package sets each wavefront processes.  (0, 1)
+    is the default, with which the library itself chooses for large fields."""
     _check(load().sgrid_set_sweep_config(int(variant), int(groups)))
