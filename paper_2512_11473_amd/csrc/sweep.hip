@@ -1247,7 +1247,8 @@ static sgrid_status gradient_entry(const sgrid_grid *g, sgrid_dtype dtype, const
     constexpr double kGradientBytes = 96.0 * 1024 * 1024;
     const sgrid::SweepConfig cfg = sgrid::current_sweep_config();
     const bool follows = dtype == SGRID_F32 || (double)nt * 512.0 < kGradientBytes;
-    const bool work = (cfg.variant != 0 || follows) && sgrid::stencil_in_worklist_order(g, cfg, dtype == SGRID_F32 ? 4 : 8);
+    const bool work =
+        (cfg.variant != 0 || follows) && sgrid::stencil_in_worklist_order(g, cfg, dtype == SGRID_F32 ? 4 : 8);
     // streaming stores when phi and the output together exceed the last-level
     // cache; not for the FP64 packed layout, whose four stores per lane each
     // fill only parts of lines (the cache merges them, streaming writes would
