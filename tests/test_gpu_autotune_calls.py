@@ -3,6 +3,7 @@ Infinity Cache every candidate's time is that of its sweeps in a call of many,
 the first one the default's.  Timings of one card differ by a few percent; sweeps
 that all read one buffer were up to 40 % off.  phi is only read, and the picked
 configuration gives the bits of the default."""
+import numpy as np
 import pytest
 
 import synth
@@ -42,6 +43,7 @@ def test_autotuned_times_are_those_of_calls():
         call(5)
         assert torch.equal(wl.phi, want)
         assert (v, groups) == sg.SWEEP_TUNE_CANDIDATES[int(table.argmin())]
+        table = np.minimum(table, sg.autotune_sweep(g, wl.phi, wl.scratch, reps=20)[2])   # the calls' are the least of three
         for c, us in zip(sg.SWEEP_TUNE_CANDIDATES, table):
             sg.set_sweep_config(*c)
             in_call = min(call(40) for _ in range(3))
